@@ -444,7 +444,8 @@ static int build_slots(dd_ctx *h, hipStream_t st) {
         const int rpw = kWave / h->bs, cw = rpw * (1024 / kWave);
         h->seg = mb;  // the packing reads it
         for (int w = 0; w < 2; ++w) {
-            const int rc = build_seg_layout(h, w, mb, cw, rpw, st);
+            int rc = build_seg_layout(h, w, mb, cw, rpw, st);
+            if (!rc) rc = build_wave_chunks(h, w, st);
             if (rc) {
                 h->seg = 0;
                 return rc;
@@ -458,6 +459,7 @@ static int build_slots(dd_ctx *h, hipStream_t st) {
         RCHK(h->alloc(&s.desc, h->n));
         RCHK(h->alloc(&s.sval64, h->n * (h->slots + w) * bb));  // upper: + inv_D
         HCHK(launch_pack_slots(h, w, st));
+        RCHK(build_wave_chunks(h, w, st));
     }
     return DD_OK;
 }

@@ -23,12 +23,10 @@
 #include "internal.h"
 #include "spmv.h"
 
-// Prefetch depth (levels loaded ahead) of the slot-layout kernel, per factor
-// storage type.  Once wavefronts without rows skip their loads, a level's
-// time is mostly the latency of its own loads, which a deeper prefetch
-// hides.  FP64 factors stop at 2: at 3 the four register sets of the upper
-// sweep no longer fit the 128 registers a wavefront of a 1024-lane
-// workgroup may hold.
+// Prefetch depth (wave-chunks fetched ahead of the one computed) of the
+// slot-layout kernel, per factor storage type.  FP64 factors stop at 2: at 3
+// the four register sets of the upper sweep no longer fit the 128 registers a
+// wavefront of a 1024-lane workgroup may hold.
 #ifndef DDILU_PD64
 #define DDILU_PD64 2
 #endif
@@ -593,26 +591,37 @@ __global__ __launch_bounds__(NT) void k_dd_apply_pipe(
 // ------------------------------------------------------------------------
 // Variant 3: slot layout.  Position p's blocks sit in fixed slots
 // p*MB..p*MB+MB-1 (zero blocks pad short rows), and its row and columns sit
-// in one 64-bit descriptor.  No load depends on another load, so the loads of
-// level l+PD are issued while level l computes: PD+1 register sets rotate,
-// and the main loop is unrolled by PD+1 so that each set keeps its registers.
+// in one 64-bit descriptor.  No load depends on another load, so loads are
+// issued ahead: PD+1 register sets rotate, and the main loop is unrolled by
+// PD+1 so that each set keeps its registers.
 //
-// A wavefront holding no row of a level skips that level's loads (about half
-// of all wavefront-levels at 16x20x20 subdomains, whose levels run from 1 to
-// 256 rows): the loads would only return zeros, and they cost issue slots of
-// the vector memory pipeline the busy wavefronts need.  Because the number
-// of loads a wavefront has in flight then depends on the level, the loads
-// and their waits are written out here (the compiler's own waits, counted
-// over both sides of the skip, would wait for the prefetched level too).
-// The loads of one fetch are buffer loads behind one scalar branch on the
-// wavefront's busy flag.  Before level l computes, the wavefront waits until
-// only the loads of levels l+1..l+PD-1 it actually issued are outstanding,
-// and then passes the registers of level l through an empty asm statement
-// ("claim"), so that no read of them is scheduled before the wait.  The
-// compiler does not know these registers are being loaded: the build checks
-// the generated code, over its control-flow graph, for any instruction that
-// touches a register between the load into it and its claim (a copy or a
-// spill would read it before the data arrives).
+// A level's positions are cut into wave-chunks of one wavefront pass each
+// (64/BS rows), and the chunks of a sweep go round the wavefronts, level
+// after level.  A wavefront therefore always holds PD + 1 chunks of its own
+// in flight: in the narrow levels at either end of a sweep (at 16x20x20 the
+// levels run from 1 to 256 rows) those lie many levels ahead, where a
+// prefetch counted in levels (each wavefront owning the same rows of every
+// level) left the narrow levels waiting for memory one by one.  It also
+// makes every wait the same constant, needs no loads for absent rows, and
+// takes levels of any width.  What bounds it: HBM where all CUs stream
+// (256 boxes of 16x20x20: 5.46 TB/s algorithmic; 64 boxes out of the Infinity
+// Cache: 58 GB/s per CU), the level chain (barrier, LDS reads, FMAs, LDS
+// write: about 0.15 us a level) for small boxes.  Measured against the
+// per-level prefetch, us per apply: scalar 16^3 12.3 -> 8.6, scalar 128^3
+// 52.9 -> 39.0, 64^3 35.4 -> 31.6, 105x132x78 with FP32 factors and the
+// learned correction 135 -> 120, 128^3 the same way 148 -> 144, 160^3 FP64
+// 428.5 -> 425.8 and FP32 factors 260.3 -> 256.5, 4^3 boxes at 64^3 36.5 ->
+// 37.4.
+//
+// The loads and their waits are written out (the compiler's own waits cannot
+// span the barrier loop between a chunk's fetch and its use).  Before a chunk
+// computes, the wavefront waits until only the loads of its PD later fetches
+// are outstanding, and then passes the chunk's registers through an empty asm
+// statement ("claim"), so that no read of them is scheduled before the wait.
+// The compiler does not know these registers are being loaded: the build
+// checks the generated code, over its control-flow graph, for any
+// instruction that touches a register between the load into it and its claim
+// (a copy or a spill would read it before the data arrives).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -672,27 +681,11 @@ __device__ __forceinline__ void vm_load(uint32_t &d, uint32_t voff, const u32x4 
 // Wait until no vector memory operation is outstanding.
 __device__ __forceinline__ void vm_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Wait until at most n*K vector memory operations are outstanding (n = 0, 1
-// or 2, wavefront-uniform).
+// Wait until at most K vector memory operations are outstanding.
 template <int K>
-__device__ __forceinline__ void vm_wait_n(int n) {
-    static_assert(K >= 0 && 2 * K < 64, "vmcnt has six bits");
-    asm volatile(
-        "s_cmp_eq_u32 %[n], 0\n\t"
-        "s_cbranch_scc1 1f\n\t"
-        "s_cmp_eq_u32 %[n], 1\n\t"
-        "s_cbranch_scc1 2f\n\t"
-        "s_waitcnt vmcnt(%[k2])\n\t"
-        "s_branch 3f\n"
-        "2:\n\t"
-        "s_waitcnt vmcnt(%[k])\n\t"
-        "s_branch 3f\n"
-        "1:\n\t"
-        "s_waitcnt vmcnt(0)\n"
-        "3:"
-        :
-        : [n] "s"(__builtin_amdgcn_readfirstlane(n)), [k] "n"(K), [k2] "n"(2 * K)
-        : "scc", "memory");
+__device__ __forceinline__ void vm_wait() {
+    static_assert(K >= 0 && K < 64, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%[k])" : : [k] "n"(K) : "memory");
 }
 
 template <int I, int N>
@@ -716,20 +709,17 @@ struct LoadPieces<N, N> {
 // address outside its subdomain's slice).
 template <int BS, typename TS, int MB, bool UPPER>
 __device__ __forceinline__ void slot_fetch(SlotRegs<BS, TS, MB, UPPER> &R, const u32x4 &srd_desc,
-                                           const u32x4 &srd_val, int32_t p0, int32_t p1, int slot, bool lane_ok,
-                                           int c, int busy) {
+                                           const u32x4 &srd_val, int32_t p0, int cnt, int rl, int c) {
     using SR = SlotRegs<BS, TS, MB, UPPER>;
     using RR = RawRun<SR::NB>;
-    const int32_t p = p0 + slot;
-    R.ok = lane_ok && p < p1;
+    const int32_t p = p0 + rl;
+    R.ok = rl < cnt;
     const uint32_t pd = R.ok ? (uint32_t)p * 8u : kOobOffset;
     const uint32_t off = R.ok ? (uint32_t)((p * BS * SR::NV + c * SR::NV) * sizeof(TS)) : kOobOffset;
-    if (busy) {
-        vm_load<0>(R.desc, pd, srd_desc);
-        LoadPieces<0, RR::N16>::run(R.run, off, srd_val);
-        if constexpr (RR::T8) vm_load<16 * RR::N16>(R.run.h, off, srd_val);
-        if constexpr (RR::T4) vm_load<16 * RR::N16 + (RR::T8 ? 8 : 0)>(R.run.w, off, srd_val);
-    }
+    vm_load<0>(R.desc, pd, srd_desc);
+    LoadPieces<0, RR::N16>::run(R.run, off, srd_val);
+    if constexpr (RR::T8) vm_load<16 * RR::N16>(R.run.h, off, srd_val);
+    if constexpr (RR::T4) vm_load<16 * RR::N16 + (RR::T8 ? 8 : 0)>(R.run.w, off, srd_val);
 }
 
 // Orders every later read of R's registers after the preceding wait.
@@ -830,130 +820,134 @@ __device__ __forceinline__ void slot_compute(TC *__restrict__ y, const SlotRegs<
     }
 }
 
-// pbase, pcount: the subdomain's positions in the streams (s*S and S, or
-// the segmented layout's offset and count).  SEG: the level table is the
-// chunk table (starts in bits 0-29, bit 30 = barrier after the chunk).
+__device__ __forceinline__ int2 wave_entries(const int2 *__restrict__ tab, int n, int wave, int nw, int lane,
+                                             int first) {
+    return tab[max(min(wave + nw * (first + lane), n - 1), 0)];
+}
+
+// One sweep of one subdomain.  pbase, pcount: the subdomain's positions in
+// the streams (s*S and S, or the segmented layout's offset and count).  tab:
+// its n wave-chunks (see Sweep::wtab) in level order; wavefront w of nw
+// takes chunks w, w + nw, ...  Chunk k+1 of a wavefront may lie levels after
+// chunk k: in between it only joins the barriers.  ent: the wavefront's
+// first 64 table entries, one per lane (wave_entries); a step reads its own
+// by a lane read, so no memory access stands in the level chain.
 template <int BS, typename TS, typename TC, int MB, int PD, bool UPPER, bool SEG = false>
-__device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, int64_t pcount, int s,
-                                            const int32_t *__restrict__ off, const int32_t *__restrict__ lp,
-                                            const uint64_t *__restrict__ desc, const TS *__restrict__ sval,
-                                            int slot, int wrow0, bool lane_ok, int c) {
+__device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, int64_t pcount,
+                                            const int2 *__restrict__ tab, int n, int nlev, int2 ent,
+                                            const uint64_t *__restrict__ desc, const TS *__restrict__ sval, int wave,
+                                            int nw, int lane) {
     static_assert(PD >= 1 && PD <= 3, "prefetch depth 1 to 3");
     using SR = SlotRegs<BS, TS, MB, UPPER>;
     constexpr int PS = SR::NV * BS;  // values per position
-    constexpr int32_t QM = SEG ? 0x3fffffff : 0x7fffffff;
+    constexpr int RPW = kWave / BS;
+    if (n == 0) return;  // uniform over the workgroup
     const u32x4 srd_desc = slice_srd(desc + pbase, pcount * 8);
     const u32x4 srd_val = slice_srd(sval + pbase * PS, pcount * PS * (int64_t)sizeof(TS));
-    const int32_t o = off[s];
-    const int nl = off[s + 1] - o - 1;
+    const int rl = lane / BS < RPW ? lane / BS : kWave, c = lane % BS;  // a lane past the last row: never ok
+    const int steps = (n - wave + nw - 1) / nw;  // this wavefront's chunks (0 when it has none)
+    int tbase = 0, next = 0;
     SR R[PD + 1];
-    int busy[PD + 1], bar[PD + 1];
-    // level bounds are read one fetch ahead, so their scalar loads complete
-    // during a level's update instead of after the barrier that follows it
-    int32_t q0 = lp[o], q1 = lp[o + 1];
-    auto fetch = [&](int k, int l) {
-        const int32_t a0 = q0 & QM, a1 = q1 & QM;
-        bar[k] = SEG ? (q0 >> 30) & 1 : 1;
-        busy[k] = a0 + wrow0 < a1 ? 1 : 0;
-        slot_fetch<BS, TS, MB, UPPER>(R[k], srd_desc, srd_val, a0, a1, slot, lane_ok, c, busy[k]);
-        const int ln = l + 1 < nl ? l + 1 : nl - 1;
-        q0 = lp[o + ln];
-        q1 = lp[o + ln + 1];
+    int lev[PD + 1];
+    auto fetch = [&](int k) {
+        if (next >= tbase + kWave) {
+            tbase += kWave;
+            ent = wave_entries(tab, n, wave, nw, lane, tbase);
+            // the wait for this load stays inside the branch
+            asm volatile("s_waitcnt vmcnt(0)" : "+v"(ent.x), "+v"(ent.y) : : "memory");
+        }
+        const int32_t p0 = __builtin_amdgcn_readlane(ent.x, next & (kWave - 1));
+        const int32_t e = __builtin_amdgcn_readlane(ent.y, next & (kWave - 1));
+        lev[k] = e >> 8;
+        slot_fetch<BS, TS, MB, UPPER>(R[k], srd_desc, srd_val, p0, next < steps ? e & 0xff : 0, rl, c);
+        ++next;
     };
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(ent.x), "+v"(ent.y) : : "memory");
 #pragma unroll
-    for (int u = 0; u < PD; ++u) fetch(u, u);
-    const int nfull = nl - nl % (PD + 1);
-    for (int l0 = 0; l0 < nfull; l0 += PD + 1) {
+    for (int u = 0; u < PD; ++u)
+        fetch(u);
+    int cur = 0;  // levels passed
+    // A step: through the barriers up to its chunk's level, then the chunk.
+    // The next fetch goes into the set the step before freed, after the first
+    // barrier, where a wavefront that skips levels has nothing else to do.
+    // Past the last chunk the fetches are empty (offsets beyond the slice),
+    // so that every wait counts the same.
+    for (int i0 = 0; i0 < steps; i0 += PD + 1) {
 #pragma unroll
         for (int u = 0; u <= PD; ++u) {
-            // set u holds level l = l0+u; the loads issued after its own are
-            // those of levels l+1..l+PD-1 (sets u+1..u+PD-1), by the
-            // wavefronts that had rows there
-            if constexpr (PD == 3)
-                vm_wait_n<SR::NLOAD>(busy[(u + 1) % (PD + 1)] + busy[(u + 2) % (PD + 1)]);
-            else if constexpr (PD == 2)
-                vm_wait_n<SR::NLOAD>(busy[(u + 1) % (PD + 1)]);
-            else
-                vm_wait_all();
-            slot_claim(R[u]);
-            const int b = bar[u];
-            fetch((u + PD) % (PD + 1), l0 + u + PD);
-            slot_compute<BS, TS, TC, MB, UPPER, SEG>(y, R[u], c);
-            if (b) __syncthreads();
-        }
-    }
-    const int rem = nl - nfull;
-#pragma unroll
-    for (int u = 0; u < PD; ++u) {
-        if (u < rem) {
-            vm_wait_all();
+            if (i0 + u >= steps) break;
+            const int l = lev[u];
+            if (cur < l) {
+                __syncthreads();
+                ++cur;
+            }
+            fetch((u + PD) % (PD + 1));
+            for (; cur < l; ++cur) __syncthreads();
+            vm_wait<PD * SR::NLOAD>();  // set u is the oldest of the PD + 1 in flight
             slot_claim(R[u]);
             slot_compute<BS, TS, TC, MB, UPPER, SEG>(y, R[u], c);
-            if (bar[u]) __syncthreads();
         }
     }
     // nothing may still be loading into these registers once they are free
     vm_wait_all();
 #pragma unroll
     for (int u = 0; u <= PD; ++u) slot_claim(R[u]);
+    for (; cur < nlev; ++cur) __syncthreads();
 }
+
+// The tables a slot kernel walks: wave-chunks of each sweep and, per
+// subdomain, its entry of Sweep::winfo.
+struct SlotTabs {
+    const int2 *ltab, *utab;
+    const int4 *linfo, *uinfo;
+};
 
 // One subdomain's apply with the slot layout: r's slice into LDS (plus the
 // learned correction), the lower sweep, the upper sweep with the diagonal
 // scaling, and the slice back to z.
 template <int BS, typename TS, typename TC, int MB, int PD, bool LIC, bool SEG = false>
 __device__ __forceinline__ void apply_slots_sub(
-    TC *__restrict__ y, int s, const double *__restrict__ r, double *__restrict__ z, int S,
-    const int32_t *__restrict__ Loff, const int32_t *__restrict__ Llp, const uint64_t *__restrict__ Ldesc,
-    const TS *__restrict__ Lval, const int32_t *__restrict__ Uoff, const int32_t *__restrict__ Ulp,
-    const uint64_t *__restrict__ Udesc, const TS *__restrict__ Uval, const LicArgs &la,
-    const int32_t *__restrict__ Lgpos = nullptr, const int32_t *__restrict__ Ugpos = nullptr) {
-    constexpr int RPW = kWave / BS;
+    TC *__restrict__ y, int s, const double *__restrict__ r, double *__restrict__ z, int S, const SlotTabs &tabs,
+    const uint64_t *__restrict__ Ldesc, const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc,
+    const TS *__restrict__ Uval, const LicArgs &la, int stopped = 0, const int32_t *__restrict__ Lgpos = nullptr,
+    const int32_t *__restrict__ Ugpos = nullptr) {
     const int64_t base = (int64_t)s * S;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
-    const int c = lane % BS, rl = lane / BS;
-    const bool lane_ok = rl < RPW;
-    const int slot = wave * RPW + rl;
-
-    // the launch may use fewer threads than the kernel's bound: just enough
-    // wavefronts for the widest level, so no wavefront is idle at every level
-    const int nt = blockDim.x;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nt / kWave;
     const double *rs = r + base * BS;
+    // table entries of both sweeps: in flight behind the slice of r
+    const int4 li = tabs.linfo[s], ui = tabs.uinfo[s];
+    const int2 le = wave_entries(tabs.ltab + li.x, li.y, wave, nw, lane, 0);
+    const int2 ue = wave_entries(tabs.utab + ui.x, ui.y, wave, nw, lane, 0);
     LicState lst;
     LicPass<BS> lpass;
     if constexpr (LIC) lic_begin<BS>(lst, lpass, base, S, s, la, tid, nt);
     load_slice<TC, !LIC>(y, rs, S * BS, tid, nt);
     __syncthreads();
+    if (stopped != 0) return;  // read before the slice: its latency is not added to the slice's
     if constexpr (LIC) lic_finish<BS, TC>(y, r, lst, lpass, la, tid, nt);
-    const int wrow0 = __builtin_amdgcn_readfirstlane(wave) * RPW;  // first slot of this wavefront
-    if constexpr (SEG) {
-        const int64_t lb = Lgpos[s], ub = Ugpos[s];
-        sweep_slots<BS, TS, TC, MB, PD, false, true>(y, lb, Lgpos[s + 1] - lb, s, Loff, Llp, Ldesc, Lval, slot,
-                                                     wrow0, lane_ok, c);
-        sweep_slots<BS, TS, TC, MB, PD, true, true>(y, ub, Ugpos[s + 1] - ub, s, Uoff, Ulp, Udesc, Uval, slot,
-                                                    wrow0, lane_ok, c);
-    } else {
-        sweep_slots<BS, TS, TC, MB, PD, false>(y, base, S, s, Loff, Llp, Ldesc, Lval, slot, wrow0, lane_ok, c);
-        sweep_slots<BS, TS, TC, MB, PD, true>(y, base, S, s, Uoff, Ulp, Udesc, Uval, slot, wrow0, lane_ok, c);
-    }
+    const int64_t lb = SEG ? (int64_t)Lgpos[s] : base, ub = SEG ? (int64_t)Ugpos[s] : base;
+    const int64_t lc = SEG ? Lgpos[s + 1] - lb : S, uc = SEG ? Ugpos[s + 1] - ub : S;
+    sweep_slots<BS, TS, TC, MB, PD, false, SEG>(y, lb, lc, tabs.ltab + li.x, li.y, li.z, le, Ldesc, Lval, wave, nw,
+                                                lane);
+    sweep_slots<BS, TS, TC, MB, PD, true, SEG>(y, ub, uc, tabs.utab + ui.x, ui.y, ui.z, ue, Udesc, Uval, wave, nw,
+                                               lane);
     double *zs = z + base * BS;
     store_slice<TC, !LIC>(zs, y, S * BS, tid, nt);
 }
 
 template <int BS, typename TS, typename TC, int NT, int MB, int PD, bool LIC, bool SEG = false>
 __global__ __launch_bounds__(NT) void k_dd_apply_slots(
-    const double *__restrict__ r, double *__restrict__ z, int S, const int32_t *__restrict__ Loff,
-    const int32_t *__restrict__ Llp, const uint64_t *__restrict__ Ldesc, const TS *__restrict__ Lval,
-    const int32_t *__restrict__ Uoff, const int32_t *__restrict__ Ulp, const uint64_t *__restrict__ Udesc,
-    const TS *__restrict__ Uval, const int32_t *__restrict__ state, LicArgs la, int64_t vstride,
-    const int32_t *__restrict__ Lgpos, const int32_t *__restrict__ Ugpos) {
-    if (state != nullptr && *state != 0) return;
+    const double *__restrict__ r, double *__restrict__ z, int S, SlotTabs tabs, const uint64_t *__restrict__ Ldesc,
+    const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc, const TS *__restrict__ Uval,
+    const int32_t *__restrict__ state, LicArgs la, int64_t vstride, const int32_t *__restrict__ Lgpos,
+    const int32_t *__restrict__ Ugpos) {
+    const int stopped = state != nullptr ? *state : 0;  // enclosing solve already finished
     extern __shared__ unsigned char dd_smem[];
     // right-hand side blockIdx.y of a batch stored one after another
     const int64_t off = (int64_t)blockIdx.y * vstride;
     apply_slots_sub<BS, TS, TC, MB, PD, LIC, SEG>(reinterpret_cast<TC *>(dd_smem), blockIdx.x, r + off, z + off, S,
-                                                  Loff, Llp, Ldesc, Lval, Uoff, Ulp, Udesc, Uval, la, Lgpos, Ugpos);
+                                                  tabs, Ldesc, Lval, Udesc, Uval, la, stopped, Lgpos, Ugpos);
 }
 
 // ------------------------------------------------------------------------
@@ -1004,10 +998,9 @@ constexpr int kWaitMax = 1 << 18;     // polls per flag (each at least 256 cycle
 
 template <int BS, typename TS, typename TC, int NT, int MB, int PD, bool LIC, int MODE>
 __global__ __launch_bounds__(NT) void k_dd_apply_slots_spmv(
-    const double *__restrict__ r, double *__restrict__ z, int S, const int32_t *__restrict__ Loff,
-    const int32_t *__restrict__ Llp, const uint64_t *__restrict__ Ldesc, const TS *__restrict__ Lval,
-    const int32_t *__restrict__ Uoff, const int32_t *__restrict__ Ulp, const uint64_t *__restrict__ Udesc,
-    const TS *__restrict__ Uval, LicArgs la, FuseArgs f) {
+    const double *__restrict__ r, double *__restrict__ z, int S, SlotTabs tabs, const uint64_t *__restrict__ Ldesc,
+    const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc, const TS *__restrict__ Uval, LicArgs la,
+    FuseArgs f) {
     constexpr int NV = MODE == 0 ? 1 : 2;
     __shared__ int ticket;
     __shared__ double red[NV][16];
@@ -1025,8 +1018,8 @@ __global__ __launch_bounds__(NT) void k_dd_apply_slots_spmv(
     }
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     if (t < nsub) {
-        apply_slots_sub<BS, TS, TC, MB, PD, LIC>(reinterpret_cast<TC *>(dd_smem), t, r, z, S, Loff, Llp, Ldesc,
-                                                 Lval, Uoff, Ulp, Udesc, Uval, la);
+        apply_slots_sub<BS, TS, TC, MB, PD, LIC>(reinterpret_cast<TC *>(dd_smem), t, r, z, S, tabs, Ldesc, Lval,
+                                                 Udesc, Uval, la);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) __hip_atomic_store(f.flag + t, f.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1413,6 +1406,10 @@ static void launch_timed(dd_ctx *h, K kern, dim3 grid, int nt, int lds, hipStrea
     }
 }
 
+static SlotTabs slot_tabs(const dd_ctx *h) {
+    return SlotTabs{h->sw[0].wtab, h->sw[1].wtab, h->sw[0].winfo, h->sw[1].winfo};
+}
+
 template <int BS, typename TS, typename TC, int NT, int MB, bool LIC>
 static hipError_t launch_slots(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
                                const TS *lv, const TS *uv, int nrhs) {
@@ -1422,18 +1419,31 @@ static hipError_t launch_slots(dd_ctx *h, const double *r, double *z, const int3
     hipError_t e = allow_full_lds(kern, done);
     if (e != hipSuccess) return e;
     const int lds = h->S * BS * (int)sizeof(TC);
-    // wavefronts for the widest level (at most NT / 64)
-    constexpr int RPW = kWave / BS;
-    const int nt = std::max(kWave, std::min(NT, (h->max_level_width + RPW - 1) / RPW * kWave));
-    launch_timed(h, kern, dim3(h->nsub, nrhs), nt, lds, st, r, z, h->S, h->lev[0].off, h->lev[0].ptr,
-                 h->sw[0].desc, lv, h->lev[1].off, h->lev[1].ptr, h->sw[1].desc, uv, state, lic_args(h),
+    launch_timed(h, kern, dim3(h->nsub, nrhs), NT, lds, st, r, z, h->S, slot_tabs(h),
+                 (const uint64_t *)h->sw[0].desc, lv, (const uint64_t *)h->sw[1].desc, uv, state, lic_args(h),
                  (int64_t)h->n * BS, (const int32_t *)nullptr, (const int32_t *)nullptr);
     return hipGetLastError();
 }
 
-// The segmented slot layout (rows of more than three blocks): workgroups of
-// 1,024 lanes (the layout's chunks are cut for that width), chunk tables as
-// level tables, MB = the layout's blocks per segment (2 or 3).
+// Lanes of the slot kernel's workgroups: enough wavefronts for the widest
+// level, rounded up to a power of two, at most 8 and, where a CU holds one
+// workgroup only, at least 2.  More wavefronts deepen the prefetch (each
+// holds PD + 1 chunks) but every barrier waits for all of them.  Measured, us
+// per apply with 2 / 4 / 8 / 16 wavefronts: 160^3 in 16x20x20 boxes (levels
+// up to 256 rows) 459 / 425 / 423 / 427, with FP32 factors 344 / 259 / 251 /
+// 252; 64^3 in 8x8x16 (64 rows) 34.0 / 32.3 / 33.2 / 36.2; 48^3 in 8^3 (48
+// rows) 15.6 / 14.4 / 16.2 / 19.6; scalar 16^3 in 8^3 (48 rows, one chunk)
+// 8.9 / 9.0 / 9.4 / 11.3 and 11.7 with 1; 64^3 in 4^3 (12 rows, 16 workgroups
+// per CU) 42 / 52 / 85 / 170 and 37 with 1.
+static int slot_threads(const dd_ctx *h, int nrhs) {
+    const int rpw = kWave / h->bs;
+    int waves = h->nsub * (int64_t)nrhs <= 256 ? 2 : 1;
+    while (waves < 8 && waves * rpw <= h->max_level_width) waves *= 2;
+    return waves * kWave;
+}
+
+// The segmented slot layout (rows of more than three blocks); MB = the
+// layout's blocks per segment (2 or 3).
 template <int BS, typename TS, typename TC>
 static hipError_t launch_seg(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
                              const TS *lv, const TS *uv, int nrhs) {
@@ -1443,10 +1453,9 @@ static hipError_t launch_seg(dd_ctx *h, const double *r, double *z, const int32_
         if (e != hipSuccess) return e;
         const int lds = h->S * BS * (int)sizeof(TC);
         const Sweep &L = h->sw[0], &U = h->sw[1];
-        launch_timed(h, kern, dim3(h->nsub, nrhs), 1024, lds, st, r, z, h->S, (const int32_t *)L.gchk,
-                     (const int32_t *)L.chk, (const uint64_t *)L.desc, lv, (const int32_t *)U.gchk,
-                     (const int32_t *)U.chk, (const uint64_t *)U.desc, uv, state, lic_args(h), (int64_t)h->n * BS,
-                     (const int32_t *)L.gpos, (const int32_t *)U.gpos);
+        launch_timed(h, kern, dim3(h->nsub, nrhs), slot_threads(h, nrhs), lds, st, r, z, h->S,
+                     slot_tabs(h), (const uint64_t *)L.desc, lv, (const uint64_t *)U.desc, uv, state, lic_args(h),
+                     (int64_t)h->n * BS, (const int32_t *)L.gpos, (const int32_t *)U.gpos);
         return hipGetLastError();
     };
     static bool done2 = false, done3 = false;
@@ -1497,8 +1506,8 @@ static hipError_t launch_fused_k(dd_ctx *h, const double *r, double *z, const Fu
     const int lds = h->S * BS * (int)sizeof(TC);
     constexpr int RPW = kWave / BS;
     const int nt = std::max(kWave, std::min(1024, (h->max_level_width + RPW - 1) / RPW * kWave));
-    kern<<<2 * h->nsub, nt, lds, st>>>(r, z, h->S, h->lev[0].off, h->lev[0].ptr, h->sw[0].desc, lv, h->lev[1].off,
-                                       h->lev[1].ptr, h->sw[1].desc, uv, lic_args(h), f);
+    kern<<<2 * h->nsub, nt, lds, st>>>(r, z, h->S, slot_tabs(h), h->sw[0].desc, lv, h->sw[1].desc, uv, lic_args(h),
+                                       f);
     return hipGetLastError();
 }
 
@@ -1628,43 +1637,22 @@ static hipError_t launch_ablation(dd_ctx *h, int variant, const double *r, doubl
     return hipGetLastError();
 }
 
+// The kernels other than the slot kernel: apply variants 1, 2 and 4-8.
 template <int BS, typename TS, typename TC, int NT>
-static hipError_t launch_typed(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
-                               int nrhs) {
+static hipError_t launch_typed(dd_ctx *h, int variant, const double *r, double *z, const int32_t *state,
+                               hipStream_t st, int nrhs) {
     const Sweep &L = h->sw[0], &U = h->sw[1];
     const int lds = h->S * BS * (int)sizeof(TC);
-    constexpr int RPP = (kWave / BS) * (NT / kWave);
-    const bool one_pass = h->max_level_width <= RPP;
     const bool lic = BS == 3 && h->lic.active;
-    int variant = h->variant;
     if (variant >= 4) {
         if constexpr (sizeof(TS) == 8 && sizeof(TC) == 8)
             return launch_ablation<BS, NT>(h, variant, r, z, state, st);
         return hipErrorInvalidValue;  // rejected by the API before launch
     }
-    // automatic: the slot kernel where the shape allows it, else the plain
-    // loop (measured faster than the pipelined one on rows of up to 17
-    // blocks: 438 against 730 us at 2M unstructured rows)
-    if (variant == 0) variant = 3;
-    // rows of more than three blocks: the segmented slot layout
-    if (variant == 3 && h->seg && !lic) {
-        const TS *lv, *uv, *dv;
-        factor_ptrs<TS>(h, true, &lv, &uv, &dv);
-        return launch_seg<BS, TS, TC>(h, r, z, state, st, lv, uv, nrhs);
-    }
-    if (variant == 3 && (!one_pass || !h->slots)) variant = 1;
-    if (variant == 2 && lic) variant = 1;  // the correction runs in 1 and 3
-    if (variant == 3) {
-        const TS *lv, *uv, *dv;
-        factor_ptrs<TS>(h, true, &lv, &uv, &dv);
-        if constexpr (BS == 3)
-            if (lic) return launch_slots_mb<BS, TS, TC, NT, true>(h, r, z, state, st, lv, uv, nrhs);
-        return launch_slots_mb<BS, TS, TC, NT, false>(h, r, z, state, st, lv, uv, nrhs);
-    }
     if (nrhs > 1) {  // the other kernels take one right-hand side per launch
         const int64_t m = h->n * BS;
         for (int q = 0; q < nrhs; ++q) {
-            hipError_t e = launch_typed<BS, TS, TC, NT>(h, r + q * m, z + q * m, state, st, 1);
+            hipError_t e = launch_typed<BS, TS, TC, NT>(h, variant, r + q * m, z + q * m, state, st, 1);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -1710,22 +1698,55 @@ static int pick_threads(const dd_ctx *h) {
 }
 
 template <int BS, typename TS, typename TC>
-static hipError_t launch_nt(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st, int nrhs) {
+static hipError_t launch_nt(dd_ctx *h, int variant, const double *r, double *z, const int32_t *state, hipStream_t st,
+                            int nrhs) {
     switch (pick_threads(h)) {
-        case 64: return launch_typed<BS, TS, TC, 64>(h, r, z, state, st, nrhs);
-        case 128: return launch_typed<BS, TS, TC, 128>(h, r, z, state, st, nrhs);
-        case 256: return launch_typed<BS, TS, TC, 256>(h, r, z, state, st, nrhs);
-        case 512: return launch_typed<BS, TS, TC, 512>(h, r, z, state, st, nrhs);
-        default: return launch_typed<BS, TS, TC, 1024>(h, r, z, state, st, nrhs);
+        case 64: return launch_typed<BS, TS, TC, 64>(h, variant, r, z, state, st, nrhs);
+        case 128: return launch_typed<BS, TS, TC, 128>(h, variant, r, z, state, st, nrhs);
+        case 256: return launch_typed<BS, TS, TC, 256>(h, variant, r, z, state, st, nrhs);
+        case 512: return launch_typed<BS, TS, TC, 512>(h, variant, r, z, state, st, nrhs);
+        default: return launch_typed<BS, TS, TC, 1024>(h, variant, r, z, state, st, nrhs);
     }
+}
+
+template <int BS, typename TS, typename TC, bool LIC>
+static hipError_t launch_slots_nt(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
+                                  const TS *lv, const TS *uv, int nrhs) {
+    switch (slot_threads(h, nrhs)) {
+        case 64: return launch_slots_mb<BS, TS, TC, 64, LIC>(h, r, z, state, st, lv, uv, nrhs);
+        case 128: return launch_slots_mb<BS, TS, TC, 128, LIC>(h, r, z, state, st, lv, uv, nrhs);
+        case 256: return launch_slots_mb<BS, TS, TC, 256, LIC>(h, r, z, state, st, lv, uv, nrhs);
+        default: return launch_slots_mb<BS, TS, TC, 512, LIC>(h, r, z, state, st, lv, uv, nrhs);
+    }
+}
+
+// Automatic choice: the slot kernel where the layout exists (segmented for
+// rows of more than three blocks), else the plain loop (measured faster than
+// the pipelined one on rows of up to 17 blocks: 438 against 730 us at 2M
+// unstructured rows).
+template <int BS, typename TS, typename TC>
+static hipError_t launch_route(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
+                               int nrhs) {
+    int variant = h->variant == 0 ? 3 : h->variant;
+    const bool lic = BS == 3 && h->lic.active;
+    if (variant == 3 && (h->slots || (h->seg && !lic))) {
+        const TS *lv, *uv, *dv;
+        factor_ptrs<TS>(h, true, &lv, &uv, &dv);
+        if (h->seg) return launch_seg<BS, TS, TC>(h, r, z, state, st, lv, uv, nrhs);
+        if constexpr (BS == 3)
+            if (lic) return launch_slots_nt<BS, TS, TC, true>(h, r, z, state, st, lv, uv, nrhs);
+        return launch_slots_nt<BS, TS, TC, false>(h, r, z, state, st, lv, uv, nrhs);
+    }
+    if (variant == 3 || (variant == 2 && lic)) variant = 1;  // the correction runs in 1 and 3
+    return launch_nt<BS, TS, TC>(h, variant, r, z, state, st, nrhs);
 }
 
 template <int BS>
 static hipError_t launch_bs(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st, int nrhs) {
     switch (h->precision) {
-        case DD_FP32: return launch_nt<BS, float, float>(h, r, z, state, st, nrhs);
-        case DD_MIXED: return launch_nt<BS, float, double>(h, r, z, state, st, nrhs);
-        default: return launch_nt<BS, double, double>(h, r, z, state, st, nrhs);
+        case DD_FP32: return launch_route<BS, float, float>(h, r, z, state, st, nrhs);
+        case DD_MIXED: return launch_route<BS, float, double>(h, r, z, state, st, nrhs);
+        default: return launch_route<BS, double, double>(h, r, z, state, st, nrhs);
     }
 }
 
@@ -1739,24 +1760,13 @@ hipError_t launch_apply_batch(dd_ctx *h, const double *r, double *z, int nrhs, h
 }
 
 // a = M_DD^{-T} g: the slot kernel run on the transposed factor streams (FP64,
-// no correction); needs 3x3 blocks, the slot layout and one-pass levels.
-template <int NT>
-static hipError_t launch_adjoint_nt(dd_ctx *h, const double *g, double *a, int nrhs, hipStream_t st) {
-    constexpr int RPP = (kWave / 3) * (NT / kWave);
-    if (h->max_level_width > RPP) return hipErrorInvalidValue;
-    const double *lv = h->lic.adj_val[0], *uv = h->lic.adj_val[1];
-    return launch_slots_mb<3, double, double, NT, false>(h, g, a, nullptr, st, lv, uv, nrhs);
-}
-
+// no correction); needs 3x3 blocks, the slot layout and levels of at most
+// one pass of 1,024 lanes.
 hipError_t launch_apply_adjoint(dd_ctx *h, const double *g, double *a, int nrhs, hipStream_t st) {
     if (h->bs != 3 || !h->slots || !h->lic.ready || !h->lic.adj_val[1]) return hipErrorInvalidValue;
-    switch (pick_threads(h)) {
-        case 64: return launch_adjoint_nt<64>(h, g, a, nrhs, st);
-        case 128: return launch_adjoint_nt<128>(h, g, a, nrhs, st);
-        case 256: return launch_adjoint_nt<256>(h, g, a, nrhs, st);
-        case 512: return launch_adjoint_nt<512>(h, g, a, nrhs, st);
-        default: return launch_adjoint_nt<1024>(h, g, a, nrhs, st);
-    }
+    if (h->max_level_width > (kWave / 3) * (1024 / kWave)) return hipErrorInvalidValue;
+    const double *lv = h->lic.adj_val[0], *uv = h->lic.adj_val[1];
+    return launch_slots_nt<3, double, double, false>(h, g, a, nullptr, st, lv, uv, nrhs);
 }
 
 hipError_t launch_precond(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,

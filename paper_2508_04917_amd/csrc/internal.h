@@ -43,6 +43,12 @@ struct Sweep {
     double *sval64 = nullptr;   // [n*MB*bb] lower, [n*(MB+1)*bb] upper
     float *sval32 = nullptr;
     int64_t snpos = 0;          // positions of the slot layout (n, or the segmented layout's count)
+    // Wave-chunks of the slot layouts: a level's positions in pieces of one
+    // wavefront pass (64/bs rows), in sweep order; {first position (relative
+    // to the subdomain), level << 8 | positions}.  winfo[s]: subdomain s's
+    // first chunk, number of chunks, number of levels.
+    int2 *wtab = nullptr;
+    int4 *winfo = nullptr;
     // Segmented slot layout (rows of more than kMaxSlots blocks): a row is
     // split into segments at consecutive positions of one wavefront; levels
     // wider than a workgroup pass are cut into chunks.  With MB blocks per
@@ -237,6 +243,9 @@ hipError_t launch_pack_slots(dd_ctx *h, int which, hipStream_t st);
 // upper; chunk width cw positions, rpw per wavefront), then the values
 int build_seg_layout(dd_ctx *h, int which, int mb, int cw, int rpw, hipStream_t st);
 hipError_t launch_seg_pack(dd_ctx *h, int which, hipStream_t st);
+// the wave-chunk table of a sweep (from its level table, or from the
+// segmented layout's chunk table)
+int build_wave_chunks(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_max_count(int64_t n, const int32_t *cnt, int32_t *out, hipStream_t st);
 hipError_t launch_export_factors(dd_ctx *h, double *f, hipStream_t st);
 // out[k] = val[src[k]] for nblk blocks of bb values

@@ -907,6 +907,76 @@ int build_seg_layout(dd_ctx *h, int which, int mb, int cw, int rpw, hipStream_t 
     return DD_OK;
 }
 
+// Wave-chunks (see Sweep::wtab): one workgroup per subdomain walks its pieces
+// (levels, or the segmented layout's chunks, whose bit 30 ends a level) 256
+// at a time; a scan over the tile places each piece's chunks.  A
+// subdomain's chunks start at wbase: an upper bound of the chunks before it
+// (a piece of m positions has at most m/rpw + 1), so no count pass is needed.
+__global__ __launch_bounds__(256) void k_wave_chunks(int S, int rpw, int seg, const int32_t *__restrict__ off,
+                                                    const int32_t *__restrict__ lp, const int32_t *__restrict__ gpos,
+                                                    int2 *__restrict__ wtab, int4 *__restrict__ winfo) {
+    __shared__ int sh[65];
+    const int s = blockIdx.x;
+    const int32_t o = off[s];
+    const int np = off[s + 1] - o - 1;
+    const int64_t pos0 = seg ? (int64_t)gpos[s] : (int64_t)s * S;
+    const int32_t wbase = (int32_t)(pos0 / rpw) + s + o;
+    constexpr int32_t QM = 0x3fffffff;
+    int chunks = 0, level = 0;  // of the tiles before
+    for (int t0 = 0; t0 < np; t0 += blockDim.x) {
+        const int i = t0 + threadIdx.x;
+        int32_t q0 = 0, q1 = 0;
+        int m = 0, ends = 0;
+        if (i < np) {
+            const int32_t a = lp[o + i];
+            q0 = seg ? a & QM : a;
+            q1 = seg ? lp[o + i + 1] & QM : lp[o + i + 1];
+            m = (q1 - q0 + rpw - 1) / rpw;
+            ends = seg ? (a >> 30) & 1 : 1;
+        }
+        int tm, tl;
+        const int at = chunks + block_excl_scan(m, sh, &tm);
+        const int lv = level + block_excl_scan(ends, sh, &tl);
+        for (int k = 0; k < m; ++k) {
+            const int32_t p0 = q0 + k * rpw;
+            wtab[wbase + at + k] = make_int2(p0, lv << 8 | min(rpw, q1 - p0));
+        }
+        chunks += tm;
+        level += tl;
+    }
+    if (threadIdx.x == 0) winfo[s] = make_int4(wbase, chunks, level, 0);
+}
+
+int build_wave_chunks(dd_ctx *h, int which, hipStream_t st) {
+    Sweep &w = h->sw[which];
+    const Levels &L = h->lev[which];
+    const int rpw = kWave / h->bs;
+    const bool seg = h->seg != 0;
+    int32_t pieces = L.ptr_len;
+    if (seg) {
+        hipError_t e = hipMemcpyAsync(&pieces, w.gchk + h->nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return h->fail(DD_EHIP, "wave chunks: %s", hipGetErrorString(e));
+    }
+    for (void *q : {(void *)w.wtab, (void *)w.winfo}) {
+        auto it = std::find(h->allocs.begin(), h->allocs.end(), q);
+        if (q && it != h->allocs.end()) {
+            (void)hipFree(q);
+            h->allocs.erase(it);
+        }
+    }
+    w.wtab = nullptr;
+    w.winfo = nullptr;
+    int rc = h->alloc(&w.wtab, w.snpos / rpw + h->nsub + pieces + 1);
+    if (!rc) rc = h->alloc(&w.winfo, h->nsub);
+    if (rc) return rc;
+    k_wave_chunks<<<h->nsub, 256, 0, st>>>(h->S, rpw, seg ? 1 : 0, seg ? w.gchk : L.off, seg ? w.chk : L.ptr, w.gpos,
+                                           w.wtab, w.winfo);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return h->fail(DD_EHIP, "wave chunks: %s", hipGetErrorString(e));
+    return DD_OK;
+}
+
 // FP64 -> FP32 copies, round to nearest even.
 __global__ void k_cast32(int64_t m, const double *in, float *out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
