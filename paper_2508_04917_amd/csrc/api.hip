@@ -236,7 +236,7 @@ static int build_handle(dd_ctx *h, const int32_t *brow_ptr, const int32_t *bcol,
         delete h;
         return code;
     };
-    if ((rc = h->alloc(&h->status, 8))) return bail(rc);
+    if ((rc = h->alloc(&h->status, 32))) return bail(rc);
     h->scan_tmp_len = scan_tmp_elems(std::max<int64_t>(n, nnzb) + 1);
     if ((rc = h->alloc(&h->scan_tmp, h->scan_tmp_len))) return bail(rc);
     if ((rc = h->alloc(&h->part_id, n)) || (rc = h->alloc(&h->new2old, n)) || (rc = h->alloc(&h->old2new, n)) ||
@@ -276,7 +276,6 @@ static int build_handle(dd_ctx *h, const int32_t *brow_ptr, const int32_t *bcol,
         PCHK(launch_partition(h, st));
     }
     PCHK(launch_row_len(h, brow_ptr, len, st));
-    PCHK(launch_max_count(n, len, h->status + 6, st));  // longest row (selects the SpMV layout)
     PCHK(exclusive_scan(len, h->aptr, n, h->scan_tmp, st));
     int32_t total = 0, status[8];
     PCHK(hipMemcpyAsync(&total, h->aptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -290,12 +289,15 @@ static int build_handle(dd_ctx *h, const int32_t *brow_ptr, const int32_t *bcol,
         h->fail(DD_EINVAL, "brow_ptr describes %d blocks, nnzb says %lld", total, (long long)nnzb);
         return bail(DD_EINVAL);
     }
-    h->max_row_a = status[6];
-    PCHK(launch_reorder_fill(h, brow_ptr, bcol, val, src, st));
+    h->max_row_a = status[6];  // selects the SpMV layout
+    PCHK(launch_reorder_rows(h, brow_ptr, bcol, src, st));
+    build_spmv_layout(h, st);
+    PCHK(launch_values(h, val, src, st));
+    // later SpMVs may run on other streams: the copy is complete before any
+    // of them is enqueued
     PCHK(hipStreamSynchronize(st));
     release(h, len);
     h->asrc = src;  // kept for ilu0_refactor
-    build_spmv_layout(h, st);
     *out = h;
     return DD_OK;
 }
@@ -352,115 +354,147 @@ extern "C" int dd_get_reordered(dd_handle h, int32_t *ptr, int32_t *col, double 
 }
 
 // ----------------------------------------------------------------- factor
-static int build_levels(dd_ctx *h, int which, hipStream_t st, int32_t *tmp_i) {
-    Levels &L = h->lev[which];
-    if (!L.lev) {
-        RCHK(h->alloc(&L.lev, h->n));
-        RCHK(h->alloc(&L.nlev, h->nsub));
-        RCHK(h->alloc(&L.off, h->nsub + 1));
-        RCHK(h->alloc(&L.rows, h->n));
+// Level sets of both sweeps, the longest row and the block count of each.
+// stats: eight device words, zero.
+static int build_levels(dd_ctx *h, hipStream_t st, int32_t *stats, int32_t *tmp_i) {
+    if (!h->uinv) RCHK(h->alloc(&h->uinv, h->n));
+    for (int w = 0; w < 2; ++w) {
+        Levels &L = h->lev[w];
+        if (!L.lev) {
+            RCHK(h->alloc(&L.lev, h->n));
+            RCHK(h->alloc(&L.nlev, h->nsub));
+            RCHK(h->alloc(&L.off, h->nsub + 1));
+            RCHK(h->alloc(&L.rows, h->n));
+        }
     }
-    HCHK(launch_levels(h, which, st));
-    HCHK(launch_plus_one(h->nsub, L.nlev, tmp_i, st));
-    HCHK(exclusive_scan(tmp_i, L.off, h->nsub, h->scan_tmp, st));
-    int32_t total = 0;
-    HCHK(hipMemcpyAsync(&total, L.off + h->nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
-    if (L.ptr) release(h, L.ptr);
-    RCHK(h->alloc(&L.ptr, total));
-    L.ptr_len = total;
-    HCHK(launch_level_lists(h, which, st));
-    // host copies of the level offsets: largest level count and widest level
-    std::vector<int32_t> off(h->nsub + 1), lp(total);
-    HCHK(hipMemcpyAsync(off.data(), L.off, off.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(lp.data(), L.ptr, lp.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
-    int maxl = 0, maxw = 0;
-    for (int s = 0; s < h->nsub; ++s) {
-        const int nl = off[s + 1] - off[s] - 1;
-        maxl = std::max(maxl, nl);
-        for (int l = 0; l < nl; ++l) maxw = std::max(maxw, lp[off[s] + l + 1] - lp[off[s] + l]);
+    HCHK(launch_level_sets(h, stats, st));
+    int32_t total[2] = {0, 0}, got[8];
+    for (int w = 0; w < 2; ++w) {
+        Levels &L = h->lev[w];
+        HCHK(launch_plus_one(h->nsub, L.nlev, tmp_i, st));
+        HCHK(exclusive_scan(tmp_i, L.off, h->nsub, h->scan_tmp, st));
+        HCHK(hipMemcpyAsync(&total[w], L.off + h->nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     }
-    L.max_levels = maxl;
-    h->max_level_width = std::max(h->max_level_width, maxw);
+    HCHK(hipMemcpyAsync(got, stats, sizeof(got), hipMemcpyDeviceToHost, st));
+    HCHK(hipStreamSynchronize(st));
+    for (int w = 0; w < 2; ++w) {
+        Levels &L = h->lev[w];
+        if (L.ptr) release(h, L.ptr);
+        L.ptr = nullptr;
+        RCHK(h->alloc(&L.ptr, total[w]));
+        L.ptr_len = total[w];
+        L.max_levels = got[2 + w];
+        h->sw[w].max_row = got[w];
+        h->sw[w].nblk = got[6 + w];
+    }
+    HCHK(launch_level_lists(h, stats, st));
     return DD_OK;
 }
 
-static int build_sweep(dd_ctx *h, int which, hipStream_t st, int32_t *cnt) {
-    Sweep &w = h->sw[which];
-    const int bb = h->bs * h->bs;
-    if (!w.prow) {
-        RCHK(h->alloc(&w.prow, h->n));
-        RCHK(h->alloc(&w.bptr, h->n + 1));
-    }
-    HCHK(launch_pack_count(h, which, cnt, st));
-    HCHK(hipMemsetAsync(h->status + 4, 0, sizeof(int32_t), st));
-    HCHK(launch_max_count(h->n, cnt, h->status + 4, st));
-    HCHK(exclusive_scan(cnt, w.bptr, h->n, h->scan_tmp, st));
-    int32_t total = 0, maxrow = 0;
-    HCHK(hipMemcpyAsync(&total, w.bptr + h->n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(&maxrow, h->status + 4, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
-    if (w.bcol) { release(h, w.bcol); release(h, w.val64); w.bcol = nullptr; w.val64 = nullptr; }
-    if (w.uraw) { release(h, w.uraw); w.uraw = nullptr; }
-    if (w.val32) { release(h, w.val32); w.val32 = nullptr; }
-    w.nblk = total;
-    w.max_row = maxrow;
-    RCHK(h->alloc(&w.bcol, total));
-    RCHK(h->alloc(&w.val64, (int64_t)total * bb));
-    if (which == 1 && !w.d64) RCHK(h->alloc(&w.d64, h->n * bb));
-    HCHK(launch_pack_fill(h, which, st));
-    return DD_OK;
-}
-
-// Slot layout for both sweeps when no row has more than kMaxSlots blocks.
-static int build_slots(dd_ctx *h, hipStream_t st) {
-    const int bb = h->bs * h->bs;
+static void drop_csr(dd_ctx *h) {
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
-        if (s.desc) { release(h, s.desc); release(h, s.sval64); }
-        if (s.sval32) release(h, s.sval32);
-        s.desc = nullptr; s.sval64 = nullptr; s.sval32 = nullptr;
-        s.snpos = 0;
+        for (void *q : {(void *)s.bcol, (void *)s.val64, (void *)s.val32, (void *)s.uraw}) release(h, q);
+        s.bcol = nullptr; s.val64 = nullptr; s.val32 = nullptr; s.uraw = nullptr;
     }
-    const int mr = std::max(h->sw[0].max_row, h->sw[1].max_row);
-    h->slots = mr <= kMaxSlots ? std::max(mr, 1) : 0;
-    h->seg = 0;
-    if (!h->slots) {
-        // rows of more than three blocks: the segmented layout, for the apply's
-        // workgroups of 1,024 lanes, with segments of two blocks (the least
-        // zero padding on the row lengths of k-nearest-neighbour graphs:
-        // 1.18x the algorithmic bytes against 1.29x with three), or of three
-        // when a row would need more than kSegMax segments of two
-        const int lo = h->sw[0].max_row, up = h->sw[1].max_row;
-        auto fits = [&](int mb) { return lo <= mb * kSegMax && up <= mb + (kSegMax - 1) * (mb + 1); };
-        const int mb = fits(2) ? 2 : (fits(3) ? 3 : 0);
-        if (!mb) return DD_OK;
-        // the walk counts positions in 32-bit integers: a row takes at most
-        // kSegMax segments and kSegMax - 1 padding positions, so stay on the
-        // plain loop where that bound could pass 2^31
-        for (int w = 0; w < 2; ++w)
-            if ((int64_t)(h->sw[w].nblk + h->n) * (2 * kSegMax) >= ((int64_t)1 << 31)) return DD_OK;
-        const int rpw = kWave / h->bs, cw = rpw * (1024 / kWave);
-        h->seg = mb;  // the packing reads it
-        for (int w = 0; w < 2; ++w) {
-            int rc = build_seg_layout(h, w, mb, cw, rpw, st);
-            if (!rc) rc = build_wave_chunks(h, w, st);
-            if (rc) {
-                h->seg = 0;
-                return rc;
-            }
+    h->csr_ready = 0;
+}
+
+// Whether the apply variant (0: automatic) reads the CSR streams.
+static bool needs_csr(const dd_ctx *h) { return !h->slots || (h->variant != 0 && h->variant != 3); }
+
+// The sweeps in CSR form: what the apply variants other than the slot kernel
+// read, and what the segmented layout is packed from.  The slot kernel's
+// handles build them on demand.
+static int ensure_csr(dd_ctx *h, hipStream_t st) {
+    if (h->csr_ready) return DD_OK;
+    const int bb = h->bs * h->bs;
+    int32_t *cnt = nullptr;
+    RCHK(h->alloc(&cnt, h->n));
+    for (int w = 0; w < 2; ++w) {
+        Sweep &s = h->sw[w];
+        if (!s.prow) {
+            RCHK(h->alloc(&s.prow, h->n));
+            RCHK(h->alloc(&s.bptr, h->n + 1));
         }
-        return DD_OK;
+        HCHK(launch_pack_count(h, w, cnt, st));
+        HCHK(exclusive_scan(cnt, s.bptr, h->n, h->scan_tmp, st));
+        RCHK(h->alloc(&s.bcol, s.nblk));
+        RCHK(h->alloc(&s.val64, s.nblk * bb));
+        if (w == 1 && !s.d64) RCHK(h->alloc(&s.d64, h->n * bb));
+        HCHK(launch_pack_fill(h, w, st));
     }
+    HCHK(hipStreamSynchronize(st));
+    release(h, cnt);
+    h->csr_ready = 1;
+    return DD_OK;
+}
+
+// The segmented layout, where the slot layout does not hold the rows.
+static int build_seg(dd_ctx *h, hipStream_t st) {
+    // rows of more than three blocks: the segmented layout, for the apply's
+    // workgroups of 1,024 lanes, with segments of two blocks (the least
+    // zero padding on the row lengths of k-nearest-neighbour graphs:
+    // 1.18x the algorithmic bytes against 1.29x with three), or of three
+    // when a row would need more than kSegMax segments of two
+    const int lo = h->sw[0].max_row, up = h->sw[1].max_row;
+    auto fits = [&](int mb) { return lo <= mb * kSegMax && up <= mb + (kSegMax - 1) * (mb + 1); };
+    const int mb = fits(2) ? 2 : (fits(3) ? 3 : 0);
+    if (!mb) return DD_OK;
+    // the walk counts positions in 32-bit integers: a row takes at most
+    // kSegMax segments and kSegMax - 1 padding positions, so stay on the
+    // plain loop where that bound could pass 2^31
+    for (int w = 0; w < 2; ++w)
+        if ((int64_t)(h->sw[w].nblk + h->n) * (2 * kSegMax) >= ((int64_t)1 << 31)) return DD_OK;
+    const int rpw = kWave / h->bs, cw = rpw * (1024 / kWave);
+    h->seg = mb;  // the packing reads it
+    for (int w = 0; w < 2; ++w) {
+        int rc = build_seg_layout(h, w, mb, cw, rpw, st);
+        if (!rc) rc = build_wave_chunks(h, w, st);
+        if (rc) {
+            h->seg = 0;
+            return rc;
+        }
+    }
+    return DD_OK;
+}
+
+// Memory of the slot layout (every row has at most kMaxSlots blocks per
+// sweep), its descriptors, tables and factor records.
+static int build_slots(dd_ctx *h, int32_t *other, hipStream_t st) {
+    const int bb = h->bs * h->bs;
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
         s.snpos = h->n;
         RCHK(h->alloc(&s.desc, h->n));
         RCHK(h->alloc(&s.sval64, h->n * (h->slots + w) * bb));  // upper: + inv_D
-        HCHK(launch_pack_slots(h, w, st));
         RCHK(build_wave_chunks(h, w, st));
     }
+    if (!h->frec) RCHK(h->alloc(&h->frec, 2 * h->n));
+    HCHK(launch_slot_records(h, other, st));
+    return DD_OK;
+}
+
+static void drop_slots(dd_ctx *h) {
+    for (int w = 0; w < 2; ++w) {
+        Sweep &s = h->sw[w];
+        for (void *q : {(void *)s.desc, (void *)s.sval64, (void *)s.sval32}) release(h, q);
+        s.desc = nullptr; s.sval64 = nullptr; s.sval32 = nullptr;
+        s.snpos = 0;
+    }
+    h->slots = h->seg = h->direct = 0;
+}
+
+// The numeric factorisation from the reordered values, on the pattern the
+// handle holds: for the slot layout's usual patterns straight into its
+// streams, otherwise block ILU0 in the dropped pattern.
+static int factor_values(dd_ctx *h, hipStream_t st) {
+    if (h->direct) {
+        HCHK(launch_bilu0_slots(h, st));
+        return DD_OK;
+    }
+    HCHK(launch_gather_blocks(h->nnzt, h->bs * h->bs, h->tsrc, h->aval, h->lu, st));
+    HCHK(launch_bilu0(h, st));
     return DD_OK;
 }
 
@@ -468,12 +502,12 @@ static int ensure_fp32(dd_ctx *h, hipStream_t st) {
     const int bb = h->bs * h->bs;
     const bool sl = h->slots || h->seg;
     const int mb = h->seg ? h->seg : h->slots;
-    if (h->sw[0].val32 && h->sw[1].val32 && h->sw[1].d32 && (!sl || h->sw[0].sval32)) return DD_OK;
+    if ((!sl || h->sw[0].sval32) && (!h->csr_ready || (h->sw[1].val32 && h->sw[1].d32))) return DD_OK;
     for (int w = 0; w < 2; ++w) {
-        if (!h->sw[w].val32) RCHK(h->alloc(&h->sw[w].val32, h->sw[w].nblk * bb));
+        if (h->csr_ready && !h->sw[w].val32) RCHK(h->alloc(&h->sw[w].val32, h->sw[w].nblk * bb));
         if (sl && !h->sw[w].sval32) RCHK(h->alloc(&h->sw[w].sval32, h->sw[w].snpos * (mb + w) * bb));
     }
-    if (!h->sw[1].d32) RCHK(h->alloc(&h->sw[1].d32, h->n * bb));
+    if (h->csr_ready && !h->sw[1].d32) RCHK(h->alloc(&h->sw[1].d32, h->n * bb));
     HCHK(launch_cast32(h, st));
     return DD_OK;
 }
@@ -490,13 +524,13 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     int32_t *tbeg = nullptr, *tlen = nullptr, *tsrc = nullptr;
     RCHK(h->alloc(&tbeg, h->n));
     RCHK(h->alloc(&tlen, h->n + 1));
-    int32_t init_status[8] = {0, 0x7fffffff, 0x7fffffff, 0, 0, 0, 0, 0};
+    int32_t init_status[24] = {0, 0x7fffffff, 0x7fffffff};  // 8-15: level statistics, 16: other patterns
     HCHK(hipMemcpyAsync(h->status, init_status, sizeof(init_status), hipMemcpyHostToDevice, st));
     // drop (Section 3.2)
     HCHK(launch_drop_count(h, tbeg, tlen, st));
     if (!h->tptr) RCHK(h->alloc(&h->tptr, h->n + 1));
     HCHK(exclusive_scan(tlen, h->tptr, h->n, h->scan_tmp, st));
-    int32_t total = 0, status[8];
+    int32_t total = 0, status[24];
     HCHK(hipMemcpyAsync(&total, h->tptr + h->n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
@@ -505,7 +539,7 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
         return h->fail(DD_EZEROPIVOT, "block row %d has no diagonal block", status[1]);
     }
     h->nnzt = total;
-    h->nlow = h->nupp = (total - h->n) / 2;  // refined below from the sweeps
+    h->nlow = h->nupp = (total - h->n) / 2;  // refined below
     if (h->tcol) { release(h, h->tcol); release(h, h->lu); }
     RCHK(h->alloc(&h->tcol, total));
     RCHK(h->alloc(&h->lu, (int64_t)total * bb));
@@ -515,30 +549,36 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     h->tsrc = nullptr;
     RCHK(h->alloc(&tsrc, total));
     HCHK(launch_drop_rows(h, tbeg, tsrc, st));
-    // level sets (Section 4.2.1) for both factors
-    h->max_level_width = 0;
-    RCHK(build_levels(h, 0, st, tlen));
-    RCHK(build_levels(h, 1, st, tlen));
-    // block ILU0 (Algorithm 5), level-scheduled per subdomain
-    HCHK(launch_bilu0(h, st));
-    HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
     h->tsrc = tsrc;  // kept for ilu0_refactor
-    if (status[2] != 0x7fffffff) {
-        release(h, tbeg); release(h, tlen);
-        return h->fail(DD_EZEROPIVOT, "singular or ill-conditioned pivot block at reordered block row %d", status[2]);
-    }
-    // ILDU0 post-pass folded into the packing of the two sweeps
-    RCHK(build_sweep(h, 0, st, tlen));
-    RCHK(build_sweep(h, 1, st, tlen));
-    RCHK(build_slots(h, st));
+    drop_csr(h);
+    drop_slots(h);
+    // level sets (Section 4.2.1) for both factors
+    RCHK(build_levels(h, st, h->status + 8, tlen));
     h->nlow = h->sw[0].nblk;
     h->nupp = h->sw[1].nblk;
-    h->precision = precision;
-    if (precision != DD_FP64) RCHK(ensure_fp32(h, st));
+    const int mr = std::max(h->sw[0].max_row, h->sw[1].max_row);
+    h->slots = mr <= kMaxSlots ? std::max(mr, 1) : 0;
+    if (h->slots) RCHK(build_slots(h, h->status + 16, st));
+    HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
     release(h, tbeg);
     release(h, tlen);
+    h->max_level_width = status[8 + 4];
+    h->direct = h->slots && !status[16];
+    // block ILU0 (Algorithm 5), level-scheduled per subdomain, and the ILDU0
+    // post-pass folded into the packing of the two sweeps
+    RCHK(factor_values(h, st));
+    HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
+    HCHK(hipStreamSynchronize(st));
+    if (status[2] != 0x7fffffff)
+        return h->fail(DD_EZEROPIVOT, "singular or ill-conditioned pivot block at reordered block row %d", status[2]);
+    if (h->slots && !h->direct)
+        for (int w = 0; w < 2; ++w) HCHK(launch_pack_slots(h, w, st));
+    if (needs_csr(h)) RCHK(ensure_csr(h, st));
+    if (!h->slots) RCHK(build_seg(h, st));
+    h->precision = precision;
+    if (precision != DD_FP64) RCHK(ensure_fp32(h, st));
+    HCHK(hipStreamSynchronize(st));
     h->factored = 1;
     h->patterned = 1;
     return DD_OK;
@@ -549,7 +589,6 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     if (!val) return h->fail(DD_EINVAL, "ilu0_refactor: null values");
     if (!h->patterned || !h->asrc || !h->tsrc) return h->fail(DD_ESTATE, "ilu0_refactor before ilu0_factor");
     hipStream_t st = as_stream(hip_stream);
-    const int bb = h->bs * h->bs;
     h->factored = 0;
     // what depends on A's values and is rebuilt by its own call
     h->lic.adj_ready = 0;
@@ -558,30 +597,25 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     h->gfactored = 0;
     if (h->sw[1].uraw) { release(h, h->sw[1].uraw); h->sw[1].uraw = nullptr; }
     // values of the reordered matrix, its sliced ELL copy and the dropped pattern
-    HCHK(launch_gather_blocks(h->nnzb, bb, h->asrc, val, h->aval, st));
-    HCHK(refresh_spmv_layout(h, st));
-    HCHK(launch_gather_blocks(h->nnzt, bb, h->tsrc, h->aval, h->lu, st));
+    HCHK(launch_values(h, val, h->asrc, st));
     // block ILU0 on the kept level sets
     int32_t init_status[8] = {0, 0x7fffffff, 0x7fffffff, 0, 0, 0, 0, 0};
     HCHK(hipMemcpyAsync(h->status, init_status, sizeof(init_status), hipMemcpyHostToDevice, st));
-    HCHK(launch_bilu0(h, st));
+    RCHK(factor_values(h, st));
     int32_t status[8];
     HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
     if (status[2] != 0x7fffffff)
         return h->fail(DD_EZEROPIVOT, "singular or ill-conditioned pivot block at reordered block row %d", status[2]);
     // ILDU0 scaling and the streaming layouts, into the existing arrays
-    HCHK(launch_pack_fill(h, 0, st));
-    HCHK(launch_pack_fill(h, 1, st));
-    if (h->slots) {
-        HCHK(launch_pack_slots(h, 0, st));
-        HCHK(launch_pack_slots(h, 1, st));
-    }
+    for (int w = 0; w < 2 && h->csr_ready; ++w) HCHK(launch_pack_fill(h, w, st));
+    if (needs_csr(h)) RCHK(ensure_csr(h, st));
+    for (int w = 0; w < 2 && h->slots && !h->direct; ++w) HCHK(launch_pack_slots(h, w, st));
     if (h->seg) {
         HCHK(launch_seg_pack(h, 0, st));
         HCHK(launch_seg_pack(h, 1, st));
     }
-    if (h->sw[0].val32) HCHK(launch_cast32(h, st));
+    if (h->sw[0].val32 || h->sw[0].sval32) HCHK(launch_cast32(h, st));
     HCHK(hipStreamSynchronize(st));
     h->factored = 1;
     return DD_OK;
@@ -727,7 +761,19 @@ extern "C" int dd_set_lic_fallback(dd_handle h, int32_t on) {
 extern "C" int dd_set_apply_variant(dd_handle h, int32_t variant) {
     if (!h) return set_global_error(DD_EINVAL, "dd_set_apply_variant: null handle");
     if (variant < 0 || variant > 8) return h->fail(DD_EINVAL, "dd_set_apply_variant: variant must be 0..8");
+    const int32_t before = h->variant;
     h->variant = variant;
+    if (h->factored && needs_csr(h) && !h->csr_ready) {
+        // the factors are complete (every factorisation ends synchronised),
+        // and so are these streams before any stream can run the variant
+        int rc = ensure_csr(h, nullptr);
+        if (!rc && h->sw[0].sval32) rc = ensure_fp32(h, nullptr);
+        if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = h->fail(DD_EHIP, "dd_set_apply_variant: synchronise");
+        if (rc) {
+            h->variant = before;
+            return rc;
+        }
+    }
     return DD_OK;
 }
 

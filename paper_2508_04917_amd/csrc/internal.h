@@ -136,6 +136,10 @@ struct dd_ctx {
     double *invd = nullptr;     // [n*bb] inv(U_II), reordered row order
     ddilu::Levels lev[2];
     ddilu::Sweep sw[2];
+    int32_t *uinv = nullptr;      // [n] upper-sweep position of each row
+    int4 *frec = nullptr;         // [2n] factor records of the slot layout (k_factor_records)
+    int32_t direct = 0;           // factored by launch_bilu0_slots (frec valid for ilu0_refactor)
+    int32_t csr_ready = 0;        // the sweeps' CSR streams are built (variants 1, 2, 4-8; segmented layout)
     int32_t factored = 0;
     int32_t patterned = 0;        // drop, levels and streaming layouts built (ilu0_refactor may run)
     int32_t precision = DD_FP64;
@@ -161,7 +165,7 @@ struct dd_ctx {
     int32_t hist_len = 0;
     std::vector<hipEvent_t> events;
     // scratch
-    int32_t *status = nullptr;  // [4] device status words
+    int32_t *status = nullptr;  // [32] device status words
     int32_t *scan_tmp = nullptr;
     int64_t scan_tmp_len = 0;
     // Krylov workspace (allocated on first solve)
@@ -226,14 +230,19 @@ int graph_partition(dd_ctx *h, const int32_t *ptr, const int32_t *col, hipStream
 hipError_t launch_check_rows(int64_t n, int64_t nnzb, const int32_t *ptr, const int32_t *col, int32_t *status,
                              hipStream_t st);
 hipError_t launch_row_len(dd_ctx *h, const int32_t *ptr, int32_t *len, hipStream_t st);
-hipError_t launch_reorder_fill(dd_ctx *h, const int32_t *ptr, const int32_t *col,
-                               const double *val, int32_t *src, hipStream_t st);
+hipError_t launch_reorder_rows(dd_ctx *h, const int32_t *ptr, const int32_t *col, int32_t *src, hipStream_t st);
 hipError_t launch_drop_count(dd_ctx *h, int32_t *tbeg, int32_t *tlen, hipStream_t st);
 hipError_t launch_drop_rows(dd_ctx *h, const int32_t *tbeg, int32_t *tsrc, hipStream_t st);
-hipError_t launch_levels(dd_ctx *h, int which, hipStream_t st);
+// both sweeps' level sets; stats (zeroed, 8 words): most blocks of a row, most
+// levels, (by launch_level_lists) the widest level, blocks: [0,1], [2,3], [4], [6,7]
+hipError_t launch_level_sets(dd_ctx *h, int32_t *stats, hipStream_t st);
 hipError_t launch_plus_one(int64_t m, const int32_t *in, int32_t *out, hipStream_t st);
-hipError_t launch_level_lists(dd_ctx *h, int which, hipStream_t st);
+hipError_t launch_level_lists(dd_ctx *h, int32_t *stats, hipStream_t st);
 hipError_t launch_bilu0(dd_ctx *h, hipStream_t st);
+// slot descriptors and factor records; *other raised where launch_bilu0_slots
+// does not apply (see k_factor_records)
+hipError_t launch_slot_records(dd_ctx *h, int32_t *other, hipStream_t st);
+hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st);
 hipError_t launch_pack_count(dd_ctx *h, int which, int32_t *cnt, hipStream_t st);
 hipError_t launch_pack_fill(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_pack_unscaled(dd_ctx *h, hipStream_t st);
@@ -246,13 +255,13 @@ hipError_t launch_seg_pack(dd_ctx *h, int which, hipStream_t st);
 // the wave-chunk table of a sweep (from its level table, or from the
 // segmented layout's chunk table)
 int build_wave_chunks(dd_ctx *h, int which, hipStream_t st);
-hipError_t launch_max_count(int64_t n, const int32_t *cnt, int32_t *out, hipStream_t st);
 hipError_t launch_export_factors(dd_ctx *h, double *f, hipStream_t st);
 // out[k] = val[src[k]] for nblk blocks of bb values
 hipError_t launch_gather_blocks(int64_t nblk, int bb, const int32_t *src, const double *val, double *out,
                                 hipStream_t st);
-// rewrite the sliced ELL copy's values after A's values changed
-hipError_t refresh_spmv_layout(dd_ctx *h, hipStream_t st);
+// A's values in the reordered numbering (src: input block of each block) and
+// the sliced ELL copy's values, from the caller's values
+hipError_t launch_values(dd_ctx *h, const double *val, const int32_t *src, hipStream_t st);
 
 hipError_t launch_apply(dd_ctx *h, const double *r, double *z, const int32_t *state,
                         hipStream_t st);
@@ -269,7 +278,8 @@ const char *variant_unsupported(const dd_ctx *h, int v);
 
 // Krylov
 hipError_t launch_spmv(dd_ctx *h, const double *x, double *y, hipStream_t st);
-// the sliced ELL copy of A for the SpMV (once per handle; synchronises st)
+// memory and tables of the SpMV's sliced ELL copy of A (once per handle;
+// launch_values writes the copy)
 void build_spmv_layout(dd_ctx *h, hipStream_t st);
 hipError_t launch_permute(int64_t n, int bs, const int32_t *map, const double *in, double *out,
                           hipStream_t st);

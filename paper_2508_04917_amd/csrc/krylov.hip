@@ -57,25 +57,52 @@ __device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int
 // it reads one contiguous run (measured at 160^3: 441 -> 408 us per SpMV,
 // same bits).  One more copy of A's blocks (plus a zero block for each
 // position a row leaves empty); the CSR arrays stay for everything else.
-// One thread per value of the copy, so that consecutive threads write
-// consecutive words (the column of a slot is written by its first value's
-// thread).
+//
+// k_ell_values writes the reordered matrix's blocks and this copy in one pass
+// over the caller's values: a wavefront takes a group, one lane per value
+// (64 / (BS*BS) rows at a time), every load of the group in flight before the
+// first store.  HBM-bound: one read and two writes of A's blocks, the writes
+// of the CSR copy in pieces of one block (1.3x their bytes measured); 128^3
+// 3x3 blocks: gather 516 + copy 765 us as two kernels -> 1,075 us.
 template <int BS>
-__global__ __launch_bounds__(256) void k_ell_fill(int64_t n, const int32_t *__restrict__ ptr,
-                                                 const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                 int32_t *__restrict__ ecol, double *__restrict__ eval,
-                                                 int64_t nslots) {
-    constexpr int RPW = kWave / BS, BB = BS * BS;
-    const int64_t total = nslots * BB;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = t / BB, e = t % BB;
-        const int64_t r = i % RPW, gk = i / RPW, k = gk % kUnroll, g = gk / kUnroll;
-        const int64_t row = g * RPW + r;
-        int64_t b = -1;
-        if (row < n && ptr[row] + k < ptr[row + 1]) b = ptr[row] + k;
-        if (e == 0) ecol[i] = b >= 0 ? col[b] : -1;
-        eval[t] = b >= 0 ? val[b * BB + e] : 0.0;
+__global__ __launch_bounds__(256) void k_ell_values(int64_t n, int64_t ngroup, const int32_t *__restrict__ ptr,
+                                                   const int32_t *__restrict__ col,
+                                                   const int32_t *__restrict__ src, const double *__restrict__ val,
+                                                   double *__restrict__ aval, int32_t *__restrict__ ecol,
+                                                   double *__restrict__ eval) {
+    constexpr int RPW = kWave / BS, BB = BS * BS, LP = kWave / BB, NP = RPW / LP;
+    static_assert(NP * LP == RPW, "whole passes");
+    const int lane = threadIdx.x & (kWave - 1), e = lane % BB, q = lane / BB;
+    const int64_t nw = (int64_t)gridDim.x * (blockDim.x / kWave);
+    for (int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; g < ngroup; g += nw) {
+        int32_t b0[NP], len[NP], from[kUnroll][NP];
+        double v[kUnroll][NP];
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const int64_t row = g * RPW + m * LP + q;
+            const bool in = q < LP && row < n;
+            b0[m] = in ? ptr[row] : 0;
+            len[m] = in ? ptr[row + 1] - b0[m] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+#pragma unroll
+            for (int m = 0; m < NP; ++m) from[k][m] = k < len[m] ? src[b0[m] + k] : -1;
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+#pragma unroll
+            for (int m = 0; m < NP; ++m) v[k][m] = from[k][m] >= 0 ? val[(int64_t)from[k][m] * BB + e] : 0.0;
+        if (q >= LP) continue;
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+#pragma unroll
+            for (int m = 0; m < NP; ++m) {
+                const int64_t slot = (g * kUnroll + k) * RPW + m * LP + q;
+                const bool in = k < len[m];
+                eval[slot * BB + e] = v[k][m];
+                if (in) aval[(int64_t)(b0[m] + k) * BB + e] = v[k][m];
+                if (e == 0) ecol[slot] = in ? col[b0[m] + k] : -1;
+            }
     }
 }
 
@@ -201,21 +228,6 @@ __global__ __launch_bounds__(256) void k_sell_fill(int64_t nslice, const int32_t
     }
 }
 
-template <int BS>
-static void launch_ell_fill(dd_ctx *h, hipStream_t st) {
-    const int rpw = kWave / BS, bb = BS * BS;
-    const int64_t nslice = (h->n + rpw - 1) / rpw;
-    if (h->ell_state == 1 && h->sell_row) {
-        const unsigned g = (unsigned)std::min<int64_t>(h->sell_nslice, 1 << 20);
-        k_sell_fill<BS><<<g, 256, 0, st>>>(h->sell_nslice, h->aptr, h->acol, h->aval, h->sell_row, h->sell_len,
-                                           h->sell_off, h->ell_col, h->ell_val);
-        return;
-    }
-    const int64_t nslots = nslice * kUnroll * rpw;
-    const unsigned g = (unsigned)std::min<int64_t>((nslots * bb + 255) / 256, 1 << 20);  // grid-stride beyond
-    k_ell_fill<BS><<<g, 256, 0, st>>>(h->n, h->aptr, h->acol, h->aval, h->ell_col, h->ell_val, nslots);
-}
-
 // Whether the SpMV of a graph-partitioned matrix runs part by part with the
 // part's x in LDS (layout 3): scalar rows (each lane's x_J is an 8-byte
 // gather, a cache line of its own in the global-memory form; measured at
@@ -239,8 +251,9 @@ static bool part_local_spmv(const dd_ctx *h) {
 // slices aligned to the parts with per-slice widths (the SpMV then runs part
 // by part, the part's x in LDS); otherwise fixed width kUnroll when no row
 // is longer, per-slice widths with the rows ranked by length when one is.
-// Called at the end of the partition step (so its time counts as setup);
-// the SpMV entry points call it again, which does nothing once it has run.
+// Called in the partition step, before launch_values writes the copy (so its
+// time counts as setup); the SpMV entry points call it again, which does
+// nothing once it has run.
 void build_spmv_layout(dd_ctx *h, hipStream_t st) {
     if (h->ell_state != 0) return;
     h->ell_state = -1;
@@ -302,25 +315,32 @@ void build_spmv_layout(dd_ctx *h, hipStream_t st) {
         return;
     }
     h->ell_state = 1;
-    if (h->bs == 3)
-        launch_ell_fill<3>(h, st);
-    else
-        launch_ell_fill<1>(h, st);
-    // later SpMVs may run on other streams: the copy is complete before any
-    // of them is enqueued
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
-        h->ell_state = -1;
-        h->sell_row = nullptr;
-    }
 }
 
-// New values of A on the same pattern: rewrite the sliced ELL copy in place.
-hipError_t refresh_spmv_layout(dd_ctx *h, hipStream_t st) {
-    if (h->ell_state != 1) return hipSuccess;
+template <int BS>
+static void launch_values_bs(dd_ctx *h, const double *val, const int32_t *src, hipStream_t st) {
+    if (h->sell_row) {
+        const unsigned g = (unsigned)std::min<int64_t>(h->sell_nslice, 1 << 20);
+        k_sell_fill<BS><<<g, 256, 0, st>>>(h->sell_nslice, h->aptr, h->acol, h->aval, h->sell_row, h->sell_len,
+                                           h->sell_off, h->ell_col, h->ell_val);
+        return;
+    }
+    const int64_t ngroup = (h->n + kWave / BS - 1) / (kWave / BS);
+    const unsigned g = (unsigned)std::min<int64_t>((ngroup + 3) / 4, 1 << 20);  // grid-stride beyond
+    k_ell_values<BS><<<g, 256, 0, st>>>(h->n, ngroup, h->aptr, h->acol, src, val, h->aval, h->ell_col, h->ell_val);
+}
+
+// The reordered matrix's values, and the sliced ELL copy in whichever form
+// the handle has.
+hipError_t launch_values(dd_ctx *h, const double *val, const int32_t *src, hipStream_t st) {
+    if (h->ell_state != 1 || h->sell_row) {
+        hipError_t e = launch_gather_blocks(h->nnzb, h->bs * h->bs, src, val, h->aval, st);
+        if (e != hipSuccess || h->ell_state != 1) return e;
+    }
     if (h->bs == 3)
-        launch_ell_fill<3>(h, st);
+        launch_values_bs<3>(h, val, src, st);
     else
-        launch_ell_fill<1>(h, st);
+        launch_values_bs<1>(h, val, src, st);
     return hipGetLastError();
 }
 

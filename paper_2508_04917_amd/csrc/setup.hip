@@ -5,6 +5,7 @@
 // streaming layout of the apply.
 #include <algorithm>
 
+#include "blocks.h"
 #include "internal.h"
 
 namespace ddilu {
@@ -15,39 +16,6 @@ constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanT * kScanItems;
 
 int64_t scan_tmp_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
-
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int t = __shfl_up(v, d);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-// Block-wide exclusive scan; sh must hold 65 ints; every thread must call.
-__device__ int block_excl_scan(int v, int *sh, int *total) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int inc = wave_incl_scan(v);
-    if (lane == 63) sh[w] = inc;
-    __syncthreads();
-    int s = 0, si = 0;
-    if (w == 0) {
-        s = lane < nw ? sh[lane] : 0;
-        si = wave_incl_scan(s);
-    }
-    __syncthreads();
-    if (w == 0) {
-        if (lane < nw) sh[lane] = si - s;
-        if (lane == 63) sh[64] = si;
-    }
-    __syncthreads();
-    *total = sh[64];
-    int res = inc - v + sh[w];
-    __syncthreads();
-    return res;
-}
 
 __global__ __launch_bounds__(kScanT) void k_scan_tiles(const int32_t *in, int64_t n, int32_t *sums) {
     __shared__ int sh[65];
@@ -136,26 +104,65 @@ hipError_t launch_partition(dd_ctx *h, hipStream_t st) {
 }
 
 // --------------------------------------------------------------- reorder
-__global__ void k_row_len(int64_t n, const int32_t *ptr, const int32_t *new2old, int32_t *len,
-                          int32_t *status) {
+// Largest v of the workgroup, at most one atomic per workgroup (256 threads).
+__device__ __forceinline__ void block_atomic_max(int v, int32_t *out) {
+    __shared__ int wmax[4];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = max(v, __shfl_xor(v, d));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int m = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+        // a stale read only costs an atomic that does not change the maximum
+        if (m > *const_cast<volatile int32_t *>(out)) atomicMax(out, m);
+    }
+}
+
+// length of each reordered row; status[6] = the longest (one atomic per row
+// serialises on the address: 375 us at 2M rows)
+__global__ __launch_bounds__(256) void k_row_len(int64_t n, const int32_t *ptr, const int32_t *new2old, int32_t *len,
+                                                int32_t *status) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t o = new2old[i];
-    const int32_t l = ptr[o + 1] - ptr[o];
-    len[i] = l;
-    if (l < 0 || l > kMaxRowBlocks) atomicMax(&status[0], 1);
+    int32_t l = 0;
+    if (i < n) {
+        const int32_t o = new2old[i];
+        l = ptr[o + 1] - ptr[o];
+        len[i] = l;
+        if (l < 0 || l > kMaxRowBlocks) atomicMax(&status[0], 1);
+    }
+    block_atomic_max(l, &status[6]);
 }
 
 // One thread per new row: map columns old->new and sort the row's
-// (column, source block) pairs by column (insertion sort in place).
-__global__ void k_reorder_rows(int64_t n, const int32_t *ptr, const int32_t *col, const int32_t *new2old,
-                               const int32_t *old2new, const int32_t *aptr, int32_t *acol,
-                               int32_t *src) {
+// (column, source block) pairs by column.  Rows of at most kRankRow blocks
+// are sorted by counting (each pair's rank is the number of pairs before it,
+// ties by position), all loads of the row in flight together and no pair
+// moved twice; longer rows by insertion in place.
+constexpr int kRankRow = 8;
+
+__global__ void k_reorder_rows(int64_t n, const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
+                               const int32_t *__restrict__ new2old, const int32_t *__restrict__ old2new,
+                               const int32_t *__restrict__ aptr, int32_t *acol, int32_t *src) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t o = new2old[i];
     const int32_t b0 = ptr[o], len = ptr[o + 1] - b0;
     const int32_t d0 = aptr[i];
+    if (len <= kRankRow) {
+        int32_t c[kRankRow];
+#pragma unroll
+        for (int k = 0; k < kRankRow; ++k) c[k] = k < len ? old2new[col[b0 + k]] : 0x7fffffff;
+#pragma unroll
+        for (int k = 0; k < kRankRow; ++k) {
+            if (k >= len) continue;
+            int rank = 0;
+#pragma unroll
+            for (int j = 0; j < kRankRow; ++j) rank += (c[j] < c[k] || (c[j] == c[k] && j < k)) ? 1 : 0;
+            acol[d0 + rank] = c[k];
+            src[d0 + rank] = b0 + k;
+        }
+        return;
+    }
     for (int k = 0; k < len; ++k) {
         int32_t c = old2new[col[b0 + k]];
         int32_t s = b0 + k;
@@ -211,14 +218,10 @@ hipError_t launch_row_len(dd_ctx *h, const int32_t *ptr, int32_t *len, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_reorder_fill(dd_ctx *h, const int32_t *ptr, const int32_t *col, const double *val,
-                               int32_t *src, hipStream_t st) {
+hipError_t launch_reorder_rows(dd_ctx *h, const int32_t *ptr, const int32_t *col, int32_t *src, hipStream_t st) {
     const int T = 256;
     k_reorder_rows<<<(unsigned)((h->n + T - 1) / T), T, 0, st>>>(h->n, ptr, col, h->new2old, h->old2new,
                                                               h->aptr, h->acol, src);
-    const int bb = h->bs * h->bs;
-    const int64_t ne = h->nnzb * bb;
-    k_gather_blocks<<<(unsigned)((ne + T - 1) / T), T, 0, st>>>(ne, bb, src, val, h->aval);
     return hipGetLastError();
 }
 
@@ -275,182 +278,7 @@ hipError_t launch_drop_rows(dd_ctx *h, const int32_t *tbeg, int32_t *tsrc, hipSt
     const int T = 256;
     k_drop_rows<<<(unsigned)((h->n + T - 1) / T), T, 0, st>>>(h->n, tbeg, h->tptr, h->acol, h->tcol, tsrc,
                                                            h->tdiag);
-    const int bb = h->bs * h->bs;
-    const int64_t ne = h->nnzt * bb;
-    k_gather_blocks<<<(unsigned)((ne + T - 1) / T), T, 0, st>>>(ne, bb, tsrc, h->aval, h->lu);
     return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- levels
-// Section 4.2.1 (Algorithm 6 semantics): inside one subdomain (one
-// workgroup), rows without a dependency get level 0; then, round after
-// round, every row whose dependencies all have a level is promoted to
-// (round + 1).  A row is promoted in the first round after its last
-// dependency got its level, so its level is 1 + the largest level among its
-// dependencies: the longest dependency path.  which = 0: dependencies are
-// the columns J < I of row I (lower factor); which = 1: columns K > I
-// (upper factor).
-constexpr int32_t kUnassigned = 0x7fffffff;
-
-__global__ __launch_bounds__(256) void k_levels(int S, int which, const int32_t *tptr, const int32_t *tcol,
-                                                int32_t *lev_out, int32_t *nlev_out) {
-    extern __shared__ int32_t sm_lev[];
-    int32_t *lev = sm_lev;
-    uint8_t *mark = reinterpret_cast<uint8_t *>(sm_lev + S);
-    __shared__ int added;
-    const int64_t base = (int64_t)blockIdx.x * S;
-    for (int i = threadIdx.x; i < S; i += blockDim.x) {
-        const int64_t gi = base + i;
-        bool dep = false;
-        for (int32_t q = tptr[gi]; q < tptr[gi + 1]; ++q) {
-            const int32_t c = tcol[q];
-            if (which == 0 ? (c < gi) : (c > gi)) {
-                dep = true;
-                break;
-            }
-        }
-        lev[i] = dep ? kUnassigned : 0;
-        mark[i] = 0;
-    }
-    __syncthreads();
-    int level = 0;
-    while (true) {
-        if (threadIdx.x == 0) added = 0;
-        __syncthreads();
-        for (int i = threadIdx.x; i < S; i += blockDim.x) {
-            if (lev[i] != kUnassigned) continue;
-            const int64_t gi = base + i;
-            bool ok = true;
-            for (int32_t q = tptr[gi]; q < tptr[gi + 1]; ++q) {
-                const int32_t c = tcol[q];
-                if ((which == 0 ? (c < gi) : (c > gi)) && lev[c - base] == kUnassigned) {
-                    ok = false;
-                    break;
-                }
-            }
-            if (ok) {
-                mark[i] = 1;
-                added = 1;
-            }
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < S; i += blockDim.x)
-            if (mark[i]) {
-                lev[i] = level + 1;
-                mark[i] = 0;
-            }
-        __syncthreads();
-        const int a = added;
-        __syncthreads();
-        if (!a) break;
-        ++level;
-    }
-    for (int i = threadIdx.x; i < S; i += blockDim.x) lev_out[base + i] = lev[i];
-    if (threadIdx.x == 0) nlev_out[blockIdx.x] = level + 1;
-}
-
-__global__ void k_plus_one(int64_t m, const int32_t *in, int32_t *out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) out[i] = in[i] + 1;
-}
-
-// Explicit DAG (Section 4.2.2): per subdomain, level offsets and the rows
-// of each level in ascending local order (a stable counting sort by level,
-// done serially by one thread so the order is evident).
-__global__ void k_level_lists(int S, const int32_t *lev_g, const int32_t *nlev, const int32_t *off,
-                              int32_t *lptr, int32_t *rows) {
-    extern __shared__ int32_t sm_ll[];
-    int32_t *cnt = sm_ll;                                       // nl + 1
-    uint16_t *lv = reinterpret_cast<uint16_t *>(sm_ll + S + 1);  // S
-    const int s = blockIdx.x;
-    const int64_t base = (int64_t)s * S;
-    const int nl = nlev[s];
-    for (int i = threadIdx.x; i < S; i += blockDim.x) lv[i] = (uint16_t)lev_g[base + i];
-    for (int l = threadIdx.x; l <= nl; l += blockDim.x) cnt[l] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 0; i < S; ++i) cnt[lv[i] + 1]++;
-        for (int l = 0; l < nl; ++l) cnt[l + 1] += cnt[l];
-        const int32_t o = off[s];
-        for (int l = 0; l <= nl; ++l) lptr[o + l] = cnt[l];
-        for (int i = 0; i < S; ++i) rows[base + cnt[lv[i]]++] = i;
-    }
-}
-
-hipError_t launch_levels(dd_ctx *h, int which, hipStream_t st) {
-    Levels &L = h->lev[which];
-    const size_t lds = (size_t)h->S * 5;
-    k_levels<<<h->nsub, 256, lds, st>>>(h->S, which, h->tptr, h->tcol, L.lev, L.nlev);
-    return hipGetLastError();
-}
-
-hipError_t launch_plus_one(int64_t m, const int32_t *in, int32_t *out, hipStream_t st) {
-    const int T = 256;
-    k_plus_one<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, in, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_level_lists(dd_ctx *h, int which, hipStream_t st) {
-    Levels &L = h->lev[which];
-    const size_t lds = (size_t)(h->S + 1) * 4 + (size_t)h->S * 2;
-    k_level_lists<<<h->nsub, 64, lds, st>>>(h->S, L.lev, L.nlev, L.off, L.ptr, L.rows);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------ block math
-template <int BS>
-__device__ __forceinline__ void blk_mul(const double *A, const double *B, double *C) {
-#pragma unroll
-    for (int i = 0; i < BS; ++i)
-#pragma unroll
-        for (int j = 0; j < BS; ++j) {
-            double s = 0.0;
-#pragma unroll
-            for (int k = 0; k < BS; ++k) s += A[i * BS + k] * B[k * BS + j];
-            C[i * BS + j] = s;
-        }
-}
-
-template <int BS>
-__device__ __forceinline__ double blk_norm1(const double *A) {
-    double m = 0.0;
-#pragma unroll
-    for (int j = 0; j < BS; ++j) {
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < BS; ++i) s += fabs(A[i * BS + j]);
-        m = fmax(m, s);
-    }
-    return m;
-}
-
-// Inverse by the adjugate; false when the determinant vanishes, a value is
-// not finite, or the 1-norm condition number exceeds 1e14.
-template <int BS>
-__device__ bool blk_inverse(const double *a, double *inv) {
-    if constexpr (BS == 1) {
-        if (!(fabs(a[0]) > 0.0) || !isfinite(a[0])) return false;
-        inv[0] = 1.0 / a[0];
-        return true;
-    } else {
-        const double c00 = a[4] * a[8] - a[5] * a[7];
-        const double c01 = a[5] * a[6] - a[3] * a[8];
-        const double c02 = a[3] * a[7] - a[4] * a[6];
-        const double det = a[0] * c00 + a[1] * c01 + a[2] * c02;
-        if (!(fabs(det) > 0.0) || !isfinite(det)) return false;
-        const double id = 1.0 / det;
-        inv[0] = c00 * id;
-        inv[1] = (a[2] * a[7] - a[1] * a[8]) * id;
-        inv[2] = (a[1] * a[5] - a[2] * a[4]) * id;
-        inv[3] = c01 * id;
-        inv[4] = (a[0] * a[8] - a[2] * a[6]) * id;
-        inv[5] = (a[2] * a[3] - a[0] * a[5]) * id;
-        inv[6] = c02 * id;
-        inv[7] = (a[1] * a[6] - a[0] * a[7]) * id;
-        inv[8] = (a[0] * a[4] - a[1] * a[3]) * id;
-        const double cond = blk_norm1<3>(a) * blk_norm1<3>(inv);
-        return cond <= 1e14;
-    }
 }
 
 // ------------------------------------------------------------------ BILU0
@@ -656,18 +484,6 @@ __global__ void k_pack_slots(int64_t n, int S, int which, int MB, const int32_t 
 #pragma unroll
             for (int j = 0; j < BS; ++j) o[i * NV + MB * BS + j] = inv[i * BS + j];
     desc[p] = dsc;
-}
-
-// Largest per-row block count of a sweep (integer max, order-free).
-__global__ void k_max_count(int64_t n, const int32_t *cnt, int32_t *out) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < n) atomicMax(out, cnt[p]);
-}
-
-hipError_t launch_max_count(int64_t n, const int32_t *cnt, int32_t *out, hipStream_t st) {
-    const int T = 256;
-    k_max_count<<<(unsigned)((n + T - 1) / T), T, 0, st>>>(n, cnt, out);
-    return hipGetLastError();
 }
 
 hipError_t launch_pack_slots(dd_ctx *h, int which, hipStream_t st) {
@@ -988,11 +804,11 @@ hipError_t launch_cast32(dd_ctx *h, hipStream_t st) {
     const int bb = h->bs * h->bs;
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
-        const int64_t m = s.nblk * bb;
+        const int64_t m = s.val32 ? s.nblk * bb : 0;
         if (m) k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, s.val64, s.val32);
     }
     const int64_t m = h->n * bb;
-    k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, h->sw[1].d64, h->sw[1].d32);
+    if (h->sw[1].d32) k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, h->sw[1].d64, h->sw[1].d32);
     if (h->slots || h->seg) {
         const int mb = h->seg ? h->seg : h->slots;
         for (int w = 0; w < 2; ++w) {
