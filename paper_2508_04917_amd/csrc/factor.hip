@@ -449,6 +449,99 @@ __device__ __forceinline__ void row_times(const double (&v)[BS], const double (&
     }
 }
 
+// One row of the factorisation on its quad (or lane): everything it reads, and
+// where its parts go.  dg: A's position of the diagonal block (the row's
+// nlow lower and nupp upper blocks next to it), J: lower columns, back: A's
+// position of A_JI or -1, lo/uo: row c of the row's slot blocks.
+template <int BS, int MB>
+struct FactorRow {
+    int64_t gi, dg, J[MB];
+    int32_t back[MB];
+    int nlow, nupp;
+    double *lo, *uo;
+};
+
+template <int BS, int MB, bool LU>
+__device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, bool ok, int c, bool store, bool first,
+                                           const double *__restrict__ aval, double *__restrict__ lrow, double *invd,
+                                           int32_t *status) {
+    constexpr int BB = BS * BS;
+    auto load = [&](const double *p, double (&v)[BS]) {
+#pragma unroll
+        for (int j = 0; j < BS; ++j) v[j] = p[j];
+    };
+    auto put = [&](double *p, const double (&v)[BS]) {
+#pragma unroll
+        for (int j = 0; j < BS; ++j) p[j] = v[j];
+    };
+    double D[BS], a[MB][BS], t[MB][BS], b[MB][BS], iv[MB][BS];
+    load(aval + R.dg * BB + c * BS, D);
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+        const bool in = k < R.nlow;
+        load(aval + (in ? R.dg - R.nlow + k : R.dg) * BB + c * BS, a[k]);
+        load(aval + (R.back[k] >= 0 ? (int64_t)R.back[k] : R.dg) * BB + c * BS, t[k]);
+        load(aval + (k < R.nupp ? R.dg + 1 + k : R.dg) * BB + c * BS, b[k]);
+        load(invd + (in ? R.J[k] : R.gi) * BB + c * BS, iv[k]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+        double L[BS], w[BS];
+        row_times<BS>(a[k], iv[k], L);
+        row_times<BS>(L, t[k], w);
+        const bool in = k < R.nlow;
+#pragma unroll
+        for (int j = 0; j < BS; ++j) {
+            L[j] = in ? L[j] : 0.0;
+            D[j] = in && R.back[k] >= 0 ? D[j] - w[j] : D[j];
+        }
+        if (ok && store) {
+            put(R.lo + k * BS, L);
+            if (LU && in) put(lrow + k * BB, L);
+        }
+    }
+    double piv[BB], inv[BB], ic[BS];
+#pragma unroll
+    for (int j = 0; j < BS; ++j) {
+        if constexpr (BS == 1) {
+            piv[0] = D[0];
+        } else {
+            piv[j] = quad_bcast<0>(D[j]);
+            piv[BS + j] = quad_bcast<1>(D[j]);
+            piv[2 * BS + j] = quad_bcast<2>(D[j]);
+        }
+    }
+    if (!blk_inverse<BS>(piv, inv)) {
+        if (ok && first) atomicMin(&status[2], (int32_t)R.gi);
+#pragma unroll
+        for (int e = 0; e < BB; ++e) inv[e] = (e % (BS + 1) == 0) ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < BS; ++j) {  // row c of the inverse
+        ic[j] = inv[j];
+#pragma unroll
+        for (int i = 1; i < BS; ++i) ic[j] = c == i ? inv[i * BS + j] : ic[j];
+    }
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+        double u[BS];
+        row_times<BS>(ic, b[k], u);
+        const bool in = k < R.nupp;
+#pragma unroll
+        for (int j = 0; j < BS; ++j) u[j] = in ? u[j] : 0.0;
+        if (ok && store) {
+            put(R.uo + k * BS, u);
+            if (LU && in) put(lrow + (R.nlow + 1 + k) * BB, b[k]);
+        }
+    }
+    if (ok && store) {
+        put(R.uo + MB * BS, ic);
+        put(invd + R.gi * BB + c * BS, ic);
+        if (LU) put(lrow + R.nlow * BB, D);
+    }
+}
+
 template <int BS, int MB>
 __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__restrict__ off,
                                                     const int32_t *__restrict__ lptr,
@@ -464,14 +557,6 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
     const int rl = lane / LR, c = min(lane % LR, BS - 1);
     const bool store = lane % LR < BS;
-    auto load = [&](const double *p, double (&v)[BS]) {
-#pragma unroll
-        for (int j = 0; j < BS; ++j) v[j] = p[j];
-    };
-    auto put = [&](double *p, const double (&v)[BS]) {
-#pragma unroll
-        for (int j = 0; j < BS; ++j) p[j] = v[j];
-    };
     int32_t p0 = lptr[o];
     for (int l = 0; l < nl; ++l) {
         const int32_t p1 = lptr[o + l + 1];
@@ -481,82 +566,67 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
             const int64_t gp = base + (ok ? p : p0);
             const int4 r0 = rec[2 * gp], r1 = rec[2 * gp + 1];
             const uint64_t d = desc[gp];
-            const int nlow = r0.w & 0xff, nupp = r0.w >> 8;
+            FactorRow<BS, MB> R;
+            R.nlow = r0.w & 0xff;
+            R.nupp = r0.w >> 8;
+            R.gi = base + (int)(d & 0xffff);
+            R.dg = r0.x + R.nlow;
             const int32_t back[3] = {r1.x, r1.y, r1.z};
-            const int64_t gi = base + (int)(d & 0xffff);
-            const int64_t dg = r0.x + nlow;
-            double D[BS], a[MB][BS], t[MB][BS], b[MB][BS], iv[MB][BS];
-            load(aval + dg * BB + c * BS, D);
 #pragma unroll
             for (int k = 0; k < MB; ++k) {
-                const int64_t J = k < nlow ? base + (int)((d >> (16 * (k + 1))) & 0xffff) : gi;
-                load(aval + (k < nlow ? r0.x + k : dg) * BB + c * BS, a[k]);
-                load(aval + (back[k] >= 0 ? back[k] : dg) * BB + c * BS, t[k]);
-                load(aval + (k < nupp ? dg + 1 + k : dg) * BB + c * BS, b[k]);
-                load(invd + J * BB + c * BS, iv[k]);
+                R.J[k] = base + (int)((d >> (16 * (k + 1))) & 0xffff);
+                R.back[k] = back[k];
             }
-            __builtin_amdgcn_sched_barrier(0);
-            double *lo = lval + (gp * BS + c) * NL, *lr = lu + (int64_t)r0.y * BB + c * BS;
-#pragma unroll
-            for (int k = 0; k < MB; ++k) {
-                double L[BS], w[BS];
-                row_times<BS>(a[k], iv[k], L);
-                row_times<BS>(L, t[k], w);
-                const bool in = k < nlow;
-#pragma unroll
-                for (int j = 0; j < BS; ++j) {
-                    L[j] = in ? L[j] : 0.0;
-                    D[j] = in && back[k] >= 0 ? D[j] - w[j] : D[j];
-                }
-                if (ok && store) {
-                    put(lo + k * BS, L);
-                    if (in) put(lr + k * BB, L);
-                }
-            }
-            double piv[BB], inv[BB], ic[BS];
-#pragma unroll
-            for (int j = 0; j < BS; ++j) {
-                if constexpr (BS == 1) {
-                    piv[0] = D[0];
-                } else {
-                    piv[j] = quad_bcast<0>(D[j]);
-                    piv[BS + j] = quad_bcast<1>(D[j]);
-                    piv[2 * BS + j] = quad_bcast<2>(D[j]);
-                }
-            }
-            if (!blk_inverse<BS>(piv, inv)) {
-                if (ok && lane % LR == 0) atomicMin(&status[2], (int32_t)gi);
-#pragma unroll
-                for (int e = 0; e < BB; ++e) inv[e] = (e % (BS + 1) == 0) ? 1.0 : 0.0;
-            }
-#pragma unroll
-            for (int j = 0; j < BS; ++j) {  // row c of the inverse
-                ic[j] = inv[j];
-#pragma unroll
-                for (int i = 1; i < BS; ++i) ic[j] = c == i ? inv[i * BS + j] : ic[j];
-            }
-            double *uo = uval + ((int64_t)r0.z * BS + c) * NU;
-#pragma unroll
-            for (int k = 0; k < MB; ++k) {
-                double u[BS];
-                row_times<BS>(ic, b[k], u);
-                const bool in = k < nupp;
-#pragma unroll
-                for (int j = 0; j < BS; ++j) u[j] = in ? u[j] : 0.0;
-                if (ok && store) {
-                    put(uo + k * BS, u);
-                    if (in) put(lr + (nlow + 1 + k) * BB, b[k]);
-                }
-            }
-            if (ok && store) {
-                put(uo + MB * BS, ic);
-                put(invd + gi * BB + c * BS, ic);
-                put(lr + nlow * BB, D);
-            }
+            R.lo = lval + (gp * BS + c) * NL;
+            R.uo = uval + ((int64_t)r0.z * BS + c) * NU;
+            factor_row<BS, MB, true>(R, ok, c, store, lane % LR == 0, aval, lu + (int64_t)r0.y * BB + c * BS, invd,
+                                     status);
         }
         p0 = p1;
         __syncthreads();
     }
+}
+
+// The same for the rows of one level of the undecomposed matrix (global ILU0):
+// records {row, A's diagonal position, nlow | nupp << 8, lower-sweep
+// position}, {J0, J1, J2, upper-sweep position}, {A's positions of A_JI, 0} in level order;
+// three slots.
+template <int BS>
+__global__ __launch_bounds__(256) void k_gfactor_slots(int32_t p0, int32_t p1, const int4 *__restrict__ rec,
+                                                      const double *__restrict__ aval, double *invd,
+                                                      double *__restrict__ lval, double *__restrict__ uval,
+                                                      int32_t *status) {
+    constexpr int LR = BS == 3 ? 4 : 1, MB = kMaxSlots;
+    const int lane = threadIdx.x & (kWave - 1), c = min(lane % LR, BS - 1);
+    const int32_t p = p0 + (int32_t)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / LR);
+    const bool ok = p < p1;
+    const int64_t q = 3 * (int64_t)(ok ? p : p0);
+    const int4 r0 = rec[q], r1 = rec[q + 1], r2 = rec[q + 2];
+    FactorRow<BS, MB> R;
+    R.gi = r0.x;
+    R.dg = r0.y;
+    R.nlow = r0.z & 0xff;
+    R.nupp = r0.z >> 8;
+    R.J[0] = r1.x; R.J[1] = r1.y; R.J[2] = r1.z;
+    R.back[0] = r2.x; R.back[1] = r2.y; R.back[2] = r2.z;
+    R.lo = lval + ((int64_t)r0.w * BS + c) * MB * BS;
+    R.uo = uval + ((int64_t)r1.w * BS + c) * (MB + 1) * BS;
+    factor_row<BS, MB, false>(R, ok, c, lane % LR < BS, lane % LR == 0, aval, nullptr, invd, status);
+}
+
+// One launch per level of the lower sweep (host offsets lp[0..nlev]).
+hipError_t launch_gfactor_slots(dd_ctx *h, const std::vector<int32_t> &lp, hipStream_t st) {
+    const int lr = h->bs == 3 ? 4 : 1;
+    for (size_t l = 0; l + 1 < lp.size(); ++l) {
+        const unsigned g = (unsigned)(((int64_t)(lp[l + 1] - lp[l]) * lr + 255) / 256);
+        if (h->bs == 3)
+            k_gfactor_slots<3><<<g, 256, 0, st>>>(lp[l], lp[l + 1], h->grec, h->aval, h->ginvd, h->gsval[0],
+                                                  h->gsval[1], h->status);
+        else
+            k_gfactor_slots<1><<<g, 256, 0, st>>>(lp[l], lp[l + 1], h->grec, h->aval, h->ginvd, h->gsval[0],
+                                                  h->gsval[1], h->status);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_slot_records(dd_ctx *h, int32_t *other, hipStream_t st) {

@@ -156,10 +156,25 @@ struct dd_ctx {
     double *hist = nullptr;       // optional residual history (device, caller-owned)
     ddilu::Lic lic;
     int32_t pc_kind = 0;          // preconditioner of bicgstab_solve: 0 DD-ILU0, 1 global ILU0
-    // global (undecomposed) ILU0 of the full reordered matrix
+    // global (undecomposed) ILU0 of the full reordered matrix.  Pattern (kept
+    // for the handle's life): rows of each level one after another, host
+    // offsets of the levels.  Where every row has at most three blocks a
+    // sweep, the factors lie in the slot layout at the decomposed sweeps'
+    // positions, columns outside the subdomain numbered after its rows
+    // (halo); boxes of one level of the subdomain graph run together.
     int32_t *glev[2] = {nullptr, nullptr};
-    int32_t gnlev[2] = {0, 0};
+    int32_t *glist[2] = {nullptr, nullptr};
+    std::vector<int32_t> glp[2];
     int32_t *gdiag = nullptr;
+    int32_t gpattern = 0;         // the above built
+    int32_t gslots = 0;           // slot layout in use (else glu/gf)
+    int32_t ghalo = 0;            // most halo rows of a subdomain, either sweep
+    int4 *grec = nullptr;         // [3n] factor records, level order
+    uint64_t *gdesc[2] = {nullptr, nullptr};
+    double *gsval[2] = {nullptr, nullptr};
+    int32_t *ghptr[2] = {nullptr, nullptr}, *ghrow[2] = {nullptr, nullptr};  // halo rows of each subdomain
+    int32_t *gbox[2] = {nullptr, nullptr};  // subdomains by level of the subdomain graph
+    std::vector<int32_t> gbp[2];            // offsets of those levels
     double *glu = nullptr, *ginvd = nullptr, *gf = nullptr;
     int32_t gfactored = 0;
     int32_t hist_len = 0;
@@ -314,6 +329,9 @@ constexpr int64_t kNoallocBytes = int64_t(128) << 20;
 // global ILU0
 int global_factor(dd_ctx *h, hipStream_t st);
 hipError_t launch_global_apply(dd_ctx *h, const double *r, double *z, int nrhs, hipStream_t st);
+hipError_t launch_gfactor_slots(dd_ctx *h, const std::vector<int32_t> &lp, hipStream_t st);
+hipError_t launch_gapply_slots(dd_ctx *h, const double *r, double *z, int nrhs, hipStream_t st);
+bool gapply_slots_fits(const dd_ctx *h, int halo);
 hipError_t launch_diag_positions(dd_ctx *h, int32_t *diag, hipStream_t st);
 
 // learned correction

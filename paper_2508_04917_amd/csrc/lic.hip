@@ -418,9 +418,21 @@ __global__ __launch_bounds__(256) void k_lic_den(int64_t m, const double *__rest
     const int q = blockIdx.x;
     __shared__ double sh[256];
     double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < m; i += blockDim.x) {
-        const double e = zdd[q * m + i] - zs[q * m + i];
-        acc += e * e;
+    constexpr int U = 8;  // loads in flight per thread and vector (one at a time: 442 us for 16 probes of 48^3)
+    for (int64_t i0 = threadIdx.x; i0 < m; i0 += U * (int64_t)blockDim.x) {
+        double a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = min(i0 + u * (int64_t)blockDim.x, m - 1);
+            a[u] = zdd[q * m + i];
+            b[u] = zs[q * m + i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * (int64_t)blockDim.x < m) {
+                const double e = a[u] - b[u];
+                acc += e * e;
+            }
     }
     sh[threadIdx.x] = acc;
     __syncthreads();
