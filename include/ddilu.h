@@ -484,7 +484,9 @@ int lic_train(dd_handle *hs, int32_t nprob, const double *const *R,
  * handle existed when h is NULL).  Owned by the library. */
 const char *dd_last_error(dd_handle h);
 
-/* Releases every device buffer of the handle. */
+/* Destroys the handle.  Its device buffers stay with the library for later
+ * handles, at most a sixteenth of the device's memory in all; dd_destroy(NULL)
+ * returns all such memory to the driver. */
 void dd_destroy(dd_handle h);
 
 #ifdef __cplusplus

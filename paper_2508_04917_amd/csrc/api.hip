@@ -33,20 +33,7 @@ int dd_ctx::fail(int code, const char *fmt, ...) {
     return code;
 }
 
-dd_ctx::~dd_ctx() {
-    for (hipEvent_t e : events) (void)hipEventDestroy(e);
-    for (void *q : allocs) (void)hipFree(q);
-    if (ks_host) (void)hipHostFree(ks_host);
-}
-
-static void release(dd_ctx *h, void *q) {
-    if (!q) return;
-    auto it = std::find(h->allocs.begin(), h->allocs.end(), q);
-    if (it != h->allocs.end()) {
-        (void)hipFree(q);
-        h->allocs.erase(it);
-    }
-}
+static void release(dd_ctx *h, void *q) { h->release(q); }
 
 #define HCHK(x)                                                                             \
     do {                                                                                    \
@@ -297,6 +284,7 @@ static int build_handle(dd_ctx *h, const int32_t *brow_ptr, const int32_t *bcol,
     // of them is enqueued
     PCHK(hipStreamSynchronize(st));
     release(h, len);
+    h->reclaim();
     h->asrc = src;  // kept for ilu0_refactor
     *out = h;
     return DD_OK;
@@ -579,6 +567,7 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     h->precision = precision;
     if (precision != DD_FP64) RCHK(ensure_fp32(h, st));
     HCHK(hipStreamSynchronize(st));
+    h->reclaim();
     h->factored = 1;
     h->patterned = 1;
     return DD_OK;
@@ -940,4 +929,7 @@ extern "C" int lic_train(dd_handle *hs, int32_t nprob, const double *const *R, c
 
 extern "C" const char *dd_last_error(dd_handle h) { return h ? h->err.c_str() : g_err.c_str(); }
 
-extern "C" void dd_destroy(dd_handle h) { delete h; }
+extern "C" void dd_destroy(dd_handle h) {
+    if (!h) ddilu::pool_trim(-1);
+    delete h;
+}

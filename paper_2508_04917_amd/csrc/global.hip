@@ -390,14 +390,6 @@ hipError_t launch_diag_positions(dd_ctx *h, int32_t *diag, hipStream_t st) {
         if (r_) return r_; \
     } while (0)
 
-static void gdrop(dd_ctx *h, void *q) {
-    auto it = std::find(h->allocs.begin(), h->allocs.end(), q);
-    if (it != h->allocs.end()) {
-        (void)hipFree(q);
-        h->allocs.erase(it);
-    }
-}
-
 // Level lists of the undecomposed matrix.
 static int global_levels(dd_ctx *h, hipStream_t st) {
     const int T = 256;
@@ -444,7 +436,7 @@ static int global_levels(dd_ctx *h, hipStream_t st) {
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) rc = h->fail(DD_EHIP, "global levels: %s", hipGetErrorString(e));
     }
-    for (void *q : {(void *)cnt, (void *)cur, (void *)tmp}) gdrop(h, q);
+    for (void *q : {(void *)cnt, (void *)cur, (void *)tmp}) h->release(q);
     return rc;
 }
 
@@ -464,7 +456,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
         if (!rc && !h->ghptr[w]) rc = h->alloc(&h->ghptr[w], h->nsub + 1);
     }
     auto bail = [&](int code) {
-        for (int w = 0; w < 2; ++w) gdrop(h, cnt[w]);
+        for (int w = 0; w < 2; ++w) h->release(cnt[w]);
         return code;
     };
     if (rc) return bail(rc);
@@ -488,7 +480,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
     int32_t *linv = nullptr;
     rc = h->alloc(&linv, h->n);
     for (int w = 0; w < 2 && !rc; ++w) {
-        if (h->ghrow[w]) gdrop(h, h->ghrow[w]);
+        if (h->ghrow[w]) h->release(h->ghrow[w]);
         h->ghrow[w] = nullptr;
         rc = h->alloc(&h->ghrow[w], hp[w].back());
         if (!rc && !h->gdesc[w]) rc = h->alloc(&h->gdesc[w], h->n);
@@ -498,7 +490,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
     if (!rc && !h->grec) rc = h->alloc(&h->grec, 3 * h->n);
     if (!rc && !h->ginvd) rc = h->alloc(&h->ginvd, h->n * bb);
     if (rc) {
-        gdrop(h, linv);
+        h->release(linv);
         return rc;
     }
     k_ghalo<true><<<boxes, 256, 0, st>>>(h->S, h->aptr, h->acol, h->gdiag, h->lev[0].rows, h->lev[1].rows,
@@ -514,7 +506,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
     }
     if (e == hipSuccess) e = hipMemcpyAsync(got, bad, sizeof(got), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    gdrop(h, linv);
+    h->release(linv);
     if (e != hipSuccess) return h->fail(DD_EHIP, "global slots: %s", hipGetErrorString(e));
     if (got[0]) return DD_OK;
     // levels of the subdomain graph: a subdomain only depends on lower
@@ -587,6 +579,7 @@ int global_factor(dd_ctx *h, hipStream_t st) {
     GCHK(hipStreamSynchronize(st));
     if (status[2] != 0x7fffffff)
         return h->fail(DD_EZEROPIVOT, "global ILU0: singular pivot at reordered block row %d", status[2]);
+    h->reclaim();
     h->gfactored = 1;
     return DD_OK;
 }

@@ -340,7 +340,7 @@ int graph_partition(dd_ctx *h, const int32_t *ptr, const int32_t *col, hipStream
     std::vector<void *> tmp;
     auto get = [&](auto **p, int64_t count) -> hipError_t {
         void *q = nullptr;
-        hipError_t e = hipMalloc(&q, (size_t)std::max<int64_t>(count, 1) * sizeof(**p));
+        hipError_t e = pool_alloc(&q, (size_t)std::max<int64_t>(count, 1) * sizeof(**p));
         if (e == hipSuccess) {
             tmp.push_back(q);
             *p = static_cast<std::remove_reference_t<decltype(*p)>>(q);
@@ -348,7 +348,10 @@ int graph_partition(dd_ctx *h, const int32_t *ptr, const int32_t *col, hipStream
         return e;
     };
     auto done = [&](int rc) {
-        for (void *q : tmp) (void)hipFree(q);
+        // kernels may still run after an error; all other exits are synchronised
+        const bool idle = hipDeviceSynchronize() == hipSuccess;
+        for (void *q : tmp)
+            if (idle) pool_free(q); else (void)hipFree(q);
         return rc;
     };
 #define GCHK(x)                                                                   \

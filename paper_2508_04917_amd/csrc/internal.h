@@ -204,28 +204,32 @@ struct dd_ctx {
     unsigned long long *fticket = nullptr;  // workgroup ticket counter
     ddilu::KrylovScalars *ks = nullptr;
     ddilu::KrylovScalars *ks_host = nullptr;  // pinned
-    std::vector<void *> allocs;
+    std::vector<void *> allocs;   // the handle's device buffers
+    std::vector<void *> retired;  // released ones that queued work may still read
+    int device = -1;
     std::string err;
 
     int fail(int code, const char *fmt, ...);
-    // hipMalloc of count elements, recorded for dd_destroy
+    int alloc_bytes(void **p, size_t bytes);
+    // device memory of count elements, recorded for dd_destroy
     template <typename T>
     int alloc(T **p, int64_t count) {
         void *q = nullptr;
-        const size_t bytes = (size_t)std::max<int64_t>(count, 1) * sizeof(T);
-        hipError_t e = hipMalloc(&q, bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(DD_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-        }
-        allocs.push_back(q);
-        *p = static_cast<T *>(q);
-        return DD_OK;
+        const int rc = alloc_bytes(&q, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
+        if (!rc) *p = static_cast<T *>(q);
+        return rc;
     }
+    void release(void *q);  // to the pool at the next reclaim()
+    void reclaim();         // waits for the device when something was released
     ~dd_ctx();
 };
 
 namespace ddilu {
+
+// device memory kept between handles (pool.hip)
+hipError_t pool_alloc(void **out, size_t bytes);
+void pool_free(void *q);      // the device must have been idle since q's last use
+void pool_trim(int device);   // back to the driver; -1: every device
 
 // exclusive scan of int32 counts: out[0] = 0, out[i+1] = out[i] + in[i];
 // returns the total in *total (synchronises the stream).  tmp: scratch of

@@ -265,13 +265,8 @@ void build_spmv_layout(dd_ctx *h, hipStream_t st) {
     h->sell_nslice = nslice;
     h->sell_spp = spp;
     auto grab = [&](size_t bytes) -> void * {
-        void *p = nullptr;
-        if (hipMalloc(&p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        h->allocs.push_back(p);  // released with the handle, used or not
-        return p;
+        void *p = nullptr;  // released with the handle, used or not
+        return h->alloc_bytes(&p, bytes) == DD_OK ? p : nullptr;
     };
     int64_t nslots = nslice * kUnroll * rpw;
     if (parts || h->max_row_a > kUnroll) {

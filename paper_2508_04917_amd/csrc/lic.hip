@@ -557,8 +557,7 @@ int lic_setup(dd_ctx *h, hipStream_t st) {
     for (void *q : {(void *)L.fI, (void *)L.fJ, (void *)L.fq, (void *)L.X, (void *)L.C, (void *)L.lrec,
                     (void *)L.lperm, (void *)L.Cr})
         if (q) {
-            h->allocs.erase(std::find(h->allocs.begin(), h->allocs.end(), q));
-            (void)hipFree(q);
+            h->release(q);
         }
     rc = h->alloc(&L.fI, nf);
     if (!rc) rc = h->alloc(&L.fJ, nf);
@@ -593,10 +592,8 @@ int lic_setup(dd_ctx *h, hipStream_t st) {
     // the adjoint apply's streams are packed on first use (training only)
     L.adj_ready = 0;
     e = hipStreamSynchronize(st);
-    for (void *q : {(void *)cnt, (void *)flag, (void *)bpos}) {
-        h->allocs.erase(std::find(h->allocs.begin(), h->allocs.end(), q));
-        (void)hipFree(q);
-    }
+    for (void *q : {(void *)cnt, (void *)flag, (void *)bpos}) h->release(q);
+    h->reclaim();
     if (e != hipSuccess) return h->fail(DD_EHIP, "lic setup: %s", hipGetErrorString(e));
     L.ready = 1;
     L.active = 0;
@@ -659,10 +656,8 @@ int lic_loss_grad_run(dd_ctx *h, const float *params, int Q, const double *R, co
     if (rc) return rc;
     if (L.work_q < Q) {
         for (void *q : {(void *)L.Z, (void *)L.G, (void *)L.A, (void *)L.rpart})
-            if (q) {
-                h->allocs.erase(std::find(h->allocs.begin(), h->allocs.end(), q));
-                (void)hipFree(q);
-            }
+            h->release(q);
+        h->reclaim();
         rc = h->alloc(&L.Z, Q * m);
         if (!rc) rc = h->alloc(&L.G, Q * m);
         if (!rc) rc = h->alloc(&L.A, Q * m);
@@ -727,8 +722,8 @@ int lic_targets_run(dd_ctx *h, int Q, const double *R, double *Zs, double *den, 
         k_lic_den<<<Q, 256, 0, st>>>(m, zdd, Zs, den);
         e = hipStreamSynchronize(st);
     }
-    h->allocs.erase(std::find(h->allocs.begin(), h->allocs.end(), (void *)zdd));
-    (void)hipFree(zdd);
+    h->release(zdd);
+    h->reclaim();
     if (e != hipSuccess) return h->fail(DD_EHIP, "lic targets: %s", hipGetErrorString(e));
     return DD_OK;
 }

@@ -1,0 +1,186 @@
+// Device memory of the handles.  hipMalloc and hipFree of a handle's buffers
+// (4 GB for 128^3 3x3 blocks) cost more than the setup kernels: freed pages
+// are cleared by the driver before they can be handed out again, 130 ms per
+// setup in a program that builds and destroys one system after another.  A
+// destroyed handle's buffers therefore stay with the library for the next
+// handle, up to a bound (kShare of the device's memory); what exceeds it, or
+// has lain unused for kIdleSeconds when the pool is next used, goes back to
+// the driver, and everything does when an allocation fails and on
+// dd_destroy(NULL).
+//
+// A block enters the pool only after the device has been idle since its last
+// possible use (dd_ctx::reclaim and the destructor synchronise the device, as
+// hipFree does), so it may be handed to any stream and thread.  One mutex
+// guards the table; no lock is held across a driver call that can wait for
+// work.
+#include <chrono>
+#include <map>
+#include <mutex>
+#include <unordered_map>
+
+#include "internal.h"
+
+namespace ddilu {
+
+namespace {
+
+using Clock = std::chrono::steady_clock;
+constexpr size_t kShare = 16;  // at most 1/kShare of a device's memory is kept
+constexpr int kIdleSeconds = 60;
+
+struct Block {
+    void *p;
+    Clock::time_point since;
+};
+
+struct Device {
+    std::multimap<size_t, Block> free;
+    size_t held = 0, bound = 0;
+};
+
+struct Pool {
+    std::mutex mu;
+    std::map<int, Device> dev;
+    std::unordered_map<void *, std::pair<size_t, int>> size;  // every block the pool handed out or holds
+};
+
+Pool &pool() {
+    static Pool *p = new Pool;  // never destroyed: handles may outlive static objects
+    return *p;
+}
+
+size_t rounded(size_t b) {
+    const size_t unit = b >= (size_t(1) << 21) ? size_t(1) << 21 : 4096;
+    return (b + unit - 1) / unit * unit;
+}
+
+void take_out(Pool &P, Device &D, std::multimap<size_t, Block>::iterator it, std::vector<void *> &out) {
+    D.held -= it->first;
+    out.push_back(it->second.p);
+    P.size.erase(it->second.p);
+    D.free.erase(it);
+}
+
+void give_back(const std::vector<void *> &v) {
+    for (void *q : v) (void)hipFree(q);
+}
+
+}  // namespace
+
+hipError_t pool_alloc(void **out, size_t bytes) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const size_t need = rounded(bytes);
+    Pool &P = pool();
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        Device &D = P.dev[dev];
+        auto it = D.free.lower_bound(need);
+        if (it != D.free.end() && it->first - need <= need / 4) {  // a quarter more than asked at most
+            *out = it->second.p;
+            D.held -= it->first;
+            D.free.erase(it);
+            return hipSuccess;
+        }
+    }
+    e = hipMalloc(out, need);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        pool_trim(dev);
+        e = hipMalloc(out, need);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e;
+        }
+    }
+    std::lock_guard<std::mutex> lock(P.mu);
+    P.size[*out] = {need, dev};
+    return hipSuccess;
+}
+
+void pool_free(void *q) {
+    if (!q) return;
+    std::vector<void *> out;
+    Pool &P = pool();
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        const auto s = P.size.find(q);
+        if (s == P.size.end()) return;
+        Device &D = P.dev[s->second.second];
+        if (!D.bound) {
+            size_t avail = 0, total = 0;
+            if (hipMemGetInfo(&avail, &total) != hipSuccess) total = 0;
+            D.bound = std::max<size_t>(total / kShare, 1);
+        }
+        const Clock::time_point now = Clock::now();
+        D.free.insert({s->second.first, Block{q, now}});
+        D.held += s->second.first;
+        for (auto it = D.free.begin(); it != D.free.end();) {
+            const auto next = std::next(it);
+            if (now - it->second.since > std::chrono::seconds(kIdleSeconds)) take_out(P, D, it, out);
+            it = next;
+        }
+        while (D.held > D.bound && !D.free.empty()) take_out(P, D, std::prev(D.free.end()), out);
+    }
+    give_back(out);
+}
+
+void pool_trim(int device) {
+    std::vector<void *> out;
+    Pool &P = pool();
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        for (auto &d : P.dev) {
+            if (device >= 0 && d.first != device) continue;
+            while (!d.second.free.empty()) take_out(P, d.second, d.second.free.begin(), out);
+        }
+    }
+    give_back(out);
+}
+
+}  // namespace ddilu
+
+void dd_ctx::release(void *q) {
+    if (!q) return;
+    auto it = std::find(allocs.begin(), allocs.end(), q);
+    if (it == allocs.end()) return;
+    allocs.erase(it);
+    retired.push_back(q);
+}
+
+// Work that may still read the retired buffers, on any stream of the handle's
+// device, ends first.
+void dd_ctx::reclaim() {
+    if (retired.empty()) return;
+    int dev = device;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    const bool other = device >= 0 && device != dev;
+    if (other && hipSetDevice(device) != hipSuccess) return;
+    const hipError_t e = hipDeviceSynchronize();
+    if (other) (void)hipSetDevice(dev);
+    if (e != hipSuccess) return;  // kept for the destructor
+    for (void *q : retired) ddilu::pool_free(q);
+    retired.clear();
+}
+
+int dd_ctx::alloc_bytes(void **p, size_t bytes) {
+    if (device < 0) (void)hipGetDevice(&device);
+    hipError_t e = ddilu::pool_alloc(p, bytes);
+    if (e != hipSuccess && !retired.empty()) {
+        reclaim();
+        e = ddilu::pool_alloc(p, bytes);
+    }
+    if (e != hipSuccess) return fail(DD_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+    allocs.push_back(*p);
+    return DD_OK;
+}
+
+dd_ctx::~dd_ctx() {
+    for (hipEvent_t e : events) (void)hipEventDestroy(e);
+    retired.insert(retired.end(), allocs.begin(), allocs.end());
+    allocs.clear();
+    reclaim();
+    for (void *q : retired) (void)hipFree(q);  // the device is in error: leave nothing in the pool
+    if (ks_host) (void)hipHostFree(ks_host);
+}

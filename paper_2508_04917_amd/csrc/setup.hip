@@ -688,13 +688,7 @@ int build_seg_layout(dd_ctx *h, int which, int mb, int cw, int rpw, hipStream_t 
     if (!rc && !w.gpos) rc = h->alloc(&w.gpos, nsub + 1);
     if (!rc && !w.gchk) rc = h->alloc(&w.gchk, nsub + 1);
     if (rc) return rc;
-    auto drop = [&](void *q) {
-        auto it = std::find(h->allocs.begin(), h->allocs.end(), q);
-        if (it != h->allocs.end()) {
-            (void)hipFree(q);
-            h->allocs.erase(it);
-        }
-    };
+    auto drop = [&](void *q) { h->release(q); };
     k_seg_walk<false><<<nsub, 256, 0, st>>>(h->S, which, mb, cw, rpw, L.off, L.ptr, w.bptr, npos, nchk, nullptr,
                                         nullptr, nullptr, nullptr);
     hipError_t e = exclusive_scan(npos, w.gpos, nsub, h->scan_tmp, st);
@@ -774,13 +768,7 @@ int build_wave_chunks(dd_ctx *h, int which, hipStream_t st) {
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return h->fail(DD_EHIP, "wave chunks: %s", hipGetErrorString(e));
     }
-    for (void *q : {(void *)w.wtab, (void *)w.winfo}) {
-        auto it = std::find(h->allocs.begin(), h->allocs.end(), q);
-        if (q && it != h->allocs.end()) {
-            (void)hipFree(q);
-            h->allocs.erase(it);
-        }
-    }
+    for (void *q : {(void *)w.wtab, (void *)w.winfo}) h->release(q);
     w.wtab = nullptr;
     w.winfo = nullptr;
     int rc = h->alloc(&w.wtab, w.snpos / rpw + h->nsub + pieces + 1);
