@@ -389,11 +389,12 @@ static void drop_csr(dd_ctx *h) {
 }
 
 // Whether the apply variant (0: automatic) reads the CSR streams.
-static bool needs_csr(const dd_ctx *h) { return !h->slots || (h->variant != 0 && h->variant != 3); }
+static bool needs_csr(const dd_ctx *h) {
+    return (!h->slots && !h->seg) || (h->variant != 0 && h->variant != 3);
+}
 
 // The sweeps in CSR form: what the apply variants other than the slot kernel
-// read, and what the segmented layout is packed from.  The slot kernel's
-// handles build them on demand.
+// read.  The slot kernel's handles build them on demand.
 static int ensure_csr(dd_ctx *h, hipStream_t st) {
     if (h->csr_ready) return DD_OK;
     const int bb = h->bs * h->bs;
@@ -420,8 +421,7 @@ static int ensure_csr(dd_ctx *h, hipStream_t st) {
 
 // The segmented layout, where the slot layout does not hold the rows.
 static int build_seg(dd_ctx *h, hipStream_t st) {
-    // rows of more than three blocks: the segmented layout, for the apply's
-    // workgroups of 1,024 lanes, with segments of two blocks (the least
+    // rows of more than three blocks: segments of two blocks (the least
     // zero padding on the row lengths of k-nearest-neighbour graphs:
     // 1.18x the algorithmic bytes against 1.29x with three), or of three
     // when a row would need more than kSegMax segments of two
@@ -429,22 +429,16 @@ static int build_seg(dd_ctx *h, hipStream_t st) {
     auto fits = [&](int mb) { return lo <= mb * kSegMax && up <= mb + (kSegMax - 1) * (mb + 1); };
     const int mb = fits(2) ? 2 : (fits(3) ? 3 : 0);
     if (!mb) return DD_OK;
-    // the walk counts positions in 32-bit integers: a row takes at most
-    // kSegMax segments and kSegMax - 1 padding positions, so stay on the
-    // plain loop where that bound could pass 2^31
+    // positions are counted in 32-bit integers: stay on the plain loop where
+    // a generous bound of them could pass 2^31
     for (int w = 0; w < 2; ++w)
         if ((int64_t)(h->sw[w].nblk + h->n) * (2 * kSegMax) >= ((int64_t)1 << 31)) return DD_OK;
-    const int rpw = kWave / h->bs, cw = rpw * (1024 / kWave);
-    h->seg = mb;  // the packing reads it
-    for (int w = 0; w < 2; ++w) {
-        int rc = build_seg_layout(h, w, mb, cw, rpw, st);
-        if (!rc) rc = build_wave_chunks(h, w, st);
-        if (rc) {
-            h->seg = 0;
-            return rc;
-        }
-    }
-    return DD_OK;
+    // the position scan holds a part's rows in LDS, as the apply its vector
+    if ((int64_t)(h->S + 1) * 4 > 163840 - 1024) return DD_OK;
+    h->seg = mb;
+    const int rc = build_seg_layout(h, st);
+    if (rc) h->seg = 0;
+    return rc;
 }
 
 // Memory of the slot layout (every row has at most kMaxSlots blocks per
@@ -562,8 +556,8 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
         return h->fail(DD_EZEROPIVOT, "singular or ill-conditioned pivot block at reordered block row %d", status[2]);
     if (h->slots && !h->direct)
         for (int w = 0; w < 2; ++w) HCHK(launch_pack_slots(h, w, st));
-    if (needs_csr(h)) RCHK(ensure_csr(h, st));
     if (!h->slots) RCHK(build_seg(h, st));
+    if (needs_csr(h)) RCHK(ensure_csr(h, st));
     h->precision = precision;
     if (precision != DD_FP64) RCHK(ensure_fp32(h, st));
     HCHK(hipStreamSynchronize(st));
@@ -600,10 +594,7 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     for (int w = 0; w < 2 && h->csr_ready; ++w) HCHK(launch_pack_fill(h, w, st));
     if (needs_csr(h)) RCHK(ensure_csr(h, st));
     for (int w = 0; w < 2 && h->slots && !h->direct; ++w) HCHK(launch_pack_slots(h, w, st));
-    if (h->seg) {
-        HCHK(launch_seg_pack(h, 0, st));
-        HCHK(launch_seg_pack(h, 1, st));
-    }
+    if (h->seg) HCHK(launch_seg_pack(h, st));
     if (h->sw[0].val32 || h->sw[0].sval32) HCHK(launch_cast32(h, st));
     HCHK(hipStreamSynchronize(st));
     h->factored = 1;

@@ -659,4 +659,234 @@ hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st) {
     return hipGetLastError();
 }
 
+// ------------------------------------------------- segmented slot layout
+// For sweeps with rows of more than three blocks.  With MB blocks per
+// segment, a lower-sweep row with nb blocks becomes ceil(nb/MB) segments (none
+// when nb = 0: y_I = r_I), an upper-sweep row one segment of MB blocks and
+// inv_D plus ceil((nb - MB)/(MB + 1)) continuations of MB + 1 blocks (the
+// extra block in the inv_D slot, which a continuation does not need); blocks
+// in column order, segments at consecutive positions; the first segment (the
+// row's owner) adds the others' partial sums in the apply, by cross-lane reads:
+// so a wave-chunk takes whole rows, as many as fit its positions.  Positions
+// follow each other without padding (chunks name their own extent), the
+// streams are the sum of the segments.
+__device__ __forceinline__ int seg_count(int which, int nb, int mb) {
+    return which == 0 ? (nb + mb - 1) / mb : 1 + (max(nb - mb, 0) + mb) / (mb + 1);
+}
+
+// positions of each subdomain (blockIdx.y = sweep)
+__global__ __launch_bounds__(256) void k_seg_count(int S, int mb, const int32_t *__restrict__ tptr,
+                                                  const int32_t *__restrict__ tcol,
+                                                  const int32_t *__restrict__ tdiag, int32_t *__restrict__ npos0,
+                                                  int32_t *__restrict__ npos1) {
+    __shared__ int sum;
+    const int which = blockIdx.y, s = blockIdx.x;
+    const int64_t base = (int64_t)s * S;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    int m = 0;
+    for (int i = threadIdx.x; i < S; i += blockDim.x) {
+        int32_t lo, hi;
+        dep_range(which, base + i, tptr, tcol, tdiag, lo, hi);
+        m += seg_count(which, hi - lo, mb);
+    }
+    atomicAdd(&sum, m);
+    __syncthreads();
+    if (threadIdx.x == 0) (which ? npos1 : npos0)[s] = sum;
+}
+
+// Position map and wave-chunks of each subdomain (one workgroup each, y =
+// sweep): a scan over the rows in sweep order gives every row's first
+// position; then one wavefront cuts each level, finding by ballot how many
+// rows the next chunk holds.  wbase bounds the chunks before: all but a
+// level's last hold more than rpw - kSegMax positions.  Placing the rows one
+// by one in one thread: 2 x 2 x 555 us for 1,024,000 rows in 250 parts; 60 us.
+__global__ __launch_bounds__(512) void k_seg_fill(int S, int mb, int rpw, const int32_t *__restrict__ tptr,
+                                                 const int32_t *__restrict__ tcol,
+                                                 const int32_t *__restrict__ tdiag, const int32_t *__restrict__ off0,
+                                                 const int32_t *__restrict__ off1, const int32_t *__restrict__ lp0,
+                                                 const int32_t *__restrict__ lp1, const int32_t *__restrict__ rows0,
+                                                 const int32_t *__restrict__ rows1,
+                                                 const int32_t *__restrict__ gpos0,
+                                                 const int32_t *__restrict__ gpos1, int2 *__restrict__ pmap0,
+                                                 int2 *__restrict__ pmap1, int2 *__restrict__ wtab0,
+                                                 int2 *__restrict__ wtab1, int4 *__restrict__ winfo0,
+                                                 int4 *__restrict__ winfo1) {
+    extern __shared__ int32_t first[];  // [S + 1] first position of each row in sweep order
+    __shared__ int sh[65];
+    const int which = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+    const int64_t base = (int64_t)s * S;
+    const int32_t *rows = which ? rows1 : rows0;
+    const int32_t g0 = (which ? gpos1 : gpos0)[s];
+    int2 *pmap = (which ? pmap1 : pmap0) + g0;
+    int done = 0;
+    for (int t0 = 0; t0 < S; t0 += nt) {
+        const int i = t0 + tid;
+        int m = 0;
+        int64_t gi = 0;
+        if (i < S) {
+            gi = base + rows[base + i];
+            int32_t lo, hi;
+            dep_range(which, gi, tptr, tcol, tdiag, lo, hi);
+            m = seg_count(which, hi - lo, mb);
+        }
+        int tot;
+        const int at = done + block_excl_scan(m, sh, &tot);
+        if (i < S) first[i] = at;
+        for (int q = 0; q < m; ++q) pmap[at + q] = make_int2((int32_t)gi, q | m << 8);
+        done += tot;
+    }
+    if (tid == 0) first[S] = done;
+    __syncthreads();
+    if (tid >= kWave) return;
+    const int32_t o = (which ? off1 : off0)[s];
+    const int nl = (which ? off1 : off0)[s + 1] - o - 1;
+    const int32_t *lp = (which ? lp1 : lp0) + o;
+    const int32_t wbase = g0 / (rpw - kSegMax + 1) + s + o;
+    int2 *wtab = (which ? wtab1 : wtab0) + wbase;
+    int chunks = 0, level = 0;  // levels without positions (the lower sweep's first) are not counted
+    for (int l = 0; l < nl; ++l) {
+        const int e = lp[l + 1], before = chunks;
+        for (int i = lp[l]; i < e;) {
+            const int p0 = first[i];
+            for (int c = kWave; c == kWave;) {
+                const int j = i + 1 + tid;
+                c = __popcll(__ballot(j <= e && first[min(j, S)] - p0 <= rpw));
+                i += c;  // at least one row: a row has at most kSegMax segments
+            }
+            const int cnt = first[i] - p0;
+            if (cnt == 0) continue;
+            if (tid == 0) wtab[chunks] = make_int2(p0, level << 8 | cnt);
+            ++chunks;
+        }
+        level += chunks > before ? 1 : 0;
+    }
+    if (tid == 0) (which ? winfo1 : winfo0)[s] = make_int4(wbase, chunks, level, 0);
+}
+
+// Position p: its segment's descriptor and values in the lane-run layout of
+// k_pack_slots (MB blocks, then inv_D in the upper sweep), from the factors
+// in the dropped pattern, Uhat = inv_D U on the way.  Lanes as in factor_row:
+// a quad per 3x3 position, lane c its blocks' row c, so stores are whole
+// runs.  An upper-sweep continuation holds its (MB+1)-th block in the inv_D
+// slot and that block's column in the row field (its own row when the slot is
+// empty: a valid LDS entry, times a zero block).  The descriptor keeps three
+// 16-bit column fields whatever MB (fields past MB empty), so that the bits 15
+// of fields 1 to 3 hold m - 1 on a row's first segment.
+template <int BS, int MB, int WHICH>
+__global__ __launch_bounds__(256) void k_seg_pack(int64_t npos, int S, const int2 *__restrict__ pmap,
+                                                 const int32_t *__restrict__ tptr, const int32_t *__restrict__ tcol,
+                                                 const int32_t *__restrict__ tdiag, const double *__restrict__ lu,
+                                                 const double *__restrict__ invd, uint64_t *__restrict__ desc,
+                                                 double *__restrict__ sval) {
+    constexpr int BB = BS * BS, LR = BS == 3 ? 4 : 1, NV = (MB + WHICH) * BS;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t p = t / LR;
+    const int l = (int)(t % LR), c = min(l, BS - 1);
+    const bool ok = p < npos;
+    const int2 e = pmap[ok ? p : 0];
+    const int k = e.y & 0xff, m = e.y >> 8;
+    const int64_t gi = e.x, base = gi / S * S;
+    int32_t lo, hi;
+    dep_range(WHICH, gi, tptr, tcol, tdiag, lo, hi);
+    const int32_t b0 = lo + (WHICH == 0 || k == 0 ? MB * k : MB + (k - 1) * (MB + 1));
+    const int32_t b1 = min(b0 + MB, hi);
+    const int32_t bx = WHICH == 1 && k > 0 && b0 + MB < hi ? b0 + MB : -1;  // a continuation's extra block
+    double iv[BS];
+#pragma unroll
+    for (int j = 0; j < BS; ++j) iv[j] = WHICH == 1 ? invd[gi * BB + c * BS + j] : 0.0;
+    double *o = sval + (p * BS + c) * NV;
+#pragma unroll
+    for (int q = 0; q < MB + WHICH; ++q) {
+        const int32_t b = q < MB ? (b0 + q < b1 ? b0 + q : -1) : bx;
+        double v[BS], u[BS];
+#pragma unroll
+        for (int j = 0; j < BS; ++j) v[j] = b >= 0 ? lu[(int64_t)b * BB + c * BS + j] : 0.0;
+        if constexpr (WHICH == 1) {
+            row_times<BS>(iv, v, u);
+#pragma unroll
+            for (int j = 0; j < BS; ++j) v[j] = q == MB && k == 0 ? iv[j] : (b >= 0 ? u[j] : 0.0);
+        }
+        if (ok && l < BS)
+#pragma unroll
+            for (int j = 0; j < BS; ++j) o[q * BS + j] = v[j];
+    }
+    if (!ok || l != 0) return;
+    uint64_t d = (uint64_t)(bx >= 0 ? tcol[bx] - (int32_t)base : (int32_t)(gi - base)) | (k > 0 ? 0x8000ull : 0ull);
+    for (int j = 0; j < 3; ++j)
+        d |= (uint64_t)(j < MB && b0 + j < b1 ? tcol[b0 + j] - (int32_t)base : 0x7fff) << (16 * (j + 1));
+    if (k == 0)
+        for (int j = 0; j < 3; ++j)
+            if (((m - 1) >> j) & 1) d |= 1ull << (16 * (j + 1) + 15);
+    desc[p] = d;
+}
+
+hipError_t launch_seg_pack(dd_ctx *h, hipStream_t st) {
+    const int lr = h->bs == 3 ? 4 : 1;
+    for (int w = 0; w < 2; ++w) {
+        Sweep &s = h->sw[w];
+        if (s.snpos == 0) continue;
+        const unsigned g = (unsigned)((s.snpos * lr + 255) / 256);
+        auto go = [&](auto kern) {
+            kern<<<g, 256, 0, st>>>(s.snpos, h->S, s.pmap, h->tptr, h->tcol, h->tdiag, h->lu, h->invd, s.desc,
+                                    s.sval64);
+        };
+        switch ((h->bs == 3 ? 0 : 4) + (h->seg == 2 ? 0 : 2) + w) {
+            case 0: go(k_seg_pack<3, 2, 0>); break;
+            case 1: go(k_seg_pack<3, 2, 1>); break;
+            case 2: go(k_seg_pack<3, 3, 0>); break;
+            case 3: go(k_seg_pack<3, 3, 1>); break;
+            case 4: go(k_seg_pack<1, 2, 0>); break;
+            case 5: go(k_seg_pack<1, 2, 1>); break;
+            case 6: go(k_seg_pack<1, 3, 0>); break;
+            default: go(k_seg_pack<1, 3, 1>); break;
+        }
+    }
+    return hipGetLastError();
+}
+
+// Positions, chunks and values of both sweeps (h->seg set).
+int build_seg_layout(dd_ctx *h, hipStream_t st) {
+    const int mb = h->seg, rpw = kWave / h->bs, bb = h->bs * h->bs, nsub = h->nsub;
+    int32_t *npos[2] = {nullptr, nullptr}, tot[2] = {0, 0};
+    int rc = DD_OK;
+    for (int w = 0; w < 2 && !rc; ++w) {
+        rc = h->alloc(&npos[w], nsub);
+        if (!rc && !h->sw[w].gpos) rc = h->alloc(&h->sw[w].gpos, nsub + 1);
+    }
+    if (rc) return rc;
+    k_seg_count<<<dim3(nsub, 2), 256, 0, st>>>(h->S, mb, h->tptr, h->tcol, h->tdiag, npos[0], npos[1]);
+    hipError_t e = hipGetLastError();
+    for (int w = 0; w < 2; ++w) {
+        if (e == hipSuccess) e = exclusive_scan(npos[w], h->sw[w].gpos, nsub, h->scan_tmp, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(&tot[w], h->sw[w].gpos + nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return h->fail(DD_EHIP, "segmented layout: %s", hipGetErrorString(e));
+    for (int w = 0; w < 2 && !rc; ++w) {
+        Sweep &s = h->sw[w];
+        for (void *q : {(void *)s.pmap, (void *)s.wtab, (void *)s.winfo, (void *)npos[w]}) h->release(q);
+        s.pmap = nullptr; s.wtab = nullptr; s.winfo = nullptr;
+        s.snpos = tot[w];
+        rc = h->alloc(&s.pmap, tot[w]);
+        if (!rc) rc = h->alloc(&s.wtab, tot[w] / (rpw - kSegMax + 1) + nsub + h->lev[w].ptr_len + 1);
+        if (!rc) rc = h->alloc(&s.winfo, nsub);
+        if (!rc) rc = h->alloc(&s.desc, tot[w]);
+        if (!rc) rc = h->alloc(&s.sval64, (int64_t)tot[w] * (mb + w) * bb);
+    }
+    if (rc) return rc;
+    Sweep &L = h->sw[0], &U = h->sw[1];
+    e = full_lds(k_seg_fill);
+    if (e == hipSuccess) {
+        k_seg_fill<<<dim3(nsub, 2), 512, (size_t)(h->S + 1) * sizeof(int32_t), st>>>(
+            h->S, mb, rpw, h->tptr, h->tcol, h->tdiag, h->lev[0].off, h->lev[1].off, h->lev[0].ptr, h->lev[1].ptr,
+            h->lev[0].rows, h->lev[1].rows, L.gpos, U.gpos, L.pmap, U.pmap, L.wtab, U.wtab, L.winfo, U.winfo);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = launch_seg_pack(h, st);
+    if (e != hipSuccess) return h->fail(DD_EHIP, "segmented layout: %s", hipGetErrorString(e));
+    return DD_OK;
+}
+
 }  // namespace ddilu

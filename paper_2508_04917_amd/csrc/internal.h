@@ -50,8 +50,7 @@ struct Sweep {
     int2 *wtab = nullptr;
     int4 *winfo = nullptr;
     // Segmented slot layout (rows of more than kMaxSlots blocks): a row is
-    // split into segments at consecutive positions of one wavefront; levels
-    // wider than a workgroup pass are cut into chunks.  With MB blocks per
+    // split into segments at consecutive positions of one wave-chunk.  With MB blocks per
     // segment (dd_ctx::seg): a lower-sweep segment holds MB blocks; in the
     // upper sweep the row's first segment holds MB blocks and inv_D, each
     // continuation MB + 1 blocks, the last one in the inv_D slot.  desc then
@@ -60,9 +59,7 @@ struct Sweep {
     // 16(k+1) (0x7FFF empty), and, for a row's first segment, its segment
     // count minus one in bits 31, 47 and 63.
     int32_t *gpos = nullptr;    // [nsub+1] first position of each subdomain
-    int32_t *gchk = nullptr;    // [nsub+1] first entry of each subdomain's chunk table
-    int32_t *chk = nullptr;     // per subdomain: chunk starts (relative; bit 30 = barrier after), end
-    int2 *pmap = nullptr;       // [snpos] CSR sweep position (-1 = padding), segment | count << 8
+    int2 *pmap = nullptr;       // [snpos] row, segment | its count << 8
 };
 
 constexpr int kSegMax = 8;  // segments of a row in the segmented layout
@@ -139,7 +136,7 @@ struct dd_ctx {
     int32_t *uinv = nullptr;      // [n] upper-sweep position of each row
     int4 *frec = nullptr;         // [2n] factor records of the slot layout (k_factor_records)
     int32_t direct = 0;           // factored by launch_bilu0_slots (frec valid for ilu0_refactor)
-    int32_t csr_ready = 0;        // the sweeps' CSR streams are built (variants 1, 2, 4-8; segmented layout)
+    int32_t csr_ready = 0;        // the sweeps' CSR streams are built (variants 1, 2, 4-8; rows neither slot layout holds)
     int32_t factored = 0;
     int32_t patterned = 0;        // drop, levels and streaming layouts built (ilu0_refactor may run)
     int32_t precision = DD_FP64;
@@ -267,12 +264,10 @@ hipError_t launch_pack_fill(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_pack_unscaled(dd_ctx *h, hipStream_t st);
 hipError_t launch_cast32(dd_ctx *h, hipStream_t st);
 hipError_t launch_pack_slots(dd_ctx *h, int which, hipStream_t st);
-// segmented slot layout: positions and chunk tables (which: 0 lower, 1
-// upper; chunk width cw positions, rpw per wavefront), then the values
-int build_seg_layout(dd_ctx *h, int which, int mb, int cw, int rpw, hipStream_t st);
-hipError_t launch_seg_pack(dd_ctx *h, int which, hipStream_t st);
-// the wave-chunk table of a sweep (from its level table, or from the
-// segmented layout's chunk table)
+// segmented slot layout of both sweeps: positions, wave-chunks, values
+int build_seg_layout(dd_ctx *h, hipStream_t st);
+hipError_t launch_seg_pack(dd_ctx *h, hipStream_t st);
+// the wave-chunk table of a sweep of the slot layout
 int build_wave_chunks(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_export_factors(dd_ctx *h, double *f, hipStream_t st);
 // out[k] = val[src[k]] for nblk blocks of bb values

@@ -499,283 +499,49 @@ hipError_t launch_pack_slots(dd_ctx *h, int which, hipStream_t st) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------- segmented slot layout
-// For sweeps with rows of more than three blocks.  With MB blocks per
-// segment, a lower-sweep row with nb blocks becomes ceil(nb/MB) segments (none
-// when nb = 0), an upper-sweep row one segment of MB blocks and inv_D plus
-// ceil((nb - MB)/(MB + 1)) continuations of MB + 1 blocks (the extra block
-// in the inv_D slot, which a continuation does not need); blocks in column
-// order, segments at consecutive positions of one wavefront; the first
-// segment (the row's owner) adds the others' partial sums in the apply.  Each level is
-// laid out in chunks of at most cw positions (one workgroup pass of the
-// apply, rpw positions per wavefront); a group that would straddle a
-// wavefront is moved to the next one (the positions skipped are padding), a
-// group that would not fit the chunk starts the next chunk of the level.
-// Only the last chunk of a level is followed by a barrier in the apply.  One
-// thread per subdomain walks its levels (count pass, then fill pass).
-// One workgroup per subdomain.  The rows of a level are taken kSegTile at a
-// time: every thread loads block counts and computes segment counts, one
-// thread places the tile's rows (the placement above, on LDS values only),
-// and every thread writes the tile's position map.
-constexpr int kSegTile = 1024;
-
-template <bool FILL>
-__global__ __launch_bounds__(256) void k_seg_walk(int S, int which, int mb, int cw, int rpw,
-                                                  const int32_t *__restrict__ off, const int32_t *__restrict__ lp,
-                                                  const int32_t *__restrict__ bptr, int32_t *npos, int32_t *nchk,
-                                                  const int32_t *__restrict__ gpos,
-                                                  const int32_t *__restrict__ gchk, int2 *pmap, int32_t *chk) {
-    __shared__ int m_s[kSegTile], at_s[kSegTile], pad_s[kSegTile];
-    __shared__ int32_t pos_s, nc_s, inchunk_s;
-    __shared__ bool open_s;
-    const int s = blockIdx.x, tid = threadIdx.x;
-    const int32_t o = off[s];
-    const int nl = off[s + 1] - o - 1;
-    const int64_t base = (int64_t)s * S;
-    const int32_t pb = FILL ? gpos[s] : 0, cb = FILL ? gchk[s] : 0;
-    if (tid == 0) {
-        pos_s = 0;
-        nc_s = 0;
-    }
-    for (int l = 0; l < nl; ++l) {
-        if (tid == 0) {
-            inchunk_s = 0;
-            open_s = false;  // a level's first position opens its first chunk
-        }
-        const int32_t k0 = lp[o + l], k1 = lp[o + l + 1];
-        for (int32_t t0 = k0; t0 < k1; t0 += kSegTile) {
-            const int cnt = min(kSegTile, k1 - t0);
-            for (int i = tid; i < cnt; i += blockDim.x) {
-                const int64_t p = base + t0 + i;
-                const int32_t nb = bptr[p + 1] - bptr[p];
-                // a lower-sweep row without blocks keeps y_I = r_I: no position
-                // (a level of such rows, the lower sweep's first, has no chunk)
-                m_s[i] = which == 0 ? (nb + mb - 1) / mb : 1 + (max(nb - mb, 0) + mb) / (mb + 1);
-            }
-            __syncthreads();
-            if (tid == 0) {
-                int32_t pos = pos_s, nc = nc_s;
-                int inchunk = inchunk_s;
-                bool open = open_s;
-                for (int i = 0; i < cnt; ++i) {
-                    const int m = m_s[i];
-                    if (m == 0) continue;
-                    int pad = (inchunk % rpw) + m > rpw ? rpw - inchunk % rpw : 0;
-                    if (!open || inchunk + pad + m > cw) {  // the level's first or next chunk
-                        if (FILL) chk[cb + nc] = pos;
-                        ++nc;
-                        inchunk = 0;
-                        pad = 0;
-                        open = true;
-                    }
-                    pad_s[i] = pad;
-                    at_s[i] = pos + pad;  // the row's first segment
-                    pos += pad + m;
-                    inchunk += pad + m;
-                }
-                pos_s = pos;
-                nc_s = nc;
-                inchunk_s = inchunk;
-                open_s = open;
-            }
-            __syncthreads();
-            if (FILL)
-                for (int i = tid; i < cnt; i += blockDim.x) {
-                    const int m = m_s[i];
-                    if (m == 0) continue;
-                    const int32_t at = at_s[i];
-                    for (int q = 0; q < pad_s[i]; ++q) pmap[pb + at - pad_s[i] + q] = make_int2(-1, 0);
-                    for (int q = 0; q < m; ++q) pmap[pb + at + q] = make_int2((int32_t)(base + t0 + i), q | (m << 8));
-                }
-            __syncthreads();  // the tile's LDS values are reused by the next tile
-        }
-        if (FILL && tid == 0 && open_s) chk[cb + nc_s - 1] |= 1 << 30;  // barrier after the level's last chunk
-        __syncthreads();
-    }
-    if (tid != 0) return;
-    int32_t nc = nc_s;
-    if (nc == 0) {  // no positions: one empty chunk, so the apply's table reads stay inside it
-        if (FILL) chk[cb] = 1 << 30;
-        ++nc;
-    }
-    if (FILL) {
-        chk[cb + nc] = pos_s;
-    } else {
-        npos[s] = pos_s;
-        nchk[s] = nc + 1;
-    }
-}
-
-// Position q: its segment's descriptor and values in the lane-run layout of
-// k_pack_slots (MB blocks, then inv_D in the upper sweep).  Padding
-// positions are continuations of local row 0 with no blocks (they read y_0
-// and write nothing).  An upper-sweep continuation holds its (MB+1)-th block
-// in the inv_D slot and that block's column in the row field (its own row
-// when the slot is empty: a valid LDS entry, times a zero block).  The
-// descriptor keeps three 16-bit column fields whatever MB (fields past MB
-// empty), so that the bits 15 of fields 1 to 3 hold m - 1 on a row's first
-// segment.
-template <int BS, int MB>
-__global__ void k_seg_pack(int64_t npos, int which, const int2 *__restrict__ pmap, const uint16_t *__restrict__ prow,
-                           const int32_t *__restrict__ bptr, const uint16_t *__restrict__ bcol,
-                           const double *__restrict__ val, const double *__restrict__ dval, uint64_t *desc,
-                           double *sval) {
-    constexpr int BB = BS * BS;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= npos) return;
-    const int NV = (MB + which) * BS;
-    double *o = sval + q * BS * NV;
-    const int2 e = pmap[q];
-    int32_t b0 = 0, b1 = 0, bx = -1;  // segment blocks [b0, b1); bx: a continuation's extra block (upper)
-    int k = 0;
-    uint64_t d;
-    if (e.x < 0) {
-        d = 0x8000ull;
-        for (int j = 0; j < 3; ++j) d |= 0x7fffull << (16 * (j + 1));
-    } else {
-        k = e.y & 0xff;
-        const int m = e.y >> 8;
-        const int32_t rb = bptr[e.x], re = bptr[e.x + 1];
-        b0 = rb + (which == 0 || k == 0 ? MB * k : MB + (k - 1) * (MB + 1));
-        b1 = min(b0 + MB, re);
-        if (which == 1 && k > 0 && b0 + MB < re) bx = b0 + MB;
-        d = (uint64_t)(bx >= 0 ? bcol[bx] : prow[e.x]) | (k > 0 ? 0x8000ull : 0ull);
-        for (int j = 0; j < 3; ++j) d |= (uint64_t)(j < MB && b0 + j < b1 ? bcol[b0 + j] : 0x7fff) << (16 * (j + 1));
-        if (k == 0)
-            for (int j = 0; j < 3; ++j)
-                if (((m - 1) >> j) & 1) d |= 1ull << (16 * (j + 1) + 15);
-    }
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-        for (int i = 0; i < BS; ++i)
-#pragma unroll
-            for (int jj = 0; jj < BS; ++jj)
-                o[i * NV + j * BS + jj] = b0 + j < b1 ? val[(int64_t)(b0 + j) * BB + i * BS + jj] : 0.0;
-    if (which == 1)
-#pragma unroll
-        for (int i = 0; i < BS; ++i)
-#pragma unroll
-            for (int jj = 0; jj < BS; ++jj)
-                o[i * NV + MB * BS + jj] = e.x < 0 ? 0.0
-                                           : k == 0 ? dval[(int64_t)e.x * BB + i * BS + jj]
-                                           : bx >= 0 ? val[(int64_t)bx * BB + i * BS + jj] : 0.0;
-    desc[q] = d;
-}
-
-hipError_t launch_seg_pack(dd_ctx *h, int which, hipStream_t st) {
-    const int T = 256;
-    Sweep &w = h->sw[which];
-    const unsigned g = (unsigned)((w.snpos + T - 1) / T);
-    if (w.snpos == 0) return hipSuccess;
-    auto go = [&](auto kern) {
-        kern<<<g, T, 0, st>>>(w.snpos, which, w.pmap, w.prow, w.bptr, w.bcol, w.val64, w.d64, w.desc, w.sval64);
-    };
-    if (h->bs == 3) {
-        if (h->seg == 2) go(k_seg_pack<3, 2>); else go(k_seg_pack<3, 3>);
-    } else {
-        if (h->seg == 2) go(k_seg_pack<1, 2>); else go(k_seg_pack<1, 3>);
-    }
-    return hipGetLastError();
-}
-
-int build_seg_layout(dd_ctx *h, int which, int mb, int cw, int rpw, hipStream_t st) {
-    Sweep &w = h->sw[which];
-    const Levels &L = h->lev[which];
-    const int nsub = h->nsub;
-    int32_t *npos = nullptr, *nchk = nullptr;
-    int rc = h->alloc(&npos, nsub);
-    if (!rc) rc = h->alloc(&nchk, nsub);
-    if (!rc && !w.gpos) rc = h->alloc(&w.gpos, nsub + 1);
-    if (!rc && !w.gchk) rc = h->alloc(&w.gchk, nsub + 1);
-    if (rc) return rc;
-    auto drop = [&](void *q) { h->release(q); };
-    k_seg_walk<false><<<nsub, 256, 0, st>>>(h->S, which, mb, cw, rpw, L.off, L.ptr, w.bptr, npos, nchk, nullptr,
-                                        nullptr, nullptr, nullptr);
-    hipError_t e = exclusive_scan(npos, w.gpos, nsub, h->scan_tmp, st);
-    if (e == hipSuccess) e = exclusive_scan(nchk, w.gchk, nsub, h->scan_tmp, st);
-    int32_t tot[2] = {0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(&tot[0], w.gpos + nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tot[1], w.gchk + nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return h->fail(DD_EHIP, "segmented layout: %s", hipGetErrorString(e));
-    for (void *q : {(void *)w.pmap, (void *)w.chk, (void *)w.desc, (void *)w.sval64, (void *)w.sval32}) drop(q);
-    w.pmap = nullptr; w.chk = nullptr; w.desc = nullptr; w.sval64 = nullptr; w.sval32 = nullptr;
-    const int bb = h->bs * h->bs;
-    w.snpos = tot[0];
-    rc = h->alloc(&w.pmap, tot[0]);
-    if (!rc) rc = h->alloc(&w.chk, tot[1]);
-    if (!rc) rc = h->alloc(&w.desc, tot[0]);
-    if (!rc) rc = h->alloc(&w.sval64, (int64_t)tot[0] * (mb + which) * bb);
-    if (rc) return rc;
-    k_seg_walk<true><<<nsub, 256, 0, st>>>(h->S, which, mb, cw, rpw, L.off, L.ptr, w.bptr, nullptr, nullptr, w.gpos,
-                                       w.gchk, w.pmap, w.chk);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = launch_seg_pack(h, which, st);
-    drop(npos);
-    drop(nchk);
-    if (e != hipSuccess) return h->fail(DD_EHIP, "segmented layout: %s", hipGetErrorString(e));
-    return DD_OK;
-}
-
-// Wave-chunks (see Sweep::wtab): one workgroup per subdomain walks its pieces
-// (levels, or the segmented layout's chunks, whose bit 30 ends a level) 256
-// at a time; a scan over the tile places each piece's chunks.  A
+// Wave-chunks (see Sweep::wtab): one workgroup per subdomain walks its levels
+// 256 at a time; a scan over the tile places each level's chunks.  A
 // subdomain's chunks start at wbase: an upper bound of the chunks before it
-// (a piece of m positions has at most m/rpw + 1), so no count pass is needed.
-__global__ __launch_bounds__(256) void k_wave_chunks(int S, int rpw, int seg, const int32_t *__restrict__ off,
-                                                    const int32_t *__restrict__ lp, const int32_t *__restrict__ gpos,
-                                                    int2 *__restrict__ wtab, int4 *__restrict__ winfo) {
+// (a level of m positions has at most m/rpw + 1), so no count pass is needed.
+__global__ __launch_bounds__(256) void k_wave_chunks(int S, int rpw, const int32_t *__restrict__ off,
+                                                    const int32_t *__restrict__ lp, int2 *__restrict__ wtab,
+                                                    int4 *__restrict__ winfo) {
     __shared__ int sh[65];
     const int s = blockIdx.x;
     const int32_t o = off[s];
-    const int np = off[s + 1] - o - 1;
-    const int64_t pos0 = seg ? (int64_t)gpos[s] : (int64_t)s * S;
-    const int32_t wbase = (int32_t)(pos0 / rpw) + s + o;
-    constexpr int32_t QM = 0x3fffffff;
-    int chunks = 0, level = 0;  // of the tiles before
-    for (int t0 = 0; t0 < np; t0 += blockDim.x) {
-        const int i = t0 + threadIdx.x;
+    const int nl = off[s + 1] - o - 1;
+    const int32_t wbase = (int32_t)((int64_t)s * S / rpw) + s + o;
+    int chunks = 0;  // of the tiles before
+    for (int t0 = 0; t0 < nl; t0 += blockDim.x) {
+        const int l = t0 + threadIdx.x;
         int32_t q0 = 0, q1 = 0;
-        int m = 0, ends = 0;
-        if (i < np) {
-            const int32_t a = lp[o + i];
-            q0 = seg ? a & QM : a;
-            q1 = seg ? lp[o + i + 1] & QM : lp[o + i + 1];
-            m = (q1 - q0 + rpw - 1) / rpw;
-            ends = seg ? (a >> 30) & 1 : 1;
+        if (l < nl) {
+            q0 = lp[o + l];
+            q1 = lp[o + l + 1];
         }
-        int tm, tl;
+        const int m = (q1 - q0 + rpw - 1) / rpw;
+        int tm;
         const int at = chunks + block_excl_scan(m, sh, &tm);
-        const int lv = level + block_excl_scan(ends, sh, &tl);
         for (int k = 0; k < m; ++k) {
             const int32_t p0 = q0 + k * rpw;
-            wtab[wbase + at + k] = make_int2(p0, lv << 8 | min(rpw, q1 - p0));
+            wtab[wbase + at + k] = make_int2(p0, l << 8 | min(rpw, q1 - p0));
         }
         chunks += tm;
-        level += tl;
     }
-    if (threadIdx.x == 0) winfo[s] = make_int4(wbase, chunks, level, 0);
+    if (threadIdx.x == 0) winfo[s] = make_int4(wbase, chunks, nl, 0);
 }
 
 int build_wave_chunks(dd_ctx *h, int which, hipStream_t st) {
     Sweep &w = h->sw[which];
     const Levels &L = h->lev[which];
     const int rpw = kWave / h->bs;
-    const bool seg = h->seg != 0;
-    int32_t pieces = L.ptr_len;
-    if (seg) {
-        hipError_t e = hipMemcpyAsync(&pieces, w.gchk + h->nsub, sizeof(int32_t), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return h->fail(DD_EHIP, "wave chunks: %s", hipGetErrorString(e));
-    }
     for (void *q : {(void *)w.wtab, (void *)w.winfo}) h->release(q);
     w.wtab = nullptr;
     w.winfo = nullptr;
-    int rc = h->alloc(&w.wtab, w.snpos / rpw + h->nsub + pieces + 1);
+    int rc = h->alloc(&w.wtab, w.snpos / rpw + h->nsub + L.ptr_len + 1);
     if (!rc) rc = h->alloc(&w.winfo, h->nsub);
     if (rc) return rc;
-    k_wave_chunks<<<h->nsub, 256, 0, st>>>(h->S, rpw, seg ? 1 : 0, seg ? w.gchk : L.off, seg ? w.chk : L.ptr, w.gpos,
-                                           w.wtab, w.winfo);
+    k_wave_chunks<<<h->nsub, 256, 0, st>>>(h->S, rpw, L.off, L.ptr, w.wtab, w.winfo);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return h->fail(DD_EHIP, "wave chunks: %s", hipGetErrorString(e));
     return DD_OK;
