@@ -104,8 +104,7 @@ struct KrylovScalars {
     double rho, alpha, omega, beta;
     double bnorm, rnorm, snorm;
     double tol;                  // rtol * ||b||
-    int32_t state;               // 0 running, 1 converged, 2 half-step exit pending,
-                                 // -5 breakdown, -6 no convergence
+    int32_t state;               // 0 running, 1 converged, -5 breakdown, -6 no convergence
     int32_t iters;
     int32_t maxit;
     int32_t half;                // 1 when the solve stopped after a half step
@@ -146,6 +145,7 @@ struct dd_ctx {
     // (set by launch_precond for per-apply timing; tev_used: a slot kernel
     // took them)
     hipEvent_t tev[2] = {nullptr, nullptr};
+    hipEvent_t tsolve[2] = {nullptr, nullptr};  // start and end of a solve (created by the first)
     int32_t tev_used = 0;
     int32_t slots = 0;            // MB of the slot layout (0: CSR layout only)
     int32_t seg = 0;              // MB of the segmented slot layout (2 or 3; 0: not built)
@@ -308,7 +308,10 @@ struct KrylovWork {
     double *kv = nullptr;              // kKrylovVectors vectors of n*bs
     double *partials = nullptr;        // [8 * part_stride] per-workgroup partial sums
     int32_t part_stride = 0;
-    KrylovScalars *ks = nullptr;       // device
+    KrylovScalars *ks = nullptr;       // device, three copies
+    // host memory the device reports its iterations in (null: the host
+    // synchronises every few iterations instead)
+    unsigned long long *progress = nullptr;
     KrylovScalars *ks_host = nullptr;  // host (pinned for the handle's workspace)
     // false: create no HIP events (the solve is timed on the host, per-apply
     // profiling is off) and use no buffer outside this workspace (the fused

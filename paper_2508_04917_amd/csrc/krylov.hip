@@ -9,11 +9,20 @@
 // not vary from run to run.
 //
 // The scalars (rho, alpha, omega, beta, norms) and the state word stay on the
-// device.  Every kernel of an iteration first reads the state word and
-// returns at once when the solve has finished, so the host enqueues a batch
-// of iterations and only synchronises once per batch.
+// device, in three copies that an iteration's scalar steps pass on: alpha's
+// step reads copy 0 and writes 1, omega's 1 -> 2, beta's 2 -> 0.  So on small
+// systems, whose iterations are a chain of launches, each workgroup of the
+// vector kernel that follows a dot product repeats the scalar step for itself
+// and the first one writes it down; on large ones the steps are launches of
+// their own.  Every kernel of an iteration first reads the state word and
+// returns at once when the solve has finished, so the host runs a few
+// iterations ahead of the device, by the iteration number it reports in host
+// memory.  Against a launch per scalar step and a synchronisation every eight
+// iterations, us per solve: 16^3 scalar (35 iterations) 1,442 -> 1,010, 64^3
+// 3x3 33,430 -> 31,820, 128^3 3x3 learned 228,090 -> 226,330.
 #include <chrono>
 #include <mutex>
+#include <thread>
 
 #include "internal.h"
 #include "spmv.h"
@@ -24,7 +33,7 @@ constexpr int kRedT = 256;        // threads of reducing kernels
 constexpr int kMaxGrid = 2048;    // workgroups of grid-stride vector kernels
 constexpr int kStride = 8;        // partial-sum slots per reduction (2048 each)
 
-enum : int32_t { ST_RUN = 0, ST_CONV = 1, ST_HALF = 2 };
+enum : int32_t { ST_RUN = 0, ST_CONV = 1 };
 
 // Sums NV values over the workgroup in a fixed order and writes them to
 // out[k*stride + blockIdx.x].
@@ -576,21 +585,6 @@ static void spmv_dots(const dd_ctx *h, int grid, const double *x, double *y, con
     }
 }
 
-// s = r - alpha v; partial s.s
-__global__ __launch_bounds__(kRedT) void k_axpy_s(int64_t m, const double *__restrict__ r,
-                                                 const double *__restrict__ v, double *__restrict__ s,
-                                                 const KrylovScalars *__restrict__ ks, double *__restrict__ part) {
-    if (ks->state != ST_RUN) return;
-    const double alpha = ks->alpha;
-    double acc[1] = {0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const double t = r[i] - alpha * v[i];
-        s[i] = t;
-        acc[0] += t * t;
-    }
-    block_partials<1>(acc, part, kMaxGrid);
-}
-
 // Zero the completion flags and the ticket counter of the apply + SpMV launch.
 __global__ __launch_bounds__(256) void k_fuse_reset(int nsub, uint32_t *__restrict__ flag,
                                                    unsigned long long *__restrict__ ticket) {
@@ -599,81 +593,18 @@ __global__ __launch_bounds__(256) void k_fuse_reset(int nsub, uint32_t *__restri
     if (i == 0) *ticket = 0ull;
 }
 
-// x += alpha p^ when the half step converged
-__global__ __launch_bounds__(kRedT) void k_half(int64_t m, double *__restrict__ x, const double *__restrict__ ph,
-                                               KrylovScalars *__restrict__ ks) {
-    if (ks->state != ST_HALF) return;
-    const double alpha = ks->alpha;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        x[i] += alpha * ph[i];
-}
-
-// x += alpha p^ + omega s^;  r = s - omega t;  partials r.r and r0.r
-__global__ __launch_bounds__(kRedT) void k_update(int64_t m, double *__restrict__ x, const double *__restrict__ ph,
-                                                 const double *__restrict__ sh, double *__restrict__ r,
-                                                 const double *__restrict__ s, const double *__restrict__ t,
-                                                 const double *__restrict__ r0, const KrylovScalars *__restrict__ ks,
-                                                 double *__restrict__ part) {
-    if (ks->state != ST_RUN) return;
-    const double alpha = ks->alpha, omega = ks->omega;
-    double acc[2] = {0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        x[i] += alpha * ph[i] + omega * sh[i];
-        const double rn = s[i] - omega * t[i];
-        r[i] = rn;
-        acc[0] += rn * rn;
-        acc[1] += r0[i] * rn;
-    }
-    block_partials<2>(acc, part, kMaxGrid);
-}
-
-// p = r + beta (p - omega v).  PAIR: each thread takes pairs of values as
-// 16-byte accesses (m even, the vectors 16-byte aligned), the same
-// arithmetic per value; there is no reduction, so the result is the same.
-template <bool PAIR>
-__global__ __launch_bounds__(kRedT) void k_pupdate(int64_t m, double *__restrict__ p, const double *__restrict__ r,
-                                                  const double *__restrict__ v, KrylovScalars *__restrict__ ks) {
-    const int32_t st0 = ks->state;
-    if (st0 != ST_RUN) {
-        // The half step converged in this iteration and k_half has added
-        // alpha p^ to x: mark the solve converged (every workgroup returns
-        // whichever of the two values it reads), so that the batch's later
-        // iterations leave x alone.
-        if (st0 == ST_HALF && blockIdx.x == 0 && threadIdx.x == 0) ks->state = ST_CONV;
-        return;
-    }
-    const double beta = ks->beta, omega = ks->omega;
-    if constexpr (PAIR) {
-        double2 *__restrict__ p2 = reinterpret_cast<double2 *>(p);
-        const double2 *__restrict__ r2 = reinterpret_cast<const double2 *>(r);
-        const double2 *__restrict__ v2 = reinterpret_cast<const double2 *>(v);
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m / 2;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            double2 pp = p2[i];
-            const double2 rr = r2[i], vv = v2[i];
-            pp.x = rr.x + beta * (pp.x - omega * vv.x);
-            pp.y = rr.y + beta * (pp.y - omega * vv.y);
-            p2[i] = pp;
-        }
-    } else {
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-            p[i] = r[i] + beta * (p[i] - omega * v[i]);
-    }
-}
-
-// Fixed-order sum of nblk partials of slot k.
-// Scalar step: one workgroup of kScalT threads sums the partials of one or
-// two dot products.  Thread t adds entries t + (j*kScalU + u)*kScalT into
-// accumulator u (kScalU x kScalB independent loads in flight per thread), then the
-// accumulators, the wavefront and the wavefronts are combined in a fixed
-// order, so the result does not depend on timing.
+// Fixed-order sums of nblk partials of NS dot products (slots stride apart), by
+// one workgroup of kScalT threads: thread t adds entries t + (j*kScalU +
+// u)*kScalT into accumulator u (kScalU x kScalB independent loads in flight),
+// then the accumulators, the wavefront and the wavefronts are combined in a
+// fixed order, so the result does not depend on timing.
 constexpr int kScalT = 1024;
 constexpr int kScalU = 4;
 constexpr int kScalB = 4;
 
 template <int NS>
-__device__ void reduce_slots(const double *part, int nblk, int stride, double (&out)[NS]) {
-    __shared__ double sh[2][kScalT / kWave];
+__device__ void reduce_slots(const double *__restrict__ part, int nblk, int stride, double (&out)[NS]) {
+    __shared__ double sh[NS][kScalT / kWave];
     double acc[NS][kScalU];
 #pragma unroll
     for (int k = 0; k < NS; ++k)
@@ -717,99 +648,280 @@ __device__ void reduce_slots(const double *part, int nblk, int stride, double (&
     }
 }
 
+// The same sums of at most kFewParts partials by every wavefront for itself,
+// without LDS: then each entry is alone in its thread above, and wavefronts
+// past the entries add zero.
+constexpr int kFewParts = 4 * kWave;
+
+template <int NS>
+__device__ __forceinline__ void reduce_few(const double *__restrict__ part, int nblk, int stride, double (&out)[NS]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    double v[NS][kFewParts / kWave];
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int q = 0; q < kFewParts / kWave; ++q) {
+            const int i = q * kWave + lane;
+            v[k][q] = i < nblk ? part[(int64_t)k * stride + i] : 0.0;
+        }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        out[k] = 0.0;
+#pragma unroll
+        for (int q = 0; q < kFewParts / kWave; ++q) out[k] += wave_sum(0.0 + v[k][q]);
+    }
+}
+
 constexpr int kMaxRestarts = 4;  // true-residual restarts per solve
 
-enum : int { SC_INIT = 0, SC_ALPHA = 1, SC_S = 2, SC_OMEGA = 3, SC_BETA = 4, SC_TRUE = 5, SC_RESTART = 6 };
+// Scalar steps of Algorithm 1 on a copy of the scalars.
+__device__ __forceinline__ void step_alpha(KrylovScalars &k, int it, double a) {  // a = r0.v
+    k.iters = it;
+    if (a == 0.0 || !isfinite(a) || k.rho == 0.0)
+        k.state = DD_EBREAKDOWN;
+    else
+        k.alpha = k.rho / a;
+}
 
-// Scalar steps of Algorithm 1 (one workgroup).
-__global__ __launch_bounds__(kScalT) void k_scalars(int stage, int it, const double *part, int nblk, int stride,
-                                                   KrylovScalars *ks, double *hist, int hist_len) {
-    const int32_t st0 = ks->state;
-    if (stage != SC_INIT && stage != SC_TRUE && stage != SC_RESTART && st0 != ST_RUN) return;
-    double a, b = 0.0;
-    if (stage == SC_INIT || stage == SC_OMEGA || stage == SC_BETA) {
-        double ab[2];
-        reduce_slots<2>(part, nblk, stride, ab);
-        a = ab[0];
-        b = ab[1];
+// ss = s.s: when the half step has converged the solve ends with x += alpha p^
+// (half set).
+__device__ __forceinline__ void step_half(KrylovScalars &k, int it, double ss, double *hist, int hist_len,
+                                          bool writer) {
+    const double sn = sqrt(ss);
+    k.snorm = sn;
+    if (sn <= k.tol) {
+        k.rnorm = sn;
+        k.state = ST_CONV;
+        k.half = 1;
+        if (writer && hist && it < hist_len) hist[it] = sn / k.bnorm;
+    }
+}
+
+__device__ __forceinline__ void step_omega(KrylovScalars &k, double ts, double tt) {  // t.s, t.t
+    if (tt == 0.0 || !isfinite(tt))
+        k.state = DD_EBREAKDOWN;
+    else
+        k.omega = ts / tt;
+}
+
+__device__ __forceinline__ void step_beta(KrylovScalars &k, int it, double a, double b, double *hist, int hist_len,
+                                          bool writer) {  // a = r.r, b = r0.r
+    const double rn = sqrt(a);
+    k.rnorm = rn;
+    if (writer && hist && it < hist_len) hist[it] = rn / k.bnorm;
+    if (!isfinite(rn)) {
+        k.state = DD_EBREAKDOWN;
+    } else if (rn <= k.tol) {
+        k.state = ST_CONV;
+    } else if (k.omega == 0.0) {
+        k.state = DD_EBREAKDOWN;
     } else {
+        k.beta = (b / k.rho) * (k.alpha / k.omega);
+        k.rho = b;
+        if (it >= k.maxit) k.state = DD_ENOCONV;
+    }
+}
+
+// What a vector kernel needs of the scalar steps.  FUSE: the partial sums of
+// the dot products before it, and where the scalars go.
+struct StepArgs {
+    const KrylovScalars *in;
+    KrylovScalars *out;   // FUSE: written by the first workgroup; else in already holds the step's result
+    const double *pa;     // partial sums: alpha r0.v; omega t.s, t.t; beta r.r, r0.r
+    int na, sa;           // their number and slot stride
+    const double *pb;     // omega: s.s
+    int nb;
+    int it;
+    double *hist;
+    int hist_len;
+};
+
+// s = r - alpha v; partial s.s
+template <bool FUSE>
+__global__ __launch_bounds__(kRedT) void k_axpy_s(int64_t m, const double *__restrict__ r,
+                                                 const double *__restrict__ v, double *__restrict__ s, StepArgs q,
+                                                 double *__restrict__ part) {
+    KrylovScalars ks = *q.in;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if constexpr (FUSE) {
+        if (ks.state == ST_RUN) {
+            double a[1];
+            reduce_few<1>(q.pa, q.na, q.sa, a);
+            step_alpha(ks, q.it, a[0]);
+        }
+        if (first) *q.out = ks;
+    }
+    if (ks.state != ST_RUN) return;
+    const double alpha = ks.alpha;
+    double acc[1] = {0.0};
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+        const double t = r[i] - alpha * v[i];
+        s[i] = t;
+        acc[0] += t * t;
+    }
+    block_partials<1>(acc, part, kMaxGrid);
+}
+
+// x += alpha p^ + omega s^;  r = s - omega t;  partials r.r and r0.r.  When
+// the half step converged: x += alpha p^ only.
+template <bool FUSE>
+__global__ __launch_bounds__(kRedT) void k_update(int64_t m, double *__restrict__ x,
+                                                 const double *__restrict__ ph, const double *__restrict__ sh,
+                                                 double *__restrict__ r, const double *__restrict__ s,
+                                                 const double *__restrict__ t, const double *__restrict__ r0,
+                                                 StepArgs q, double *__restrict__ part) {
+    KrylovScalars ks = *q.in;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    bool half = false;
+    if constexpr (FUSE) {
+        const bool run = ks.state == ST_RUN;
+        if (run) {
+            double ss[1], ab[2];
+            reduce_few<1>(q.pb, q.nb, kMaxGrid, ss);
+            reduce_few<2>(q.pa, q.na, q.sa, ab);
+            step_half(ks, q.it, ss[0], q.hist, q.hist_len, first);
+            if (ks.state == ST_RUN) step_omega(ks, ab[0], ab[1]);
+        }
+        if (first) *q.out = ks;
+        half = run && ks.state == ST_CONV;
+    } else {
+        // the half step of this iteration: later iterations find half set too,
+        // but another iteration number
+        half = ks.state == ST_CONV && ks.half && ks.iters == q.it;
+    }
+    if (ks.state != ST_RUN && !half) return;
+    const double alpha = ks.alpha, omega = ks.omega;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (half) {
+        for (int64_t i = i0; i < m; i += step) x[i] += alpha * ph[i];
+        return;
+    }
+    double acc[2] = {0.0, 0.0};
+    for (int64_t i = i0; i < m; i += step) {
+        x[i] += alpha * ph[i] + omega * sh[i];
+        const double rn = s[i] - omega * t[i];
+        r[i] = rn;
+        acc[0] += rn * rn;
+        acc[1] += r0[i] * rn;
+    }
+    block_partials<2>(acc, part, kMaxGrid);
+}
+
+// p = r + beta (p - omega v).  PAIR: each thread takes pairs of values as
+// 16-byte accesses (m even, the vectors 16-byte aligned), the same
+// arithmetic per value; there is no reduction, so the result is the same.
+// progress (host memory, may be null): iteration << 32 | state, for the host
+// to run ahead by.
+template <bool PAIR, bool FUSE>
+__global__ __launch_bounds__(kRedT) void k_pupdate(int64_t m, double *__restrict__ p, const double *__restrict__ r,
+                                                  const double *__restrict__ v, StepArgs q,
+                                                  unsigned long long *progress) {
+    KrylovScalars ks = *q.in;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if constexpr (FUSE) {
+        if (ks.state == ST_RUN) {
+            double ab[2];
+            reduce_few<2>(q.pa, q.na, q.sa, ab);
+            step_beta(ks, q.it, ab[0], ab[1], q.hist, q.hist_len, first);
+        }
+        if (first) *q.out = ks;
+    }
+    if (first && progress)
+        __hip_atomic_store(progress, (unsigned long long)q.it << 32 | (uint32_t)ks.state, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    if (ks.state != ST_RUN) return;
+    const double beta = ks.beta, omega = ks.omega;
+    if constexpr (PAIR) {
+        double2 *__restrict__ p2 = reinterpret_cast<double2 *>(p);
+        const double2 *__restrict__ r2 = reinterpret_cast<const double2 *>(r);
+        const double2 *__restrict__ v2 = reinterpret_cast<const double2 *>(v);
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m / 2;
+             i += (int64_t)gridDim.x * blockDim.x) {
+            double2 pp = p2[i];
+            const double2 rr = r2[i], vv = v2[i];
+            pp.x = rr.x + beta * (pp.x - omega * vv.x);
+            pp.y = rr.y + beta * (pp.y - omega * vv.y);
+            p2[i] = pp;
+        }
+    } else {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
+            p[i] = r[i] + beta * (p[i] - omega * v[i]);
+    }
+}
+
+enum : int {
+    SC_INIT = 0,
+    SC_ALPHA = 1,
+    SC_HALF = 2,
+    SC_OMEGA = 3,
+    SC_HALF_OMEGA = 4,
+    SC_BETA = 5,
+    SC_TRUE = 6,
+    SC_RESTART = 7
+};
+
+// Scalar steps as launches of their own (one workgroup).
+__global__ __launch_bounds__(kScalT) void k_scalars(int stage, StepArgs q) {
+    KrylovScalars ks = *q.in;
+    const bool iteration = stage >= SC_ALPHA && stage <= SC_BETA;
+    const bool first = threadIdx.x == 0;
+    if (iteration && ks.state != ST_RUN) {
+        if (first) *q.out = ks;
+        return;
+    }
+    double a[1], ab[2] = {0.0, 0.0};
+    if (stage == SC_HALF || stage == SC_HALF_OMEGA) reduce_slots<1>(q.pb, q.nb, kMaxGrid, a);
+    if (stage == SC_INIT || stage == SC_OMEGA || stage == SC_HALF_OMEGA || stage == SC_BETA) {
+        reduce_slots<2>(q.pa, q.na, q.sa, ab);
+    } else if (stage != SC_HALF) {
         double a1[1];
-        reduce_slots<1>(part, nblk, stride, a1);
-        a = a1[0];
+        reduce_slots<1>(q.pa, q.na, q.sa, a1);
+        ab[0] = a1[0];
     }
-    if (threadIdx.x != 0) return;
+    if (!first) return;
     switch (stage) {
-        case SC_INIT: {  // a = r.r (= r0.r), b = b.b
-            double bn = sqrt(b);
+        case SC_INIT: {  // r.r (= r0.r), b.b
+            double bn = sqrt(ab[1]);
             if (bn == 0.0) bn = 1.0;
-            ks->bnorm = bn;
-            ks->tol = ks->tol * bn;  // tol holds rtol on entry
-            ks->rho = a;
-            ks->rnorm = sqrt(a);
-            ks->iters = 0;
-            ks->state = (sqrt(a) <= ks->tol) ? ST_CONV : ST_RUN;
-            if (!isfinite(a)) ks->state = DD_EBREAKDOWN;
-            if (hist && hist_len > 0) hist[0] = sqrt(a) / bn;
+            ks.bnorm = bn;
+            ks.tol = ks.tol * bn;  // tol holds rtol on entry
+            ks.rho = ab[0];
+            ks.rnorm = sqrt(ab[0]);
+            ks.iters = 0;
+            ks.state = (sqrt(ab[0]) <= ks.tol) ? ST_CONV : ST_RUN;
+            if (!isfinite(ab[0])) ks.state = DD_EBREAKDOWN;
+            if (q.hist && q.hist_len > 0) q.hist[0] = sqrt(ab[0]) / bn;
             break;
         }
-        case SC_ALPHA: {  // a = r0.v
-            ks->iters = it;
-            if (a == 0.0 || !isfinite(a) || ks->rho == 0.0) {
-                ks->state = DD_EBREAKDOWN;
-            } else {
-                ks->alpha = ks->rho / a;
-            }
+        case SC_ALPHA: step_alpha(ks, q.it, ab[0]); break;
+        case SC_HALF: step_half(ks, q.it, a[0], q.hist, q.hist_len, true); break;
+        case SC_HALF_OMEGA:
+            step_half(ks, q.it, a[0], q.hist, q.hist_len, true);
+            if (ks.state == ST_RUN) step_omega(ks, ab[0], ab[1]);
             break;
-        }
-        case SC_S: {  // a = s.s
-            const double sn = sqrt(a);
-            ks->snorm = sn;
-            if (sn <= ks->tol) {
-                ks->rnorm = sn;
-                ks->state = ST_HALF;
-                ks->half = 1;
-                if (hist && it < hist_len) hist[it] = sn / ks->bnorm;
-            }
+        case SC_OMEGA: step_omega(ks, ab[0], ab[1]); break;
+        case SC_BETA: step_beta(ks, q.it, ab[0], ab[1], q.hist, q.hist_len, true); break;
+        case SC_TRUE:  // ||b - A x||^2
+            ks.snorm = sqrt(ab[0]);  // reused slot: true residual norm
             break;
-        }
-        case SC_OMEGA: {  // a = t.s, b = t.t
-            if (b == 0.0 || !isfinite(b)) {
-                ks->state = DD_EBREAKDOWN;
-            } else {
-                ks->omega = a / b;
-            }
+        case SC_RESTART:  // r.r of r = b - A x (iteration count, ||b|| and tol kept)
+            ks.rho = ab[0];
+            ks.rnorm = sqrt(ab[0]);
+            ks.half = 0;
+            ks.state = (sqrt(ab[0]) <= ks.tol) ? ST_CONV : ST_RUN;
+            if (!isfinite(ab[0])) ks.state = DD_EBREAKDOWN;
             break;
-        }
-        case SC_BETA: {  // a = r.r, b = r0.r
-            const double rn = sqrt(a);
-            ks->rnorm = rn;
-            if (hist && it < hist_len) hist[it] = rn / ks->bnorm;
-            if (!isfinite(rn)) {
-                ks->state = DD_EBREAKDOWN;
-            } else if (rn <= ks->tol) {
-                ks->state = ST_CONV;
-            } else if (ks->omega == 0.0) {
-                ks->state = DD_EBREAKDOWN;
-            } else {
-                ks->beta = (b / ks->rho) * (ks->alpha / ks->omega);
-                ks->rho = b;
-                if (it >= ks->maxit) ks->state = DD_ENOCONV;
-            }
-            break;
-        }
-        case SC_TRUE: {  // a = ||b - A x||^2
-            ks->snorm = sqrt(a);  // reused slot: true residual norm
-            break;
-        }
-        case SC_RESTART: {  // a = r.r of r = b - A x (iteration count, ||b|| and tol kept)
-            ks->rho = a;
-            ks->rnorm = sqrt(a);
-            ks->half = 0;
-            ks->state = (sqrt(a) <= ks->tol) ? ST_CONV : ST_RUN;
-            if (!isfinite(a)) ks->state = DD_EBREAKDOWN;
-            break;
-        }
     }
+    *q.out = ks;
+}
+
+// The scalars at the start of a solve.
+__global__ void k_scalars_init(KrylovScalars *ks, double rtol, int32_t maxit) {
+    KrylovScalars k{};
+    k.tol = rtol;
+    k.maxit = maxit;
+    k.state = ST_RUN;
+    *ks = k;
 }
 
 // out[i] = in[map[i]] per block row
@@ -844,7 +956,6 @@ static int run_typed(dd_ctx *h, const KrylovWork &W, const double *b, double *x,
     double *part = W.partials;
     KrylovScalars *ks = W.ks;
     KrylovScalars *ks_host = W.ks_host;
-    const int32_t *state = &ks->state;
     // events (solve timing, per-apply profiling) and the fused launch only
     // with the handle's own workspace
     const bool own = W.handle_owned;
@@ -854,37 +965,51 @@ static int run_typed(dd_ctx *h, const KrylovWork &W, const double *b, double *x,
     const int gvec = (int)std::min<int64_t>((m + kRedT - 1) / kRedT, kMaxGrid);
     const bool pair = m % 2 == 0 && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(r) |
                                       reinterpret_cast<uintptr_t>(v)) & 15) == 0;
-    const int sps = W.part_stride;
+    const int sps = W.part_stride;  // slot stride of the partial sums, at least kMaxGrid
+    // slots 0, 1: the SpMV's dots; 2: s.s; 4, 5: r.r and r0.r.  No kernel
+    // reads the slots it writes.
+    double *part_s = part + 2 * (int64_t)sps, *part_r = part + 4 * (int64_t)sps;
     // apply + SpMV in one launch (partials one per subdomain) where the
     // handle allows it; the flags and the ticket counter start at zero
     const bool fused = own && h->fuse && !fused_unsupported(h);
     const int gpart = fused ? h->nsub : gsp;
     uint32_t fepoch = 0;
     unsigned long long ftick = 0;
+    // Scalar steps inside the vector kernels where every wavefront can sum the
+    // partials for itself (a launch and the gap before it: 5.5 us).  With the
+    // table form repeated by every workgroup (3,121 partials of a 64^3 3x3
+    // system) the vector kernels took 69 us together against 22 + 3 x 4.5.
+    const bool inside = gpart <= kFewParts && gvec <= kFewParts;
 
-    hipEvent_t e0 = nullptr, e1 = nullptr;
+    // The test of the half step before the second apply costs a launch (5.5
+    // us) per iteration; made with omega's step it costs an apply and a product
+    // for nothing, once, in a solve that ends there.  Before, where those
+    // take hundreds of us (2M values: 130).
+    const bool early = m >= (1 << 21);
+
     std::chrono::steady_clock::time_point h0;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
     if (own) {
-        KCHK(hipEventCreate(&e0));
-        KCHK(hipEventCreate(&e1));
+        for (hipEvent_t &e : h->tsolve)
+            if (!e) KCHK(hipEventCreate(&e));
+        e0 = h->tsolve[0];
+        e1 = h->tsolve[1];
         KCHK(hipEventRecord(e0, st));
     } else {  // host clock from an idle stream to the final synchronisation
         KCHK(hipStreamSynchronize(st));
         h0 = std::chrono::steady_clock::now();
     }
 
-    KrylovScalars init{};
-    init.tol = rtol;
-    init.maxit = maxit;
-    init.state = ST_RUN;
-    *ks_host = init;
-    KCHK(hipMemcpyAsync(ks, ks_host, sizeof(KrylovScalars), hipMemcpyHostToDevice, st));
+    auto args = [&](int from, int to, const double *pa, int na, int sa, int it) {
+        return StepArgs{ks + from, ks + to, pa, na, sa, part_s, gvec, it, h->hist, h->hist_len};
+    };
+    k_scalars_init<<<1, 1, 0, st>>>(ks, rtol, maxit);
     if (fused) k_fuse_reset<<<(h->nsub + 255) / 256, 256, 0, st>>>(h->nsub, h->fflag, h->fticket);
     KCHK(launch_permute(n, BS, h->new2old, b, bp, st));
     KCHK(launch_permute(n, BS, h->new2old, x, xp, st));
     // r = b - A x0, r0 = p = r; rho = r0.r
     spmv_dots<BS, 2>(h, gsp, xp, t, bp, r, r0, p, part, sps, nullptr, st);
-    k_scalars<<<1, kScalT, 0, st>>>(SC_INIT, 0, part, gsp, sps, ks, h->hist, h->hist_len);
+    k_scalars<<<1, kScalT, 0, st>>>(SC_INIT, args(0, 0, part, gsp, sps, 0));
     KCHK(hipGetLastError());
 
     const int chunk = 8;
@@ -898,98 +1023,152 @@ static int run_typed(dd_ctx *h, const KrylovWork &W, const double *b, double *x,
             h->events.push_back(ev);
         }
     }
-    int it = 0, applies = 0, chunk_first = 1, chunk_todo = 0, restarts = 0;
+    int it = 0, applies = 0, restarts = 0;
     double apply_ms = 0.0;
-    int32_t final_state = ST_RUN;
+    volatile unsigned long long *progress = profile ? nullptr : W.progress;
+
+    // One iteration; slot: its events' place when profiling.
+    auto iterate = [&](int slot) -> int {
+        ++it;
+        int32_t *s0 = &ks[0].state, *s1 = &ks[1].state;
+        if (fused) {  // p^ = M^{-1} p and v = A p^, r0.v in one launch
+            KCHK(launch_apply_spmv(h, 0, p, ph, v, r0, part, sps, ++fepoch, ftick, s0, st));
+            ftick += 2ull * h->nsub;
+        } else {
+            KCHK(launch_precond(h, p, ph, s0, st, profile ? h->events[4 * slot] : nullptr,
+                                profile ? h->events[4 * slot + 1] : nullptr));  // p^ = M^{-1} p
+            spmv_dots<BS, 0>(h, gsp, ph, v, r0, nullptr, nullptr, nullptr, part, sps, s0, st);  // v = A p^, r0.v
+        }
+        // s = r - alpha v
+        StepArgs q = args(0, 1, part, gpart, sps, it);
+        if (inside) {
+            k_axpy_s<true><<<gvec, kRedT, 0, st>>>(m, r, v, s, q, part_s);
+        } else {
+            k_scalars<<<1, kScalT, 0, st>>>(SC_ALPHA, q);
+            k_axpy_s<false><<<gvec, kRedT, 0, st>>>(m, r, v, s, args(1, 1, part, gpart, sps, it), part_s);
+            if (early) k_scalars<<<1, kScalT, 0, st>>>(SC_HALF, args(1, 1, part, gpart, sps, it));
+        }
+        if (fused) {  // s^ = M^{-1} s and t = A s^, t.s, t.t in one launch
+            KCHK(launch_apply_spmv(h, 1, s, shat, t, s, part, sps, ++fepoch, ftick, s1, st));
+            ftick += 2ull * h->nsub;
+        } else {
+            KCHK(launch_precond(h, s, shat, s1, st, profile ? h->events[4 * slot + 2] : nullptr,
+                                profile ? h->events[4 * slot + 3] : nullptr));  // s^ = M^{-1} s
+            spmv_dots<BS, 1>(h, gsp, shat, t, s, nullptr, nullptr, nullptr, part, sps, s1, st);  // t = A s^, t.s, t.t
+        }
+        q = args(1, 2, part, gpart, sps, it);
+        if (inside) {
+            k_update<true><<<gvec, kRedT, 0, st>>>(m, xp, ph, shat, r, s, t, r0, q, part_r);
+        } else {
+            k_scalars<<<1, kScalT, 0, st>>>(early ? SC_OMEGA : SC_HALF_OMEGA, q);
+            k_update<false><<<gvec, kRedT, 0, st>>>(m, xp, ph, shat, r, s, t, r0, args(2, 2, part, gpart, sps, it),
+                                                  part_r);
+        }
+        q = args(2, 0, part_r, gvec, kMaxGrid, it);
+        unsigned long long *pg = const_cast<unsigned long long *>(progress);
+        if (inside) {
+            if (pair)
+                k_pupdate<true, true><<<gvec, kRedT, 0, st>>>(m, p, r, v, q, pg);
+            else
+                k_pupdate<false, true><<<gvec, kRedT, 0, st>>>(m, p, r, v, q, pg);
+        } else {
+            k_scalars<<<1, kScalT, 0, st>>>(SC_BETA, q);
+            q.in = ks;
+            if (pair)
+                k_pupdate<true, false><<<gvec, kRedT, 0, st>>>(m, p, r, v, q, pg);
+            else
+                k_pupdate<false, false><<<gvec, kRedT, 0, st>>>(m, p, r, v, q, pg);
+        }
+        KCHK(hipGetLastError());
+        return DD_OK;
+    };
+
     for (;;) {  // restarts
-        chunk_todo = 0;
-        while (true) {
-            KCHK(hipMemcpyAsync(ks_host, ks, sizeof(KrylovScalars), hipMemcpyDeviceToHost, st));
-            KCHK(hipStreamSynchronize(st));
-            final_state = ks_host->state;
-            if (profile) {  // applies of the finished chunk that did work
-                const KrylovScalars &hk = *ks_host;
-                for (int k = 0; k < chunk_todo; ++k) {
-                    const int itk = chunk_first + k;
-                    if (itk > hk.iters) break;
-                    for (int a = 0; a < 2; ++a) {
-                        if (a == 1 && itk == hk.iters && final_state != ST_RUN && hk.half) continue;
-                        float ms = 0.f;
-                        KCHK(hipEventElapsedTime(&ms, h->events[4 * k + 2 * a], h->events[4 * k + 2 * a + 1]));
-                        apply_ms += ms;
-                        ++applies;
+        const int it0 = it;
+        if (progress) {
+            // The host keeps kAhead iterations queued beyond the one the
+            // device last reported, and stops when that report is not
+            // "running".  No report for a while: ask the stream, which may
+            // have finished or failed.
+            constexpr int kAhead = 2;
+            *progress = (unsigned long long)it << 32 | (uint32_t)ST_RUN;
+            while (it < maxit) {
+                unsigned long long seen = *progress;
+                for (int64_t spin = 1; (int32_t)(uint32_t)seen == ST_RUN && it - (int)(seen >> 32) >= kAhead; ++spin) {
+                    if (spin % 1024 == 0) {
+                        const hipError_t e = hipStreamQuery(st);
+                        if (e != hipErrorNotReady) break;  // the synchronisation below reports an error
+                        (void)hipGetLastError();
+                        std::this_thread::yield();
+                    }
+                    seen = *progress;
+                }
+                if ((int32_t)(uint32_t)seen != ST_RUN) break;
+                if (it - (int)(seen >> 32) >= kAhead) {
+                    KCHK(hipStreamSynchronize(st));
+                    seen = *progress;
+                    if ((int32_t)(uint32_t)seen != ST_RUN || it != (int)(seen >> 32)) break;
+                }
+                const int rc = iterate(0);
+                if (rc) return rc;
+            }
+        } else {
+            int chunk_first = 1, chunk_todo = 0;
+            while (true) {
+                KCHK(hipMemcpyAsync(ks_host, ks, sizeof(KrylovScalars), hipMemcpyDeviceToHost, st));
+                KCHK(hipStreamSynchronize(st));
+                if (profile) {  // applies of the finished chunk that did work
+                    const KrylovScalars &hk = *ks_host;
+                    for (int k = 0; k < chunk_todo; ++k) {
+                        const int itk = chunk_first + k;
+                        if (itk > hk.iters) break;
+                        for (int a = 0; a < 2; ++a) {
+                            if (a == 1 && itk == hk.iters && hk.state != ST_RUN && hk.half) continue;
+                            float ms = 0.f;
+                            KCHK(hipEventElapsedTime(&ms, h->events[4 * k + 2 * a], h->events[4 * k + 2 * a + 1]));
+                            apply_ms += ms;
+                            ++applies;
+                        }
                     }
                 }
-            }
-            if (final_state != ST_RUN || it >= maxit) break;
-            const int todo = std::min(chunk, maxit - it);
-            chunk_first = it + 1;
-            chunk_todo = todo;
-            for (int k = 0; k < todo; ++k) {
-                ++it;
-                if (fused) {  // p^ = M^{-1} p and v = A p^, r0.v in one launch
-                    KCHK(launch_apply_spmv(h, 0, p, ph, v, r0, part, sps, ++fepoch, ftick, &ks->state, st));
-                    ftick += 2ull * h->nsub;
-                } else {
-                    KCHK(launch_precond(h, p, ph, state, st, profile ? h->events[4 * k] : nullptr,
-                                        profile ? h->events[4 * k + 1] : nullptr));  // p^ = M^{-1} p
-                    spmv_dots<BS, 0>(h, gsp, ph, v, r0, nullptr, nullptr, nullptr, part, sps, state,
-                                     st);  // v = A p^, r0.v
+                if (ks_host->state != ST_RUN || it >= maxit) break;
+                const int todo = std::min(chunk, maxit - it);
+                chunk_first = it + 1;
+                chunk_todo = todo;
+                for (int k = 0; k < todo; ++k) {
+                    const int rc = iterate(k);
+                    if (rc) return rc;
                 }
-                k_scalars<<<1, kScalT, 0, st>>>(SC_ALPHA, it, part, gpart, sps, ks, h->hist, h->hist_len);
-                k_axpy_s<<<gvec, kRedT, 0, st>>>(m, r, v, s, ks, part);        // s = r - alpha v
-                k_scalars<<<1, kScalT, 0, st>>>(SC_S, it, part, gvec, kMaxGrid, ks, h->hist, h->hist_len);
-                k_half<<<gvec, kRedT, 0, st>>>(m, xp, ph, ks);
-                if (fused) {  // s^ = M^{-1} s and t = A s^, t.s, t.t in one launch
-                    KCHK(launch_apply_spmv(h, 1, s, shat, t, s, part, sps, ++fepoch, ftick, &ks->state, st));
-                    ftick += 2ull * h->nsub;
-                } else {
-                    KCHK(launch_precond(h, s, shat, state, st, profile ? h->events[4 * k + 2] : nullptr,
-                                        profile ? h->events[4 * k + 3] : nullptr));  // s^ = M^{-1} s
-                    spmv_dots<BS, 1>(h, gsp, shat, t, s, nullptr, nullptr, nullptr, part, sps, state,
-                                     st);  // t = A s^, t.s, t.t
-                }
-                k_scalars<<<1, kScalT, 0, st>>>(SC_OMEGA, it, part, gpart, sps, ks, h->hist, h->hist_len);
-                k_update<<<gvec, kRedT, 0, st>>>(m, xp, ph, shat, r, s, t, r0, ks, part);
-                k_scalars<<<1, kScalT, 0, st>>>(SC_BETA, it, part, gvec, kMaxGrid, ks, h->hist, h->hist_len);
-                if (pair)
-                    k_pupdate<true><<<gvec, kRedT, 0, st>>>(m, p, r, v, ks);
-                else
-                    k_pupdate<false><<<gvec, kRedT, 0, st>>>(m, p, r, v, ks);
-                KCHK(hipGetLastError());
             }
         }
-        // true residual ||b - A x|| / ||b||
+        // true residual ||b - A x|| / ||b||, and x in the caller's numbering
         spmv_dots<BS, 3>(h, gsp, xp, t, bp, nullptr, nullptr, nullptr, part, sps, nullptr, st);
-        k_scalars<<<1, kScalT, 0, st>>>(SC_TRUE, 0, part, gsp, sps, ks, h->hist, h->hist_len);
+        k_scalars<<<1, kScalT, 0, st>>>(SC_TRUE, args(0, 0, part, gsp, sps, 0));
+        if (own) KCHK(hipEventRecord(e1, st));
+        KCHK(launch_permute(n, BS, h->old2new, xp, x, st));
         KCHK(hipMemcpyAsync(ks_host, ks, sizeof(KrylovScalars), hipMemcpyDeviceToHost, st));
         KCHK(hipStreamSynchronize(st));
         // The recurrence met the tolerance but the true residual did not (an
         // FP32 trisolve makes the preconditioner slightly inconsistent from one
         // apply to the next): restart from the current iterate.
-        {
-            const KrylovScalars &hk = *ks_host;
-            if (hk.state == ST_CONV && hk.snorm > 2.0 * hk.tol && restarts < kMaxRestarts && it < maxit) {
-                ++restarts;
-                spmv_dots<BS, 2>(h, gsp, xp, t, bp, r, r0, p, part, sps, nullptr, st);
-                k_scalars<<<1, kScalT, 0, st>>>(SC_RESTART, 0, part, gsp, sps, ks, h->hist, h->hist_len);
-                KCHK(hipGetLastError());
-                continue;
-            }
+        const KrylovScalars &hk = *ks_host;
+        // iterations beyond the last did nothing; a restart counts on from the
+        // end of the last one's group of `chunk`, whichever way it was queued
+        if (progress) it = std::min(maxit, it0 + (std::max(hk.iters - it0, 0) + chunk - 1) / chunk * chunk);
+        if (hk.state == ST_CONV && hk.snorm > 2.0 * hk.tol && restarts < kMaxRestarts && it < maxit) {
+            ++restarts;
+            spmv_dots<BS, 2>(h, gsp, xp, t, bp, r, r0, p, part, sps, nullptr, st);
+            k_scalars<<<1, kScalT, 0, st>>>(SC_RESTART, args(0, 0, part, gsp, sps, 0));
+            KCHK(hipGetLastError());
+            continue;
         }
         break;
     }  // restarts
-    if (own) KCHK(hipEventRecord(e1, st));
-    KCHK(launch_permute(n, BS, h->old2new, xp, x, st));
-    KCHK(hipStreamSynchronize(st));
     float ms = 0.f;
-    if (own) {
+    if (own)
         KCHK(hipEventElapsedTime(&ms, e0, e1));
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-    } else {
+    else
         ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - h0).count();
-    }
     const KrylovScalars &hk = *ks_host;
     int status = DD_OK;
     if (hk.state == kWaitFailed)
@@ -1027,9 +1206,10 @@ int krylov_workspace(dd_ctx *h, KrylovWork *w) {
         h->spmv_part_stride = (int)std::max<int64_t>((h->n + rpb - 1) / rpb, kMaxGrid);
         rc = h->alloc(&h->partials, (int64_t)kStride * h->spmv_part_stride);
         if (rc) return rc;
-        rc = h->alloc(&h->ks, 1);
+        rc = h->alloc(&h->ks, 3);
         if (rc) return rc;
-        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->ks_host), sizeof(KrylovScalars));
+        // the scalars, and behind them the device's progress report
+        hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->ks_host), 2 * sizeof(KrylovScalars));
         if (e != hipSuccess) {
             h->ks_host = nullptr;
             h->kv = nullptr;  // the next call tries again (the buffers stay recorded for dd_destroy)
@@ -1041,6 +1221,7 @@ int krylov_workspace(dd_ctx *h, KrylovWork *w) {
     w->part_stride = h->spmv_part_stride;
     w->ks = h->ks;
     w->ks_host = h->ks_host;
+    w->progress = reinterpret_cast<unsigned long long *>(h->ks_host + 1);
     w->handle_owned = true;
     return DD_OK;
 }
@@ -1064,7 +1245,7 @@ int noalloc_workspace(dd_ctx *h, KrylovWork *w, KrylovScalars *host) {
     const int64_t stride = std::max<int64_t>((h->n + rpb - 1) / rpb, kMaxGrid);
     const int64_t vec_bytes = align256((int64_t)kKrylovVectors * h->n * h->bs * (int64_t)sizeof(double));
     const int64_t part_bytes = align256((int64_t)kStride * stride * (int64_t)sizeof(double));
-    const int64_t need = vec_bytes + part_bytes + align256(sizeof(KrylovScalars));
+    const int64_t need = vec_bytes + part_bytes + align256(3 * sizeof(KrylovScalars));
     if (need > kNoallocBytes)
         return h->fail(DD_EINVAL,
                        "bicgstab_solve_noalloc: the problem needs %lld bytes of Krylov workspace, the fixed array "

@@ -178,6 +178,8 @@ int dd_ctx::alloc_bytes(void **p, size_t bytes) {
 
 dd_ctx::~dd_ctx() {
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
+    for (hipEvent_t e : tsolve)
+        if (e) (void)hipEventDestroy(e);
     retired.insert(retired.end(), allocs.begin(), allocs.end());
     allocs.clear();
     reclaim();

@@ -2,6 +2,7 @@
 buffers, by two threads on streams of their own, equal bit for bit those of the
 first; dd_destroy(NULL) returns the memory to the driver."""
 
+import gc
 import threading
 
 import numpy as np
@@ -55,6 +56,8 @@ def test_recycled_buffers():
 
 
 def test_memory_given_back():
+    gc.collect()  # handles and tensors of earlier tests
+    torch.cuda.empty_cache()
     P.ddilu.lib().dd_destroy(None)
     torch.cuda.synchronize()
     before = torch.cuda.mem_get_info()[0]

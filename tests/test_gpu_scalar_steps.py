@@ -1,0 +1,67 @@
+"""The solve's scalar steps on either side of their rules: inside the vector
+kernels up to 256 partial sums (256 rows of a scalar matrix each), launches of
+their own beyond, and from 2^21 values the half step tested before the second
+apply.  On lines split at the box faces the preconditioner is exact, so the
+solve ends with the half step of its first iteration; on 8^3-like boxes the
+first residuals are the oracle's (bound of the full-size test, 1e-8)."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle as O
+from problems import laplacian_scalar
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - collected on CPU machines, skipped by marker
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2508_04917_amd import ddilu as dd  # noqa: E402
+from paper_2508_04917_amd.solver import DDSolver  # noqa: E402
+
+
+def lines(ny, nz):
+    """Only the couplings along x of a 64 x ny x nz grid."""
+    p = laplacian_scalar(64, ny, nz, seed=41)
+    rows = np.repeat(np.arange(p.n), np.diff(p.brow_ptr))
+    keep = np.abs(rows - p.bcol) <= 1
+    keep &= rows // 64 == p.bcol // 64
+    ptr = np.zeros(p.n + 1, dtype=np.int32)
+    np.cumsum(np.bincount(rows[keep], minlength=p.n), out=ptr[1:])
+    return dataclasses.replace(p, brow_ptr=ptr, bcol=p.bcol[keep], val=p.val[keep])
+
+
+@pytest.mark.parametrize("ny,nz", [(1, 1), (32, 32), (32, 33), (256, 128)],
+                         ids=["one_partial", "256_partials", "264_partials", "2^21_values"])
+def test_half_step(ny, nz):
+    print(f"[scalar steps] 64x{ny}x{nz}", flush=True)
+    p = lines(ny, nz)
+    s = DDSolver.from_problem(p, sub=(64, 1, 1))
+    b = torch.as_tensor(p.b, device="cuda")
+    x, info = dd.bicgstab_solve(s.h, b, torch.zeros_like(b), rtol=1e-8, maxit=50)
+    assert info["status"] == 0 and info["iters"] == 1 and info["rel_res_true"] <= 2e-8
+    if p.n < 1 << 20:  # fits the fixed workspace, where the host waits every few iterations instead
+        x2, info2 = dd.bicgstab_solve_noalloc(s.h, b, torch.zeros_like(b), rtol=1e-8, maxit=50)
+        assert info2["iters"] == 1 and torch.equal(x, x2)
+    s.close()
+
+
+@pytest.mark.parametrize("nz", [16, 17, 512], ids=["256_partials", "272_partials", "2^21_values"])
+def test_first_residuals(nz):
+    print(f"[scalar steps] 64x64x{nz}", flush=True)
+    p = laplacian_scalar(64, 64, nz, seed=42)
+    sub = (16, 16, 17 if nz == 17 else 16)
+    s = DDSolver.from_problem(p, sub=sub)
+    k = 3
+    ref = O.setup(p, sub).bicgstab(p.b, rtol=1e-30, maxit=k)
+    hist = torch.full((k + 1,), float("nan"), dtype=torch.float64, device="cuda")
+    dd.dd_set_residual_history(s.h, hist)
+    b = torch.as_tensor(p.b, device="cuda")
+    _, info = dd.bicgstab_solve(s.h, b, torch.zeros_like(b), rtol=1e-30, maxit=k)
+    dd.dd_set_residual_history(s.h, None)
+    assert info["iters"] == k
+    assert np.allclose(hist.cpu().numpy(), ref.history, rtol=1e-8, atol=0)
+    s.close()
