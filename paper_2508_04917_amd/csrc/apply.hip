@@ -936,6 +936,22 @@ __device__ __forceinline__ void apply_slots_sub(
     store_slice<TC, !LIC>(zs, y, S * BS, tid, nt);
 }
 
+// The subdomain (.x, an index along the grid's x) and the right-hand side (.y)
+// a workgroup of a batch takes.  Workgroups go round the 8 XCDs in launch
+// order, and each XCD has an L2 of its own: it gets a contiguous run of the
+// items ordered right-hand side fastest, so the right-hand sides of a
+// subdomain run side by side on one L2 and stream its factors from memory
+// once.  The runs' lengths (T / 8, one more in the first T % 8) are the
+// numbers of workgroups each XCD gets, so every item is taken once.  A single
+// right-hand side reads every factor once whatever the order.
+__device__ __forceinline__ uint2 batch_item() {
+    const uint32_t Q = gridDim.y;
+    if (Q == 1) return make_uint2(blockIdx.x, 0u);
+    const uint32_t T = gridDim.x * Q, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7u;
+    const uint32_t item = xcd * (T >> 3) + min(xcd, T & 7u) + (id >> 3), s = item / Q;
+    return make_uint2(s, item - s * Q);
+}
+
 template <int BS, typename TS, typename TC, int NT, int MB, int PD, bool LIC, bool SEG = false>
 __global__ __launch_bounds__(NT) void k_dd_apply_slots(
     const double *__restrict__ r, double *__restrict__ z, int S, SlotTabs tabs, const uint64_t *__restrict__ Ldesc,
@@ -944,15 +960,15 @@ __global__ __launch_bounds__(NT) void k_dd_apply_slots(
     const int32_t *__restrict__ Ugpos) {
     const int stopped = state != nullptr ? *state : 0;  // enclosing solve already finished
     extern __shared__ unsigned char dd_smem[];
-    // right-hand side blockIdx.y of a batch stored one after another
-    const int64_t off = (int64_t)blockIdx.y * vstride;
-    apply_slots_sub<BS, TS, TC, MB, PD, LIC, SEG>(reinterpret_cast<TC *>(dd_smem), blockIdx.x, r + off, z + off, S,
+    const uint2 item = batch_item();
+    const int64_t off = (int64_t)item.y * vstride;  // a batch's right-hand sides lie one after another
+    apply_slots_sub<BS, TS, TC, MB, PD, LIC, SEG>(reinterpret_cast<TC *>(dd_smem), (int)item.x, r + off, z + off, S,
                                                   tabs, Ldesc, Lval, Udesc, Uval, la, stopped, Lgpos, Ugpos);
 }
 
 // ------------------------------------------------------------------------
 // One sweep of the global (undecomposed) ILU0 over the subdomains of one level
-// of the subdomain graph, right-hand side blockIdx.y: the subdomain's slice
+// of the subdomain graph and one right-hand side: the subdomain's slice
 // (src) and its halo, the rows of finished subdomains it depends on (z), in
 // LDS, then the slot sweep on descriptors that number the halo rows after the
 // subdomain's own.  The columns of a row outside the subdomain come before
@@ -968,8 +984,9 @@ __global__ __launch_bounds__(512) void k_dd_apply_slots_global(
     const uint64_t *__restrict__ desc, const double *__restrict__ sval, int64_t vstride) {
     extern __shared__ unsigned char dd_smem[];
     double *y = reinterpret_cast<double *>(dd_smem);
-    const int s = box[blockIdx.x];
-    const int64_t base = (int64_t)s * S, rhs = (int64_t)blockIdx.y * vstride;
+    const uint2 item = batch_item();
+    const int s = box[item.x];
+    const int64_t base = (int64_t)s * S, rhs = (int64_t)item.y * vstride;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nt / kWave;
     const int4 wi = winfo[s];

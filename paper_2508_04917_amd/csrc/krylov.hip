@@ -18,7 +18,7 @@
 // returns at once when the solve has finished, so the host runs a few
 // iterations ahead of the device, by the iteration number it reports in host
 // memory.  Against a launch per scalar step and a synchronisation every eight
-// iterations, us per solve: 16^3 scalar (35 iterations) 1,442 -> 1,010, 64^3
+// iterations, us per solve: 16^3 scalar (23 iterations) 1,442 -> 1,010, 64^3
 // 3x3 33,430 -> 31,820, 128^3 3x3 learned 228,090 -> 226,330.
 #include <chrono>
 #include <mutex>
