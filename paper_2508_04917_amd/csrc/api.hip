@@ -400,6 +400,7 @@ static int ensure_csr(dd_ctx *h, hipStream_t st) {
     const int bb = h->bs * h->bs;
     int32_t *cnt = nullptr;
     RCHK(h->alloc(&cnt, h->n));
+    HCHK(launch_lu_blocks(h, st));
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
         if (!s.prow) {
@@ -591,6 +592,7 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     if (status[2] != 0x7fffffff)
         return h->fail(DD_EZEROPIVOT, "singular or ill-conditioned pivot block at reordered block row %d", status[2]);
     // ILDU0 scaling and the streaming layouts, into the existing arrays
+    if (h->csr_ready) HCHK(launch_lu_blocks(h, st));
     for (int w = 0; w < 2 && h->csr_ready; ++w) HCHK(launch_pack_fill(h, w, st));
     if (needs_csr(h)) RCHK(ensure_csr(h, st));
     for (int w = 0; w < 2 && h->slots && !h->direct; ++w) HCHK(launch_pack_slots(h, w, st));
@@ -630,7 +632,10 @@ extern "C" int dd_get_factors(dd_handle h, int32_t *ptr, int32_t *col, double *f
     hipStream_t st = as_stream(hip_stream);
     if (ptr) HCHK(hipMemcpyAsync(ptr, h->tptr, (h->n + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     if (col) HCHK(hipMemcpyAsync(col, h->tcol, h->nnzt * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
-    if (f) HCHK(launch_export_factors(h, f, st));
+    if (f) {
+        HCHK(launch_lu_blocks(h, st));
+        HCHK(launch_export_factors(h, f, st));
+    }
     return DD_OK;
 }
 
@@ -643,6 +648,7 @@ static int prepare_variant(dd_ctx *h, const char *who, hipStream_t st) {
     Sweep &U = h->sw[1];
     if (h->variant == 7 && !U.uraw) {
         RCHK(h->alloc(&U.uraw, U.nblk * h->bs * h->bs));
+        HCHK(launch_lu_blocks(h, st));
         HCHK(launch_pack_unscaled(h, st));
     }
     return DD_OK;

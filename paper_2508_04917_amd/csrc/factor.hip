@@ -417,12 +417,13 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
 // A 3x3 row takes four lanes (the fourth repeats the third and stores
 // nothing): lane c holds row c of every block, loads and stores 24
 // contiguous bytes of it, and takes the other rows from its quad's lanes
-// (quad_perm moves, no LDS).  Latency-bound level by level, so all loads of a
+// (quad_perm moves, no LDS).  Latency-bound level by level: all loads of a
 // row are issued together, branch-free (positions past a row's end re-read
-// its diagonal block): one memory round trip a level.  With the loads
-// behind the row's own branches the kernel took 1,786 us on 2,097,152 3x3
-// rows in 512 boxes of 16^3; like this 1,364 us (2.3 TB/s).  It replaces
-// a gather (516 us), the factorisation (1,656) and two packs (864 each).
+// its diagonal block), and a wavefront loads its next chunk's blocks while it
+// computes this one.  Beyond that bound by its stores: 2,097,152 3x3 rows in
+// 512 boxes of 16^3 took 1,330 us with a copy of L and U in the dropped
+// pattern, which few callers read (k_lu_blocks makes it for them), 913 us
+// without (1.1 GB read, 1.2 GB written).
 template <int Q>
 __device__ __forceinline__ double quad_bcast(double v) {
     constexpr int P = Q * 0x55;  // quad_perm: lane Q of each four
@@ -461,45 +462,64 @@ struct FactorRow {
     double *lo, *uo;
 };
 
-template <int BS, int MB, bool LU>
-__device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, bool ok, int c, bool store, bool first,
-                                           const double *__restrict__ aval, double *__restrict__ lrow, double *invd,
-                                           int32_t *status) {
-    constexpr int BB = BS * BS;
-    auto load = [&](const double *p, double (&v)[BS]) {
+// Row c of a row's blocks of A: diagonal, lower, A_JI of the lower columns,
+// upper (positions past the row's end re-read its diagonal block).
+template <int BS, int MB>
+struct FactorVals {
+    double D[BS], a[MB][BS], t[MB][BS], b[MB][BS];
+};
+
+template <int BS>
+__device__ __forceinline__ void load_row(const double *p, double (&v)[BS]) {
 #pragma unroll
-        for (int j = 0; j < BS; ++j) v[j] = p[j];
-    };
+    for (int j = 0; j < BS; ++j) v[j] = p[j];
+}
+
+template <int BS, int MB>
+__device__ __forceinline__ void factor_values(const FactorRow<BS, MB> &R, int c, const double *__restrict__ aval,
+                                              FactorVals<BS, MB> &V) {
+    constexpr int BB = BS * BS;
+    load_row<BS>(aval + R.dg * BB + c * BS, V.D);
+#pragma unroll
+    for (int k = 0; k < MB; ++k) {
+        load_row<BS>(aval + (k < R.nlow ? R.dg - R.nlow + k : R.dg) * BB + c * BS, V.a[k]);
+        load_row<BS>(aval + (R.back[k] >= 0 ? (int64_t)R.back[k] : R.dg) * BB + c * BS, V.t[k]);
+        load_row<BS>(aval + (k < R.nupp ? R.dg + 1 + k : R.dg) * BB + c * BS, V.b[k]);
+    }
+}
+
+// Row c of the lower columns' pivot inverses.
+template <int BS, int MB>
+__device__ __forceinline__ void factor_pivots(const FactorRow<BS, MB> &R, int c, const double *invd,
+                                              double (&iv)[MB][BS]) {
+#pragma unroll
+    for (int k = 0; k < MB; ++k) load_row<BS>(invd + (k < R.nlow ? R.J[k] : R.gi) * BS * BS + c * BS, iv[k]);
+}
+
+template <int BS, int MB>
+__device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, const FactorVals<BS, MB> &V,
+                                           const double (&iv)[MB][BS], bool ok, int c, bool store, bool first,
+                                           double *invd, int32_t *status) {
+    constexpr int BB = BS * BS;
     auto put = [&](double *p, const double (&v)[BS]) {
 #pragma unroll
         for (int j = 0; j < BS; ++j) p[j] = v[j];
     };
-    double D[BS], a[MB][BS], t[MB][BS], b[MB][BS], iv[MB][BS];
-    load(aval + R.dg * BB + c * BS, D);
+    double D[BS];
 #pragma unroll
-    for (int k = 0; k < MB; ++k) {
-        const bool in = k < R.nlow;
-        load(aval + (in ? R.dg - R.nlow + k : R.dg) * BB + c * BS, a[k]);
-        load(aval + (R.back[k] >= 0 ? (int64_t)R.back[k] : R.dg) * BB + c * BS, t[k]);
-        load(aval + (k < R.nupp ? R.dg + 1 + k : R.dg) * BB + c * BS, b[k]);
-        load(invd + (in ? R.J[k] : R.gi) * BB + c * BS, iv[k]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < BS; ++j) D[j] = V.D[j];
 #pragma unroll
     for (int k = 0; k < MB; ++k) {
         double L[BS], w[BS];
-        row_times<BS>(a[k], iv[k], L);
-        row_times<BS>(L, t[k], w);
+        row_times<BS>(V.a[k], iv[k], L);
+        row_times<BS>(L, V.t[k], w);
         const bool in = k < R.nlow;
 #pragma unroll
         for (int j = 0; j < BS; ++j) {
             L[j] = in ? L[j] : 0.0;
             D[j] = in && R.back[k] >= 0 ? D[j] - w[j] : D[j];
         }
-        if (ok && store) {
-            put(R.lo + k * BS, L);
-            if (LU && in) put(lrow + k * BB, L);
-        }
+        if (ok && store) put(R.lo + k * BS, L);
     }
     double piv[BB], inv[BB], ic[BS];
 #pragma unroll
@@ -526,19 +546,15 @@ __device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, bool ok, 
 #pragma unroll
     for (int k = 0; k < MB; ++k) {
         double u[BS];
-        row_times<BS>(ic, b[k], u);
+        row_times<BS>(ic, V.b[k], u);
         const bool in = k < R.nupp;
 #pragma unroll
         for (int j = 0; j < BS; ++j) u[j] = in ? u[j] : 0.0;
-        if (ok && store) {
-            put(R.uo + k * BS, u);
-            if (LU && in) put(lrow + (R.nlow + 1 + k) * BB, b[k]);
-        }
+        if (ok && store) put(R.uo + k * BS, u);
     }
     if (ok && store) {
         put(R.uo + MB * BS, ic);
         put(invd + R.gi * BB + c * BS, ic);
-        if (LU) put(lrow + R.nlow * BB, D);
     }
 }
 
@@ -546,10 +562,11 @@ template <int BS, int MB>
 __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__restrict__ off,
                                                     const int32_t *__restrict__ lptr,
                                                     const uint64_t *__restrict__ desc, const int4 *__restrict__ rec,
-                                                    const double *__restrict__ aval, double *__restrict__ lu,
-                                                    double *invd, double *__restrict__ lval,
-                                                    double *__restrict__ uval, int32_t *status) {
-    constexpr int BB = BS * BS, LR = BS == 3 ? 4 : 1, RPW = kWave / LR, NL = MB * BS, NU = (MB + 1) * BS;
+                                                    const double *__restrict__ aval, double *invd,
+                                                    double *__restrict__ lval, double *__restrict__ uval,
+                                                    int32_t *status) {
+    constexpr int LR = BS == 3 ? 4 : 1, RPW = kWave / LR, NL = MB * BS, NU = (MB + 1) * BS;
+    extern __shared__ int32_t lp[];  // the levels' first positions
     const int s = blockIdx.x;
     const int64_t base = (int64_t)s * S;
     const int32_t o = off[s];
@@ -557,32 +574,72 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
     const int rl = lane / LR, c = min(lane % LR, BS - 1);
     const bool store = lane % LR < BS;
-    int32_t p0 = lptr[o];
-    for (int l = 0; l < nl; ++l) {
-        const int32_t p1 = lptr[o + l + 1];
-        for (int32_t pb = p0 + wave * RPW; pb < p1; pb += nw * RPW) {  // wavefront-uniform
-            const int32_t p = pb + rl;
-            const bool ok = p < p1;
-            const int64_t gp = base + (ok ? p : p0);
-            const int4 r0 = rec[2 * gp], r1 = rec[2 * gp + 1];
-            const uint64_t d = desc[gp];
-            FactorRow<BS, MB> R;
-            R.nlow = r0.w & 0xff;
-            R.nupp = r0.w >> 8;
-            R.gi = base + (int)(d & 0xffff);
-            R.dg = r0.x + R.nlow;
-            const int32_t back[3] = {r1.x, r1.y, r1.z};
-#pragma unroll
-            for (int k = 0; k < MB; ++k) {
-                R.J[k] = base + (int)((d >> (16 * (k + 1))) & 0xffff);
-                R.back[k] = back[k];
-            }
-            R.lo = lval + (gp * BS + c) * NL;
-            R.uo = uval + ((int64_t)r0.z * BS + c) * NU;
-            factor_row<BS, MB, true>(R, ok, c, store, lane % LR == 0, aval, lu + (int64_t)r0.y * BB + c * BS, invd,
-                                     status);
+    for (int i = threadIdx.x; i <= nl; i += blockDim.x) lp[i] = lptr[o + i];
+    __syncthreads();
+
+    // A chunk: up to RPW rows of one level from position pb; this wavefront's
+    // chunks follow each other level by level (l = nl: none left).
+    struct Chunk {
+        int l, pb;
+    };
+    auto settle = [&](Chunk k) -> Chunk {  // to the level that has the position, if this one does not
+        while (k.l < nl && k.pb >= lp[k.l + 1]) {
+            ++k.l;
+            if (k.l < nl) k.pb = lp[k.l] + wave * RPW;
         }
-        p0 = p1;
+        k.l = __builtin_amdgcn_readfirstlane(k.l);
+        k.pb = __builtin_amdgcn_readfirstlane(k.pb);
+        return k;
+    };
+    struct Record {
+        int4 r0, r1;
+        uint64_t d;
+    };
+    auto place = [&](const Chunk &k) -> int64_t {  // a lane past the level's end repeats a row of it
+        if (k.l >= nl) return base;
+        return base + (k.pb + rl < lp[k.l + 1] ? k.pb + rl : lp[k.l]);
+    };
+    auto fetch = [&](const Chunk &k) -> Record {
+        const int64_t gp = place(k);
+        return Record{rec[2 * gp], rec[2 * gp + 1], desc[gp]};
+    };
+    auto row = [&](const Chunk &k, const Record &q) -> FactorRow<BS, MB> {
+        FactorRow<BS, MB> R;
+        R.nlow = q.r0.w & 0xff;
+        R.nupp = q.r0.w >> 8;
+        R.gi = base + (int)(q.d & 0xffff);
+        R.dg = q.r0.x + R.nlow;
+        const int32_t back[3] = {q.r1.x, q.r1.y, q.r1.z};
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            R.J[j] = base + (int)((q.d >> (16 * (j + 1))) & 0xffff);
+            R.back[j] = back[j];
+        }
+        R.lo = lval + (place(k) * BS + c) * NL;
+        R.uo = uval + ((int64_t)q.r0.z * BS + c) * NU;
+        return R;
+    };
+    Chunk k0 = settle({0, wave * RPW}), k1 = settle({k0.l, k0.pb + nw * RPW});
+    Record q0 = fetch(k0), q1 = fetch(k1);
+    FactorVals<BS, MB> v0, v1;
+    factor_values<BS, MB>(row(k0, q0), c, aval, v0);
+    for (int l = 0; l < nl; ++l) {
+        while (k0.l == l) {
+            const FactorRow<BS, MB> R = row(k0, q0);
+            double iv[MB][BS];
+            factor_pivots<BS, MB>(R, c, invd, iv);
+            // the next chunk's blocks and the record of the one after it
+            const Chunk k2 = settle({k1.l, k1.pb + nw * RPW});
+            factor_values<BS, MB>(row(k1, q1), c, aval, v1);
+            const Record q2 = fetch(k2);
+            __builtin_amdgcn_sched_barrier(0);
+            factor_row<BS, MB>(R, v0, iv, k0.pb + rl < lp[l + 1], c, store, lane % LR == 0, invd, status);
+            k0 = k1;
+            k1 = k2;
+            q0 = q1;
+            q1 = q2;
+            v0 = v1;
+        }
         __syncthreads();
     }
 }
@@ -611,7 +668,12 @@ __global__ __launch_bounds__(256) void k_gfactor_slots(int32_t p0, int32_t p1, c
     R.back[0] = r2.x; R.back[1] = r2.y; R.back[2] = r2.z;
     R.lo = lval + ((int64_t)r0.w * BS + c) * MB * BS;
     R.uo = uval + ((int64_t)r1.w * BS + c) * (MB + 1) * BS;
-    factor_row<BS, MB, false>(R, ok, c, lane % LR < BS, lane % LR == 0, aval, nullptr, invd, status);
+    FactorVals<BS, MB> V;
+    double iv[MB][BS];
+    factor_values<BS, MB>(R, c, aval, V);
+    factor_pivots<BS, MB>(R, c, invd, iv);
+    __builtin_amdgcn_sched_barrier(0);
+    factor_row<BS, MB>(R, V, iv, ok, c, lane % LR < BS, lane % LR == 0, invd, status);
 }
 
 // One launch per level of the lower sweep (host offsets lp[0..nlev]).
@@ -644,9 +706,11 @@ hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st) {
     const int rpw = h->bs == 3 ? kWave / 4 : kWave;
     int waves = 1;  // for the widest level, at most 8
     while (waves < 8 && waves * rpw < h->max_level_width) waves *= 2;
+    const size_t lds = (size_t)(L.max_levels + 1) * sizeof(int32_t);
     auto go = [&](auto kern) {
-        kern<<<h->nsub, waves * kWave, 0, st>>>(h->S, L.off, L.ptr, h->sw[0].desc, h->frec, h->aval, h->lu, h->invd,
-                                                h->sw[0].sval64, h->sw[1].sval64, h->status);
+        if (lds > 65536) (void)full_lds(kern);
+        kern<<<h->nsub, waves * kWave, lds, st>>>(h->S, L.off, L.ptr, h->sw[0].desc, h->frec, h->aval, h->invd, h->sw[0].sval64,
+                                                h->sw[1].sval64, h->status);
     };
     switch ((h->bs == 3 ? 0 : 3) + h->slots) {
         case 1: go(k_bilu0_slots<3, 1>); break;
@@ -656,6 +720,40 @@ hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st) {
         case 5: go(k_bilu0_slots<1, 2>); break;
         default: go(k_bilu0_slots<1, 3>); break;
     }
+    return hipGetLastError();
+}
+
+// L and U in the dropped pattern, from the streams and the matrix (the
+// patterns of k_bilu0_slots leave U's off-diagonal blocks as A's): for the
+// CSR streams, the adjoint streams and the export.  Their diagonal blocks are
+// inv_D's, so lu's are not written.  Written with every factorisation, the
+// copy was 1.1 of its 2.3 GB of stores (2,097,152 3x3 rows).
+template <int BS>
+__global__ __launch_bounds__(256) void k_lu_blocks(int64_t n, int MB, const int4 *__restrict__ rec,
+                                                  const double *__restrict__ aval, const double *__restrict__ lval,
+                                                  double *__restrict__ lu) {
+    constexpr int BB = BS * BS;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t p = t / (2 * MB);
+    if (p >= n) return;
+    const int j = (int)(t - p * 2 * MB), k = j < MB ? j : j - MB;
+    const int4 r = rec[2 * p];
+    const int nlow = r.w & 0xff, nupp = r.w >> 8;
+    if (k >= (j < MB ? nlow : nupp)) return;
+    const int at = j < MB ? k : nlow + 1 + k;
+#pragma unroll
+    for (int e = 0; e < BB; ++e)
+        lu[(int64_t)(r.y + at) * BB + e] = j < MB ? lval[(p * BS + e / BS) * MB * BS + k * BS + e % BS]
+                                                  : aval[(int64_t)(r.x + at) * BB + e];
+}
+
+hipError_t launch_lu_blocks(dd_ctx *h, hipStream_t st) {
+    if (!h->direct) return hipSuccess;  // the factorisation left them
+    const unsigned g = (unsigned)((h->n * 2 * h->slots + 255) / 256);
+    if (h->bs == 3)
+        k_lu_blocks<3><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->aval, h->sw[0].sval64, h->lu);
+    else
+        k_lu_blocks<1><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->aval, h->sw[0].sval64, h->lu);
     return hipGetLastError();
 }
 

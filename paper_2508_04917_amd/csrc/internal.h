@@ -128,7 +128,7 @@ struct dd_ctx {
     // dropped pattern and factors
     int64_t nnzt = 0, nlow = 0, nupp = 0;
     int32_t *tptr = nullptr, *tcol = nullptr, *tdiag = nullptr;
-    double *lu = nullptr;       // L\U in the dropped pattern
+    double *lu = nullptr;       // L\U in the dropped pattern (see launch_lu_blocks)
     double *invd = nullptr;     // [n*bb] inv(U_II), reordered row order
     ddilu::Levels lev[2];
     ddilu::Sweep sw[2];
@@ -260,6 +260,7 @@ hipError_t launch_bilu0(dd_ctx *h, hipStream_t st);
 hipError_t launch_slot_records(dd_ctx *h, int32_t *other, hipStream_t st);
 hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st);
 hipError_t launch_pack_count(dd_ctx *h, int which, int32_t *cnt, hipStream_t st);
+hipError_t launch_lu_blocks(dd_ctx *h, hipStream_t st);  // lu, before it is read
 hipError_t launch_pack_fill(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_pack_unscaled(dd_ctx *h, hipStream_t st);
 hipError_t launch_cast32(dd_ctx *h, hipStream_t st);

@@ -612,10 +612,12 @@ int lic_adjoint_streams(dd_ctx *h, hipStream_t st) {
             if (rc) return rc;
         }
     }
+    hipError_t e = launch_lu_blocks(h, st);
+    if (e != hipSuccess) return h->fail(DD_EHIP, "adjoint streams: %s", hipGetErrorString(e));
     for (int w = 0; w < 2; ++w)
         k_pack_adjoint<<<g, T, 0, st>>>(h->n, h->S, w, h->slots, h->tptr, h->tcol, h->lu, h->invd,
                                         h->lev[w].rows, L.adj_val[w]);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return h->fail(DD_EHIP, "adjoint streams: %s", hipGetErrorString(e));
     L.adj_ready = 1;
     return DD_OK;
