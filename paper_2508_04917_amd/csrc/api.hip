@@ -345,6 +345,7 @@ extern "C" int dd_get_reordered(dd_handle h, int32_t *ptr, int32_t *col, double 
 // Level sets of both sweeps, the longest row and the block count of each.
 // stats: eight device words, zero.
 static int build_levels(dd_ctx *h, hipStream_t st, int32_t *stats, int32_t *tmp_i) {
+    if (!h->linv) RCHK(h->alloc(&h->linv, h->n));
     if (!h->uinv) RCHK(h->alloc(&h->uinv, h->n));
     for (int w = 0; w < 2; ++w) {
         Levels &L = h->lev[w];
@@ -444,7 +445,7 @@ static int build_seg(dd_ctx *h, hipStream_t st) {
 
 // Memory of the slot layout (every row has at most kMaxSlots blocks per
 // sweep), its descriptors, tables and factor records.
-static int build_slots(dd_ctx *h, int32_t *other, hipStream_t st) {
+static int build_slots(dd_ctx *h, int32_t *stats, hipStream_t st) {
     const int bb = h->bs * h->bs;
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
@@ -454,7 +455,7 @@ static int build_slots(dd_ctx *h, int32_t *other, hipStream_t st) {
         RCHK(build_wave_chunks(h, w, st));
     }
     if (!h->frec) RCHK(h->alloc(&h->frec, 2 * h->n));
-    HCHK(launch_slot_records(h, other, st));
+    HCHK(launch_slot_records(h, stats, st));
     return DD_OK;
 }
 
@@ -507,7 +508,7 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     int32_t *tbeg = nullptr, *tlen = nullptr, *tsrc = nullptr;
     RCHK(h->alloc(&tbeg, h->n));
     RCHK(h->alloc(&tlen, h->n + 1));
-    int32_t init_status[24] = {0, 0x7fffffff, 0x7fffffff};  // 8-15: level statistics, 16: other patterns
+    int32_t init_status[24] = {0, 0x7fffffff, 0x7fffffff};  // 8-15: level statistics, 16: other patterns, 17: reach
     HCHK(hipMemcpyAsync(h->status, init_status, sizeof(init_status), hipMemcpyHostToDevice, st));
     // drop (Section 3.2)
     HCHK(launch_drop_count(h, tbeg, tlen, st));
@@ -548,6 +549,7 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     release(h, tlen);
     h->max_level_width = status[8 + 4];
     h->direct = h->slots && !status[16];
+    h->reach = status[16 + 1];
     // block ILU0 (Algorithm 5), level-scheduled per subdomain, and the ILDU0
     // post-pass folded into the packing of the two sweeps
     RCHK(factor_values(h, st));

@@ -179,8 +179,8 @@ __global__ void k_plus_one(int64_t m, const int32_t *in, int32_t *out) {
 // rows of each level in ascending local order: a stable counting sort by
 // level.  Each wavefront owns a contiguous run of rows; it counts them per
 // level, the counts are scanned level by level and wavefront by wavefront,
-// and it places its rows 64 at a time, equal levels ranked by lane.  inv
-// (upper sweep): position of each row.  2,097,152 rows, both sweeps: 790 us
+// and it places its rows 64 at a time, equal levels ranked by lane.  linv,
+// uinv: position of each row.  2,097,152 rows, both sweeps: 790 us
 // with one thread per subdomain -> 68 us.
 constexpr int kSortLevels = 1024;  // one level per thread in the scan
 
@@ -191,7 +191,8 @@ __global__ __launch_bounds__(kLevT) void k_level_sort(int S, const int32_t *__re
                                                      const int32_t *__restrict__ off0,
                                                      const int32_t *__restrict__ off1, int32_t *__restrict__ ptr0,
                                                      int32_t *__restrict__ ptr1, int32_t *__restrict__ rows0,
-                                                     int32_t *__restrict__ rows1, int32_t *__restrict__ uinv,
+                                                     int32_t *__restrict__ rows1, int32_t *__restrict__ linv,
+                                                     int32_t *__restrict__ uinv,
                                                      int32_t *__restrict__ stats) {
     extern __shared__ int32_t cnt[];  // [wavefronts][levels]
     __shared__ int sh[65];
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kLevT) void k_level_sort(int S, const int32_t *__re
             if (l == ll) {
                 const int p = p0 + __popcll(same & ((1ull << lane) - 1));
                 rows[p] = i;
-                if (which) uinv[base + i] = (int32_t)(base + p);
+                (which ? uinv : linv)[base + i] = (int32_t)(base + p);
             }
             if (lane == lead) at[ll] = p0 + __popcll(same);
             todo &= ~same;
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(kLevT) void k_level_sort(int S, const int32_t *__re
 // The same sort by one thread per subdomain, for subdomains of more levels
 // than k_level_sort scans.
 __global__ void k_level_lists(int S, int which, const int32_t *lev_g, const int32_t *nlev, const int32_t *off,
-                              int32_t *lptr, int32_t *rows, int32_t *uinv, int32_t *stats) {
+                              int32_t *lptr, int32_t *rows, int32_t *inv, int32_t *stats) {
     extern __shared__ int32_t sm_ll[];
     int32_t *cnt = sm_ll;                                       // nl + 1
     uint16_t *lv = reinterpret_cast<uint16_t *>(sm_ll + S + 1);  // S
@@ -272,7 +273,7 @@ __global__ void k_level_lists(int S, int which, const int32_t *lev_g, const int3
         for (int i = 0; i < S; ++i) {
             const int p = cnt[lv[i]]++;
             rows[base + p] = i;
-            if (which) uinv[base + i] = (int32_t)(base + p);
+            inv[base + i] = (int32_t)(base + p);
         }
         atomicMax(&stats[4], widest);
     }
@@ -318,7 +319,7 @@ hipError_t launch_level_lists(dd_ctx *h, int32_t *stats, hipStream_t st) {
         hipError_t e = full_lds(k_level_sort);
         if (e != hipSuccess) return e;
         k_level_sort<<<dim3(h->nsub, 2), nt, (size_t)(nt / kWave) * nl * sizeof(int32_t), st>>>(
-            h->S, L.lev, U.lev, L.nlev, U.nlev, L.off, U.off, L.ptr, U.ptr, L.rows, U.rows, h->uinv, stats);
+            h->S, L.lev, U.lev, L.nlev, U.nlev, L.off, U.off, L.ptr, U.ptr, L.rows, U.rows, h->linv, h->uinv, stats);
         return hipGetLastError();
     }
     const size_t lds = (size_t)(h->S + 1) * 4 + (size_t)h->S * 2;
@@ -326,7 +327,7 @@ hipError_t launch_level_lists(dd_ctx *h, int32_t *stats, hipStream_t st) {
     if (e != hipSuccess) return e;
     for (int w = 0; w < 2; ++w)
         k_level_lists<<<h->nsub, 64, lds, st>>>(h->S, w, h->lev[w].lev, h->lev[w].nlev, h->lev[w].off, h->lev[w].ptr,
-                                                h->lev[w].rows, h->uinv, stats);
+                                                h->lev[w].rows, w ? h->uinv : h->linv, stats);
     return hipGetLastError();
 }
 
@@ -359,18 +360,22 @@ __global__ __launch_bounds__(256) void k_slot_desc(int64_t n, int S, const int32
 // pattern, upper-sweep position, lower blocks | upper blocks << 8} and, per
 // lower block L_IJ, the position in A's array of A_JI (-1 where row J has no
 // block in column I).  When a lower block's row J shares another column
-// K > J with row I, ILU0 updates more than the pivot block: *other is raised
+// K > J with row I, ILU0 updates more than the pivot block: stats[0] is raised
 // and the general kernel (k_bilu0) factors the matrix.
 __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const int32_t *__restrict__ tptr,
                                                        const int32_t *__restrict__ tcol,
                                                        const int32_t *__restrict__ tdiag,
                                                        const int32_t *__restrict__ tsrc,
                                                        const int32_t *__restrict__ rows0,
+                                                       const int32_t *__restrict__ linv,
                                                        const int32_t *__restrict__ uinv, int4 *__restrict__ rec,
-                                                       int32_t *other) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const int64_t gi = (p / S) * (int64_t)S + rows0[p];
+                                                       int32_t *__restrict__ stats) {
+    __shared__ int far;
+    // threads past the end repeat the last position
+    const int64_t p = min((int64_t)blockIdx.x * blockDim.x + threadIdx.x, n - 1);
+    if (threadIdx.x == 0) far = 0;
+    __syncthreads();
+    const int64_t base = (p / S) * (int64_t)S, gi = base + rows0[p];
     const int32_t tb = tptr[gi], td = tdiag[gi], te = tptr[gi + 1];
     constexpr int ML = 2 * kMaxSlots + 1;  // blocks of a row of the slot layout
     int32_t c[ML], back[kMaxSlots];
@@ -379,16 +384,18 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
     for (int j = 0; j < ML; ++j) c[j] = tcol[min(tb + j, te - 1)];
 #pragma unroll
     for (int j = 1; j < ML; ++j) more |= tb + j < te && c[j] == c[j - 1];  // repeated blocks
-    int32_t jd[kMaxSlots], je[kMaxSlots];
+    int32_t jd[kMaxSlots], je[kMaxSlots], jp[kMaxSlots], back_by = 0;
 #pragma unroll
     for (int k = 0; k < kMaxSlots; ++k) {
         const int32_t J = tb + k < td ? c[k] : (int32_t)gi;
         jd[k] = tdiag[J];
         je[k] = tptr[J + 1];
+        jp[k] = linv[J];
     }
 #pragma unroll
     for (int k = 0; k < kMaxSlots; ++k) {
         back[k] = -1;
+        back_by = max(back_by, (int32_t)p - jp[k]);
         int32_t at = -1;
 #pragma unroll
         for (int u = 1; u <= kMaxSlots; ++u) {
@@ -400,9 +407,14 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
         }
         if (at >= 0) back[k] = tsrc[at];
     }
-    rec[2 * p] = make_int4(tsrc[tb], tb, uinv[gi], (td - tb) | (te - td - 1) << 8);
-    rec[2 * p + 1] = make_int4(back[0], back[1], back[2], 0);
-    if (more) *other = 1;
+    auto local = [&](int32_t q) { return (uint32_t)(q - base) & 0xffffu; };
+    rec[2 * p] = make_int4(tsrc[tb], tb, uinv[gi],
+                           (int32_t)((td - tb) | (te - td - 1) << 8 | local(jp[0]) << 16));
+    rec[2 * p + 1] = make_int4(back[0], back[1], back[2], (int32_t)(local(jp[1]) | local(jp[2]) << 16));
+    if (more) stats[0] = 1;
+    if (back_by > 0) atomicMax(&far, back_by);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(&stats[1], far);
 }
 
 // Block ILU0 (Algorithm 5, IKJ order), the ILDU0 scaling and both sweeps'
@@ -417,13 +429,17 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
 // A 3x3 row takes four lanes (the fourth repeats the third and stores
 // nothing): lane c holds row c of every block, loads and stores 24
 // contiguous bytes of it, and takes the other rows from its quad's lanes
-// (quad_perm moves, no LDS).  Latency-bound level by level: all loads of a
-// row are issued together, branch-free (positions past a row's end re-read
-// its diagonal block), and a wavefront loads its next chunk's blocks while it
-// computes this one.  Beyond that bound by its stores: 2,097,152 3x3 rows in
-// 512 boxes of 16^3 took 1,330 us with a copy of L and U in the dropped
-// pattern, which few callers read (k_lu_blocks makes it for them), 913 us
-// without (1.1 GB read, 1.2 GB written).
+// (quad_perm moves, no LDS).  All loads of a row are issued together,
+// branch-free (positions past a row's end re-read its diagonal block), one
+// chunk ahead.  The inverses pass through a ring in LDS by position (RING),
+// so the barrier between levels waits for no memory access; where the rows
+// reach too far back for the LDS they pass through invd.  One box alone takes
+// 4.7 us a level of 16^3 (7.1 with the inverses through invd and nothing
+// loaded ahead); many are bound by their requests to the L2, pieces of 24
+// bytes.  2,097,152 3x3 rows in 512 boxes of 16^3: 1,330 us with a copy of L
+// and U in the dropped pattern, which few callers read (k_lu_blocks makes it
+// for them), 913 us without, 855 us with the ring (1.1 GB read, 1.2 GB
+// written).
 template <int Q>
 __device__ __forceinline__ double quad_bcast(double v) {
     constexpr int P = Q * 0x55;  // quad_perm: lane Q of each four
@@ -499,7 +515,7 @@ __device__ __forceinline__ void factor_pivots(const FactorRow<BS, MB> &R, int c,
 template <int BS, int MB>
 __device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, const FactorVals<BS, MB> &V,
                                            const double (&iv)[MB][BS], bool ok, int c, bool store, bool first,
-                                           double *invd, int32_t *status) {
+                                           double *invd, int32_t *status, double (&ic)[BS]) {
     constexpr int BB = BS * BS;
     auto put = [&](double *p, const double (&v)[BS]) {
 #pragma unroll
@@ -521,7 +537,7 @@ __device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, const Fac
         }
         if (ok && store) put(R.lo + k * BS, L);
     }
-    double piv[BB], inv[BB], ic[BS];
+    double piv[BB], inv[BB];
 #pragma unroll
     for (int j = 0; j < BS; ++j) {
         if constexpr (BS == 1) {
@@ -558,15 +574,24 @@ __device__ __forceinline__ void factor_row(const FactorRow<BS, MB> &R, const Fac
     }
 }
 
-template <int BS, int MB>
+// LDS writes before it are seen by LDS reads after it; memory accesses stay
+// in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int BS, int MB, bool RING>
 __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__restrict__ off,
                                                     const int32_t *__restrict__ lptr,
                                                     const uint64_t *__restrict__ desc, const int4 *__restrict__ rec,
                                                     const double *__restrict__ aval, double *invd,
                                                     double *__restrict__ lval, double *__restrict__ uval,
-                                                    int32_t *status) {
-    constexpr int LR = BS == 3 ? 4 : 1, RPW = kWave / LR, NL = MB * BS, NU = (MB + 1) * BS;
-    extern __shared__ int32_t lp[];  // the levels' first positions
+                                                    int32_t *status, int ring, int lp_at) {
+    constexpr int BB = BS * BS, LR = BS == 3 ? 4 : 1, RPW = kWave / LR, NL = MB * BS, NU = (MB + 1) * BS;
+    extern __shared__ double pivots[];  // RING: inverse of position p at p mod ring (a power of two)
+    int32_t *lp = reinterpret_cast<int32_t *>(pivots + lp_at);  // the levels' first positions
     const int s = blockIdx.x;
     const int64_t base = (int64_t)s * S;
     const int32_t o = off[s];
@@ -595,18 +620,18 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
         int4 r0, r1;
         uint64_t d;
     };
-    auto place = [&](const Chunk &k) -> int64_t {  // a lane past the level's end repeats a row of it
-        if (k.l >= nl) return base;
-        return base + (k.pb + rl < lp[k.l + 1] ? k.pb + rl : lp[k.l]);
+    auto place = [&](const Chunk &k) -> int {  // a lane past the level's end repeats a row of it
+        if (k.l >= nl) return 0;
+        return k.pb + rl < lp[k.l + 1] ? k.pb + rl : lp[k.l];
     };
     auto fetch = [&](const Chunk &k) -> Record {
-        const int64_t gp = place(k);
+        const int64_t gp = base + place(k);
         return Record{rec[2 * gp], rec[2 * gp + 1], desc[gp]};
     };
     auto row = [&](const Chunk &k, const Record &q) -> FactorRow<BS, MB> {
         FactorRow<BS, MB> R;
         R.nlow = q.r0.w & 0xff;
-        R.nupp = q.r0.w >> 8;
+        R.nupp = q.r0.w >> 8 & 0xff;
         R.gi = base + (int)(q.d & 0xffff);
         R.dg = q.r0.x + R.nlow;
         const int32_t back[3] = {q.r1.x, q.r1.y, q.r1.z};
@@ -615,32 +640,60 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
             R.J[j] = base + (int)((q.d >> (16 * (j + 1))) & 0xffff);
             R.back[j] = back[j];
         }
-        R.lo = lval + (place(k) * BS + c) * NL;
+        R.lo = lval + ((base + place(k)) * BS + c) * NL;
         R.uo = uval + ((int64_t)q.r0.z * BS + c) * NU;
         return R;
     };
+    int lev = 0;  // barriers passed
     Chunk k0 = settle({0, wave * RPW}), k1 = settle({k0.l, k0.pb + nw * RPW});
     Record q0 = fetch(k0), q1 = fetch(k1);
-    FactorVals<BS, MB> v0, v1;
-    factor_values<BS, MB>(row(k0, q0), c, aval, v0);
-    for (int l = 0; l < nl; ++l) {
-        while (k0.l == l) {
-            const FactorRow<BS, MB> R = row(k0, q0);
-            double iv[MB][BS];
-            factor_pivots<BS, MB>(R, c, invd, iv);
-            // the next chunk's blocks and the record of the one after it
-            const Chunk k2 = settle({k1.l, k1.pb + nw * RPW});
-            factor_values<BS, MB>(row(k1, q1), c, aval, v1);
-            const Record q2 = fetch(k2);
-            __builtin_amdgcn_sched_barrier(0);
-            factor_row<BS, MB>(R, v0, iv, k0.pb + rl < lp[l + 1], c, store, lane % LR == 0, invd, status);
-            k0 = k1;
-            k1 = k2;
-            q0 = q1;
-            q1 = q2;
-            v0 = v1;
+    FactorVals<BS, MB> va, vb;
+    factor_values<BS, MB>(row(k0, q0), c, aval, va);
+    // one chunk from v; next: the set for the following chunk's blocks
+    auto step = [&](const FactorVals<BS, MB> &v, FactorVals<BS, MB> &next) {
+        for (; lev < k0.l; ++lev) {
+            if constexpr (RING)
+                lds_barrier();
+            else
+                __syncthreads();
         }
-        __syncthreads();
+        const FactorRow<BS, MB> R = row(k0, q0);
+        double iv[MB][BS];
+        if constexpr (RING) {
+            const int jp[3] = {(int)((uint32_t)q0.r0.w >> 16), q0.r1.w & 0xffff, (int)((uint32_t)q0.r1.w >> 16)};
+#pragma unroll
+            for (int j = 0; j < MB; ++j) load_row<BS>(pivots + ((jp[j] & (ring - 1)) * BB + c * BS), iv[j]);
+        } else {
+            factor_pivots<BS, MB>(R, c, invd, iv);
+        }
+        const Chunk k2 = settle({k1.l, k1.pb + nw * RPW});
+        const Record q2 = fetch(k2);
+        factor_values<BS, MB>(row(k1, q1), c, aval, next);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool ok = k0.pb + rl < lp[k0.l + 1];
+        double ic[BS];
+        factor_row<BS, MB>(R, v, iv, ok, c, store, lane % LR == 0, invd, status, ic);
+        if constexpr (RING) {
+            if (ok && store) {
+#pragma unroll
+                for (int j = 0; j < BS; ++j) pivots[((k0.pb + rl) & (ring - 1)) * BB + c * BS + j] = ic[j];
+            }
+        }
+        k0 = k1;
+        k1 = k2;
+        q0 = q1;
+        q1 = q2;
+    };
+    while (k0.l < nl) {
+        step(va, vb);
+        if (k0.l >= nl) break;
+        step(vb, va);
+    }
+    for (; lev < nl; ++lev) {
+        if constexpr (RING)
+            lds_barrier();
+        else
+            __syncthreads();
     }
 }
 
@@ -669,11 +722,11 @@ __global__ __launch_bounds__(256) void k_gfactor_slots(int32_t p0, int32_t p1, c
     R.lo = lval + ((int64_t)r0.w * BS + c) * MB * BS;
     R.uo = uval + ((int64_t)r1.w * BS + c) * (MB + 1) * BS;
     FactorVals<BS, MB> V;
-    double iv[MB][BS];
+    double iv[MB][BS], ic[BS];
     factor_values<BS, MB>(R, c, aval, V);
     factor_pivots<BS, MB>(R, c, invd, iv);
     __builtin_amdgcn_sched_barrier(0);
-    factor_row<BS, MB>(R, V, iv, ok, c, lane % LR < BS, lane % LR == 0, invd, status);
+    factor_row<BS, MB>(R, V, iv, ok, c, lane % LR < BS, lane % LR == 0, invd, status, ic);
 }
 
 // One launch per level of the lower sweep (host offsets lp[0..nlev]).
@@ -691,13 +744,13 @@ hipError_t launch_gfactor_slots(dd_ctx *h, const std::vector<int32_t> &lp, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_slot_records(dd_ctx *h, int32_t *other, hipStream_t st) {
+hipError_t launch_slot_records(dd_ctx *h, int32_t *stats, hipStream_t st) {
     const int T = 256;
     const unsigned g = (unsigned)((h->n + T - 1) / T);
     k_slot_desc<<<dim3(g, 2), T, 0, st>>>(h->n, h->S, h->tptr, h->tcol, h->tdiag, h->lev[0].rows, h->lev[1].rows,
                                           h->sw[0].desc, h->sw[1].desc);
-    k_factor_records<<<g, T, 0, st>>>(h->n, h->S, h->tptr, h->tcol, h->tdiag, h->tsrc, h->lev[0].rows, h->uinv,
-                                      h->frec, other);
+    k_factor_records<<<g, T, 0, st>>>(h->n, h->S, h->tptr, h->tcol, h->tdiag, h->tsrc, h->lev[0].rows, h->linv,
+                                      h->uinv, h->frec, stats);
     return hipGetLastError();
 }
 
@@ -706,20 +759,38 @@ hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st) {
     const int rpw = h->bs == 3 ? kWave / 4 : kWave;
     int waves = 1;  // for the widest level, at most 8
     while (waves < 8 && waves * rpw < h->max_level_width) waves *= 2;
-    const size_t lds = (size_t)(L.max_levels + 1) * sizeof(int32_t);
+    // The ring holds a row's inverse until every row that reads it is done: no
+    // row reads further back than the records found, and the rows of one
+    // level are written in any order.
+    const size_t lp = (size_t)(L.max_levels + 1) * sizeof(int32_t), one = (size_t)h->bs * h->bs * sizeof(double);
+    int ring = 1;
+    while (ring < h->reach + h->max_level_width) ring *= 2;
+    const bool in_lds = ring * one + lp <= 163840 - 1024;
+    const size_t lds = (in_lds ? ring * one : 0) + lp;
     auto go = [&](auto kern) {
         if (lds > 65536) (void)full_lds(kern);
-        kern<<<h->nsub, waves * kWave, lds, st>>>(h->S, L.off, L.ptr, h->sw[0].desc, h->frec, h->aval, h->invd, h->sw[0].sval64,
-                                                h->sw[1].sval64, h->status);
+        kern<<<h->nsub, waves * kWave, lds, st>>>(h->S, L.off, L.ptr, h->sw[0].desc, h->frec, h->aval, h->invd,
+                                                h->sw[0].sval64, h->sw[1].sval64, h->status, ring,
+                                                in_lds ? ring * h->bs * h->bs : 0);
     };
-    switch ((h->bs == 3 ? 0 : 3) + h->slots) {
-        case 1: go(k_bilu0_slots<3, 1>); break;
-        case 2: go(k_bilu0_slots<3, 2>); break;
-        case 3: go(k_bilu0_slots<3, 3>); break;
-        case 4: go(k_bilu0_slots<1, 1>); break;
-        case 5: go(k_bilu0_slots<1, 2>); break;
-        default: go(k_bilu0_slots<1, 3>); break;
-    }
+    auto pick = [&](auto bs, auto mb) {
+        if (in_lds)
+            go(k_bilu0_slots<decltype(bs)::value, decltype(mb)::value, true>);
+        else
+            go(k_bilu0_slots<decltype(bs)::value, decltype(mb)::value, false>);
+    };
+    auto slots = [&](auto bs) {
+        if (h->slots == 1)
+            pick(bs, std::integral_constant<int, 1>{});
+        else if (h->slots == 2)
+            pick(bs, std::integral_constant<int, 2>{});
+        else
+            pick(bs, std::integral_constant<int, 3>{});
+    };
+    if (h->bs == 3)
+        slots(std::integral_constant<int, 3>{});
+    else
+        slots(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 
@@ -738,7 +809,7 @@ __global__ __launch_bounds__(256) void k_lu_blocks(int64_t n, int MB, const int4
     if (p >= n) return;
     const int j = (int)(t - p * 2 * MB), k = j < MB ? j : j - MB;
     const int4 r = rec[2 * p];
-    const int nlow = r.w & 0xff, nupp = r.w >> 8;
+    const int nlow = r.w & 0xff, nupp = r.w >> 8 & 0xff;
     if (k >= (j < MB ? nlow : nupp)) return;
     const int at = j < MB ? k : nlow + 1 + k;
 #pragma unroll

@@ -132,7 +132,8 @@ struct dd_ctx {
     double *invd = nullptr;     // [n*bb] inv(U_II), reordered row order
     ddilu::Levels lev[2];
     ddilu::Sweep sw[2];
-    int32_t *uinv = nullptr;      // [n] upper-sweep position of each row
+    int32_t *linv = nullptr, *uinv = nullptr;  // [n] lower- and upper-sweep position of each row
+    int32_t reach = 0;            // how many positions back a row's lower columns lie at most (k_factor_records)
     int4 *frec = nullptr;         // [2n] factor records of the slot layout (k_factor_records)
     int32_t direct = 0;           // factored by launch_bilu0_slots (frec valid for ilu0_refactor)
     int32_t csr_ready = 0;        // the sweeps' CSR streams are built (variants 1, 2, 4-8; rows neither slot layout holds)
@@ -255,9 +256,9 @@ hipError_t launch_level_sets(dd_ctx *h, int32_t *stats, hipStream_t st);
 hipError_t launch_plus_one(int64_t m, const int32_t *in, int32_t *out, hipStream_t st);
 hipError_t launch_level_lists(dd_ctx *h, int32_t *stats, hipStream_t st);
 hipError_t launch_bilu0(dd_ctx *h, hipStream_t st);
-// slot descriptors and factor records; *other raised where launch_bilu0_slots
-// does not apply (see k_factor_records)
-hipError_t launch_slot_records(dd_ctx *h, int32_t *other, hipStream_t st);
+// slot descriptors and factor records; stats (zeroed): [0] raised where
+// launch_bilu0_slots does not apply, [1] reach (see k_factor_records)
+hipError_t launch_slot_records(dd_ctx *h, int32_t *stats, hipStream_t st);
 hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st);
 hipError_t launch_pack_count(dd_ctx *h, int which, int32_t *cnt, hipStream_t st);
 hipError_t launch_lu_blocks(dd_ctx *h, hipStream_t st);  // lu, before it is read

@@ -38,6 +38,15 @@ def one_sided(nx, ny, nz, seed):
     return keep(p, ~drop | (rows == p.bcol))
 
 
+def comb(ny, seed):
+    """2 x ny rows, coupled along x everywhere and along y at x = 1: ny rows
+    in the first level, which the rows of the one-row levels after it reach
+    back to (ny positions), so that 2 ny inverses have to stay at hand."""
+    p = random_blocks(2, ny, 1, seed=seed)
+    rows = np.repeat(np.arange(p.n), np.diff(p.brow_ptr))
+    return keep(p, (rows // 2 == p.bcol // 2) | ((rows % 2 == 1) & (p.bcol % 2 == 1)))
+
+
 def triangles(nx, ny, bs, seed):
     """Triangular mesh: three lower neighbours that couple to each other, so
     ILU0 updates off-diagonal blocks too."""
@@ -68,6 +77,10 @@ CASES = {
     "triangles": (lambda: triangles(24, 20, 3, seed=44), (12, 20, 1)),
     "triangles_scalar": (lambda: triangles(64, 30, 1, seed=45), (64, 15, 1)),
     "levels_1100": (lambda: laplacian_scalar(1100, 2, 1, seed=46), (1100, 1, 1)),
+    "inverses_1024": (lambda: comb(512, seed=51), (2, 512, 1)),
+    "inverses_1026": (lambda: comb(513, seed=52), (2, 513, 1)),
+    "inverses_2048": (lambda: comb(1024, seed=53), (2, 1024, 1)),
+    "inverses_2050": (lambda: comb(1025, seed=54), (2, 1025, 1)),  # more than the LDS holds
     "rows_5000": (lambda: laplacian_scalar(25, 20, 20, seed=47), (25, 20, 10)),
     "rows_10240": (lambda: laplacian_scalar(32, 32, 20, seed=48), (32, 32, 10)),
 }
