@@ -68,50 +68,64 @@ __device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int
 // position a row leaves empty); the CSR arrays stay for everything else.
 //
 // k_ell_values writes the reordered matrix's blocks and this copy in one pass
-// over the caller's values: a wavefront takes a group, one lane per value
-// (64 / (BS*BS) rows at a time), every load of the group in flight before the
-// first store.  HBM-bound: one read and two writes of A's blocks, the writes
-// of the CSR copy in pieces of one block (1.3x their bytes measured); 128^3
-// 3x3 blocks: gather 516 + copy 765 us as two kernels -> 1,075 us.
+// over the caller's values, one wavefront per group: it reads the values in
+// CSR order (one lane per value, all loads of the group in flight), writes
+// them so, and passes them through LDS into the copy's order.  Bound by the
+// stores, one read and two writes of A's blocks: 128^3 3x3 blocks, gather 516
+// + copy 765 us as two kernels, 1,070 us with the lanes in the copy's order
+// (its stores to the CSR array then come in pieces of one block) -> 648 us.
 template <int BS>
 __global__ __launch_bounds__(256) void k_ell_values(int64_t n, int64_t ngroup, const int32_t *__restrict__ ptr,
                                                    const int32_t *__restrict__ col,
                                                    const int32_t *__restrict__ src, const double *__restrict__ val,
                                                    double *__restrict__ aval, int32_t *__restrict__ ecol,
                                                    double *__restrict__ eval) {
-    constexpr int RPW = kWave / BS, BB = BS * BS, LP = kWave / BB, NP = RPW / LP;
-    static_assert(NP * LP == RPW, "whole passes");
-    const int lane = threadIdx.x & (kWave - 1), e = lane % BB, q = lane / BB;
+    constexpr int RPW = kWave / BS, BB = BS * BS, NS = kUnroll * RPW;  // rows, slots of a group
+    constexpr int P = (NS * BB + kWave - 1) / kWave;                   // passes over its values
+    __shared__ double vs[4][NS * BB];
+    __shared__ int32_t cs[4][NS], from[4][NS];
+    __shared__ uint16_t at[4][NS];  // a block's slot
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    // LDS is this wavefront's own: its accesses stay in order
+    auto fence = [] { asm volatile("" ::: "memory"); };
     const int64_t nw = (int64_t)gridDim.x * (blockDim.x / kWave);
     for (int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; g < ngroup; g += nw) {
-        int32_t b0[NP], len[NP], from[kUnroll][NP];
-        double v[kUnroll][NP];
+        int l0 = lane;  // opaque: a value's block and place in it are cheaper to compute again than to hold
+        asm volatile("" : "+v"(l0));
+        const int64_t r0 = g * RPW + min(lane, RPW);
+        const int32_t p0 = ptr[min(r0, n)], p1 = ptr[min(r0 + (lane < RPW ? 1 : 0), n)];
+        const int32_t b0 = __shfl(p0, 0), nb = __shfl(p1, RPW - 1) - b0;
+        for (int i = lane; i < NS; i += kWave) cs[w][i] = -1;
+        if (nb < NS)
+            for (int t = lane; t < NS * BB; t += kWave) vs[w][t] = 0.0;
+        for (int i = lane; i < nb; i += kWave) from[w][i] = src[b0 + i];
 #pragma unroll
-        for (int m = 0; m < NP; ++m) {
-            const int64_t row = g * RPW + m * LP + q;
-            const bool in = q < LP && row < n;
-            b0[m] = in ? ptr[row] : 0;
-            len[m] = in ? ptr[row + 1] - b0[m] : 0;
+        for (int k = 0; k < kUnroll; ++k)
+            if (p0 + k < p1) at[w][p0 - b0 + k] = (uint16_t)(k * RPW + lane);
+        fence();
+        double v[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int t = l0 + q * kWave;
+            v[q] = t < nb * BB ? val[(int64_t)from[w][t / BB] * BB + t % BB] : 0.0;
         }
+        for (int i = lane; i < nb; i += kWave) cs[w][at[w][i]] = col[b0 + i];
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k)
-#pragma unroll
-            for (int m = 0; m < NP; ++m) from[k][m] = k < len[m] ? src[b0[m] + k] : -1;
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k)
-#pragma unroll
-            for (int m = 0; m < NP; ++m) v[k][m] = from[k][m] >= 0 ? val[(int64_t)from[k][m] * BB + e] : 0.0;
-        if (q >= LP) continue;
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k)
-#pragma unroll
-            for (int m = 0; m < NP; ++m) {
-                const int64_t slot = (g * kUnroll + k) * RPW + m * LP + q;
-                const bool in = k < len[m];
-                eval[slot * BB + e] = v[k][m];
-                if (in) aval[(int64_t)(b0[m] + k) * BB + e] = v[k][m];
-                if (e == 0) ecol[slot] = in ? col[b0[m] + k] : -1;
+        for (int q = 0; q < P; ++q) {
+            const int t = l0 + q * kWave;
+            if (t < nb * BB) {
+                aval[(int64_t)b0 * BB + t] = v[q];
+                vs[w][at[w][t / BB] * BB + t % BB] = v[q];
             }
+        }
+        fence();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int t = l0 + q * kWave;
+            if (t < NS * BB) eval[g * (NS * BB) + t] = vs[w][t];
+        }
+        for (int i = lane; i < NS; i += kWave) ecol[g * NS + i] = cs[w][i];
+        fence();
     }
 }
 
