@@ -310,6 +310,7 @@ static unsigned mlp_blocks(int64_t nf) {
 // depend on timing.
 constexpr int kWgFaces = 256;  // faces per chunk
 constexpr int kWgTiles = 33;   // 16x16 output tiles over the three layers
+constexpr int kWgU = 16;       // instructions a wavefront loads ahead for
 
 __global__ __launch_bounds__(256) void k_wgrad_mfma(int64_t nf, const float *__restrict__ dOUT,
                                                     const float *__restrict__ G2, const float *__restrict__ G1,
@@ -330,14 +331,26 @@ __global__ __launch_bounds__(256) void k_wgrad_mfma(int64_t nf, const float *__r
     }
     const int i = ti * 16 + (lane & 15), k = tk * 16 + (lane & 15), fl = lane >> 4;
     const int64_t f0 = (int64_t)chunk * kWgFaces;
+    const bool ain = i < na, bin = k < nb;
+    const float bpad = k == nb ? 1.f : 0.f;
+    const float *ap = A + (ain ? i : 0), *bp = B + (bin ? k : 0);
     mf4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int g = 0; g < kWgFaces; g += 4) {
-        const int64_t f = f0 + g + fl;
-        const bool fok = f < nf;
-        const float a = (fok && i < na) ? A[f * na + i] : 0.f;
-        const float b = !fok ? 0.f : (k < nb ? B[f * nb + k] : (k == nb ? 1.f : 0.f));
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+    // kWgU instructions' operands in flight together, loaded without branches
+    // (positions outside re-read a valid one): with the loads behind their
+    // conditions 31 us on 27,648 faces, like this 17 us
+    for (int g = 0; g < kWgFaces; g += 4 * kWgU) {
+        float a[kWgU], b[kWgU];
+#pragma unroll
+        for (int u = 0; u < kWgU; ++u) {
+            const int64_t f = min(f0 + g + 4 * u + fl, nf - 1);
+            a[u] = ap[f * na];
+            b[u] = bp[f * nb];
+        }
+#pragma unroll
+        for (int u = 0; u < kWgU; ++u) {
+            const bool fok = f0 + g + 4 * u + fl < nf;
+            acc = mfma4(fok && ain ? a[u] : 0.f, !fok ? 0.f : (bin ? b[u] : bpad), acc);
+        }
     }
     double *out = part + (int64_t)chunk * kNParam;
     const int col = tk * 16 + (lane & 15);
@@ -351,11 +364,22 @@ __global__ __launch_bounds__(256) void k_wgrad_mfma(int64_t nf, const float *__r
     }
 }
 
-__global__ void k_wgrad_sum(int nchunk, const double *__restrict__ part, float *grad, int accumulate) {
+// One thread per parameter, sixteen chunks' partials in flight (one after
+// another: 28 us for 108 chunks, like this 5.6 us).
+__global__ __launch_bounds__(64) void k_wgrad_sum(int nchunk, const double *__restrict__ part, float *grad,
+                                                  int accumulate) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= kNParam) return;
+    constexpr int U = 16;
     double s = 0.0;
-    for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * kNParam + e];
+    for (int c0 = 0; c0 < nchunk; c0 += U) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = part[(int64_t)min(c0 + u, nchunk - 1) * kNParam + e];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u < nchunk) s += v[u];
+    }
     grad[e] = accumulate ? grad[e] + (float)s : (float)s;
 }
 
@@ -386,61 +410,96 @@ __global__ __launch_bounds__(256) void k_lic_residual(int64_t m, const double *_
     }
 }
 
-// loss += sum_q (sum of partials of probe q) / (Q den_q); one workgroup.
-// Thread t adds partials t, t + kLossT, ... of each probe in order, then a
-// fixed tree over the workgroup, probes in order: the result does not depend
-// on timing.
-constexpr int kLossT = 256;
+// The sum of kSumT values, added in pairs kSumT/2 apart, then kSumT/4, ... 1:
+// lane l of a wavefront holds values l, l + 64, l + 128, l + 192; the result is
+// lane 0's.
+constexpr int kSumT = 256;
+
+__device__ __forceinline__ double tree_sum(const double (&s)[kSumT / 64]) {
+    double t = (s[0] + s[2]) + (s[1] + s[3]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) t += __shfl_down(t, d);
+    return t;
+}
+
+// loss += sum_q (sum of partials of probe q) / (Q den_q); one workgroup, one
+// wavefront per probe (a probe's partials in kSumT strided sums, each in
+// order, then the tree above), probes in order: the result does not depend on
+// timing.  Latency-bound; with the whole workgroup on one probe after another
+// 35 us for 16 probes of 1,296 partials, like this 5.7 us.
+constexpr int kLossT = 1024;
 
 __global__ __launch_bounds__(kLossT) void k_lic_loss(int Q, int nblk, int part_stride,
                                                      const double *__restrict__ part,
                                                      const double *__restrict__ den, double *loss) {
-    __shared__ double sh[kLossT];
+    constexpr int NW = kLossT / 64, U = kSumT / 64, K = 4;  // K entries of each sum in flight
+    __shared__ double sh[NW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     double L = 0.0;
-    for (int q = 0; q < Q; ++q) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kLossT) s += part[q * part_stride + b];
-        sh[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = kLossT / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
+    for (int q0 = 0; q0 < Q; q0 += NW) {
+        const int q = min(q0 + w, Q - 1);
+        double s[U] = {0.0, 0.0, 0.0, 0.0};
+        for (int b0 = lane; b0 < nblk; b0 += K * kSumT) {
+            double v[K][U];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int b = b0 + u * 64 + k * kSumT;
+                    v[k][u] = b < nblk ? part[(int64_t)q * part_stride + b] : 0.0;
+                }
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (b0 + u * 64 + k * kSumT < nblk) s[u] += v[k][u];
         }
-        if (threadIdx.x == 0) L += sh[0] / (Q * den[q]);
+        const double t = tree_sum(s);
+        if (lane == 0) sh[w] = t / (Q * den[q]);
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int k = 0; k < NW && q0 + k < Q; ++k) L += sh[k];
         __syncthreads();
     }
     if (threadIdx.x == 0) *loss += L;
 }
 
-// den_q = ||z_DD,q - z*_q||^2 (one workgroup per probe, fixed order).
-__global__ __launch_bounds__(256) void k_lic_den(int64_t m, const double *__restrict__ zdd,
-                                                 const double *__restrict__ zs, double *den) {
-    const int q = blockIdx.x;
-    __shared__ double sh[256];
+// den_q = ||z_DD,q - z*_q||^2: the strided sums of a probe by kSumT / 64
+// workgroups of one wavefront (one workgroup per probe could not draw its
+// 5.3 MB from memory in less than 105 us at 48^3; like this 50 + 4 us), then the
+// tree.
+__global__ __launch_bounds__(64) void k_lic_den(int64_t m, const double *__restrict__ zdd,
+                                                const double *__restrict__ zs, double *__restrict__ part) {
+    const int q = blockIdx.x, t = blockIdx.y * 64 + threadIdx.x;
+    const double *a = zdd + q * m, *b = zs + q * m;
     double acc = 0.0;
-    constexpr int U = 8;  // loads in flight per thread and vector (one at a time: 442 us for 16 probes of 48^3)
-    for (int64_t i0 = threadIdx.x; i0 < m; i0 += U * (int64_t)blockDim.x) {
-        double a[U], b[U];
+    constexpr int U = 30;  // loads in flight per thread and vector (the wait counter holds 63)
+    for (int64_t i0 = t; i0 < m; i0 += U * kSumT) {
+        double x[U], y[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t i = min(i0 + u * (int64_t)blockDim.x, m - 1);
-            a[u] = zdd[q * m + i];
-            b[u] = zs[q * m + i];
+            const int64_t i = min(i0 + u * kSumT, m - 1);
+            x[u] = a[i];
+            y[u] = b[i];
         }
+        __builtin_amdgcn_sched_barrier(0);  // or each load waits for the one before
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (i0 + u * (int64_t)blockDim.x < m) {
-                const double e = a[u] - b[u];
+            if (i0 + u * kSumT < m) {
+                const double e = x[u] - y[u];
                 acc += e * e;
             }
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) den[q] = sh[0];
+    part[q * kSumT + t] = acc;
+}
+
+__global__ __launch_bounds__(64) void k_lic_den_sum(const double *__restrict__ part, double *__restrict__ den) {
+    const int q = blockIdx.x;
+    double s[kSumT / 64];
+#pragma unroll
+    for (int u = 0; u < kSumT / 64; ++u) s[u] = part[q * kSumT + u * 64 + threadIdx.x];
+    const double t = tree_sum(s);
+    if (threadIdx.x == 0) den[q] = t;
 }
 
 // dC_f[a][b] = sum_q a_q[I][a] r_q[J][b] (FP32 result, FP64 sum).
@@ -698,7 +757,7 @@ int lic_loss_grad_run(dd_ctx *h, const float *params, int Q, const double *R, co
         const int nchunk = (int)((L.nf + kWgFaces - 1) / kWgFaces);
         k_wgrad_mfma<<<dim3(nchunk, (kWgTiles + 3) / 4), 256, 0, st>>>(L.nf, L.dC, L.G2, L.G1, L.H2, L.H1, L.X,
                                                                         L.wpart);
-        k_wgrad_sum<<<(kNParam + 255) / 256, 256, 0, st>>>(nchunk, L.wpart, grad, accumulate);
+        k_wgrad_sum<<<(kNParam + 63) / 64, 64, 0, st>>>(nchunk, L.wpart, grad, accumulate);
     } else if (!accumulate) {
         e = hipMemsetAsync(grad, 0, kNParam * sizeof(float), st);
     }
@@ -709,8 +768,8 @@ int lic_loss_grad_run(dd_ctx *h, const float *params, int Q, const double *R, co
 
 int lic_targets_run(dd_ctx *h, int Q, const double *R, double *Zs, double *den, hipStream_t st) {
     const int64_t m = h->n * 3;
-    double *zdd = nullptr;
-    int rc = h->alloc(&zdd, Q * m);
+    double *zdd = nullptr;  // the plain applies, and behind them the strided sums
+    int rc = h->alloc(&zdd, Q * m + Q * kSumT);
     if (rc) return rc;
     const int32_t saved_prec = h->precision;
     const int32_t saved_active = h->lic.active;
@@ -721,7 +780,8 @@ int lic_targets_run(dd_ctx *h, int Q, const double *R, double *Zs, double *den, 
     h->precision = saved_prec;
     h->lic.active = saved_active;
     if (e == hipSuccess) {
-        k_lic_den<<<Q, 256, 0, st>>>(m, zdd, Zs, den);
+        k_lic_den<<<dim3(Q, kSumT / 64), 64, 0, st>>>(m, zdd, Zs, zdd + Q * m);
+        k_lic_den_sum<<<Q, 64, 0, st>>>(zdd + Q * m, den);
         e = hipStreamSynchronize(st);
     }
     h->release(zdd);
