@@ -35,10 +35,25 @@ constexpr int kStride = 8;        // partial-sum slots per reduction (2048 each)
 
 enum : int32_t { ST_RUN = 0, ST_CONV = 1 };
 
+// The block of rows a workgroup of a product takes.  Workgroups go round the
+// 8 XCDs in launch order, each with an L2 of its own, and neighbouring rows
+// read the same values of x: each XCD takes kRun neighbouring blocks of every
+// 8 kRun (the last, incomplete 8 kRun in launch order).  us per product
+// without / with runs of 4, 16, 64 blocks and with one run per XCD: 160^3 415
+// / 404, 408, 409, 440 (the XCDs then stream far apart); 128^3 213 / 210, 210,
+// 214, 220; graph parts of 3x3 blocks 310 / 306, 302, 304, 316; 64^3 25.4 /
+// 24.9, 24.7, 24.1, 23.8.
+constexpr uint32_t kRun = 8;
+
+__device__ __forceinline__ uint32_t row_block() {
+    const uint32_t id = blockIdx.x, first = id / (8 * kRun) * (8 * kRun), r = id - first;
+    return first + 8 * kRun > gridDim.x ? id : first + (r & 7u) * kRun + (r >> 3);
+}
+
 // Sums NV values over the workgroup in a fixed order and writes them to
-// out[k*stride + blockIdx.x].
+// out[k*stride + blk].
 template <int NV>
-__device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int stride) {
+__device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int stride, uint32_t blk) {
     __shared__ double sh[NV][16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
@@ -52,7 +67,7 @@ __device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int
         for (int k = 0; k < NV; ++k) {
             double t = 0.0;
             for (int i = 0; i < nw; ++i) t += sh[k][i];
-            out[k * stride + blockIdx.x] = t;
+            out[k * stride + blk] = t;
         }
     }
 }
@@ -64,7 +79,7 @@ __device__ __forceinline__ void block_partials(double (&v)[NV], double *out, int
 // end).  In the CSR layout the k-th blocks of a wavefront's rows lie one row
 // length apart, so each load instruction touches RPW separate pieces; here
 // it reads one contiguous run (measured at 160^3: 441 -> 408 us per SpMV,
-// same bits).  One more copy of A's blocks (plus a zero block for each
+// same bits, before the blocks ran by XCD).  One more copy of A's blocks (plus a zero block for each
 // position a row leaves empty); the CSR arrays stay for everything else.
 //
 // k_ell_values writes the reordered matrix's blocks and this copy in one pass
@@ -411,7 +426,7 @@ __device__ __forceinline__ double row_product(const SpmvMat &m, const double *__
 template <int BS, int LAYOUT>
 __global__ __launch_bounds__(kRedT) void k_spmv(SpmvMat m, const double *__restrict__ x, double *__restrict__ y) {
     const int lane = threadIdx.x & 63;
-    const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int64_t gw = ((int64_t)row_block() * blockDim.x + threadIdx.x) >> 6;
     const int c = lane % BS, rl = lane / BS;
     const int64_t row = slot_row<BS, LAYOUT>(m, gw, rl);
     if (row >= 0) y[row * BS + c] = row_product<BS, LAYOUT>(m, x, gw, rl, row, c);
@@ -484,7 +499,7 @@ __global__ __launch_bounds__(1024) void k_spmv_part(SpmvMat m, int S, int spp, c
             acc[0] += rr * rr;
         }
     }
-    if constexpr (MODE != 4) block_partials<NV>(acc, part, part_stride);
+    if constexpr (MODE != 4) block_partials<NV>(acc, part, part_stride, blockIdx.x);
 }
 
 template <int BS, int MODE>
@@ -551,7 +566,8 @@ __global__ __launch_bounds__(kRedT) void k_spmv_dots(SpmvMat m, const double *__
     double acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-    const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const uint32_t blk = row_block();
+    const int64_t gw = ((int64_t)blk * blockDim.x + threadIdx.x) >> 6;
     const int64_t row = slot_row<BS, LAYOUT>(m, gw, rl);
     if (row >= 0) {
         const int64_t e = row * BS + c;
@@ -575,7 +591,7 @@ __global__ __launch_bounds__(kRedT) void k_spmv_dots(SpmvMat m, const double *__
             acc[0] += rr * rr;
         }
     }
-    block_partials<NV>(acc, part, part_stride);
+    block_partials<NV>(acc, part, part_stride, blk);
 }
 
 // Launch k_spmv_dots on the handle's layout.
@@ -773,7 +789,7 @@ __global__ __launch_bounds__(kRedT) void k_axpy_s(int64_t m, const double *__res
         s[i] = t;
         acc[0] += t * t;
     }
-    block_partials<1>(acc, part, kMaxGrid);
+    block_partials<1>(acc, part, kMaxGrid, blockIdx.x);
 }
 
 // x += alpha p^ + omega s^;  r = s - omega t;  partials r.r and r0.r.  When
@@ -818,7 +834,7 @@ __global__ __launch_bounds__(kRedT) void k_update(int64_t m, double *__restrict_
         acc[0] += rn * rn;
         acc[1] += r0[i] * rn;
     }
-    block_partials<2>(acc, part, kMaxGrid);
+    block_partials<2>(acc, part, kMaxGrid, blockIdx.x);
 }
 
 // p = r + beta (p - omega v).  PAIR: each thread takes pairs of values as
