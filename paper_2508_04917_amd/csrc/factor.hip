@@ -434,12 +434,13 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
 // chunk ahead.  The inverses pass through a ring in LDS by position (RING),
 // so the barrier between levels waits for no memory access; where the rows
 // reach too far back for the LDS they pass through invd.  One box alone takes
-// 4.7 us a level of 16^3 (7.1 with the inverses through invd and nothing
+// 4.3 us a level of 16^3 (7.1 with the inverses through invd and nothing
 // loaded ahead); many are bound by their requests to the L2, pieces of 24
-// bytes.  2,097,152 3x3 rows in 512 boxes of 16^3: 1,330 us with a copy of L
-// and U in the dropped pattern, which few callers read (k_lu_blocks makes it
-// for them), 913 us without, 855 us with the ring (1.1 GB read, 1.2 GB
-// written).
+// bytes (a word of each line fetched one chunk earlier: 877 us, 4 wavefronts
+// a box instead of 8: 843).  2,097,152 3x3 rows in 512 boxes of 16^3: 1,330
+// us with a copy of L and U in the dropped pattern, which few callers read
+// (k_lu_blocks makes it for them), 913 us without, 796 us with the ring (1.1
+// GB read, 1.2 GB written).
 template <int Q>
 __device__ __forceinline__ double quad_bcast(double v) {
     constexpr int P = Q * 0x55;  // quad_perm: lane Q of each four
@@ -651,6 +652,11 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
     factor_values<BS, MB>(row(k0, q0), c, aval, va);
     // one chunk from v; next: the set for the following chunk's blocks
     auto step = [&](const FactorVals<BS, MB> &v, FactorVals<BS, MB> &next) {
+        // in flight before the barriers: what does not depend on the levels
+        const Chunk k2 = settle({k1.l, k1.pb + nw * RPW});
+        const Record q2 = fetch(k2);
+        factor_values<BS, MB>(row(k1, q1), c, aval, next);
+        __builtin_amdgcn_sched_barrier(0);
         for (; lev < k0.l; ++lev) {
             if constexpr (RING)
                 lds_barrier();
@@ -666,10 +672,6 @@ __global__ __launch_bounds__(512) void k_bilu0_slots(int S, const int32_t *__res
         } else {
             factor_pivots<BS, MB>(R, c, invd, iv);
         }
-        const Chunk k2 = settle({k1.l, k1.pb + nw * RPW});
-        const Record q2 = fetch(k2);
-        factor_values<BS, MB>(row(k1, q1), c, aval, next);
-        __builtin_amdgcn_sched_barrier(0);
         const bool ok = k0.pb + rl < lp[k0.l + 1];
         double ic[BS];
         factor_row<BS, MB>(R, v, iv, ok, c, store, lane % LR == 0, invd, status, ic);
