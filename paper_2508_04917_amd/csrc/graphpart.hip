@@ -85,35 +85,62 @@ __global__ void k_gp_src(int64_t n, const int32_t *label, const int32_t *segk, c
 }
 
 // one BFS level: the vertices at distance d reach their unvisited neighbours
-// of the same segment (every writer stores the same d + 1).  Few threads have
-// a vertex at d, so a level costs the latency of one vertex: its neighbours
+// of the same segment (every writer stores the same d + 1).  Few vertices are
+// at d, so a level costs a launch and the latency of one vertex: its neighbours
 // are read kNb at a time, all labels and distances of a batch in flight
-// together (one neighbour after another: 14 us a level at 1M vertices).
+// together (one neighbour after another: 14 us a level at 1M vertices), and a
+// workgroup collects the vertices at d among kPer distances per thread before
+// it follows them, which takes a quarter of the workgroups (one distance per
+// thread 6.9 us a level, four 5.9, eight 6.0).
 constexpr int kNb = 8;
+constexpr int kPer = 4;  // distances a thread reads
 
 __global__ __launch_bounds__(kT) void k_gp_level(int64_t n, const int32_t *__restrict__ ptr,
                                                 const int32_t *__restrict__ col, const int32_t *__restrict__ label,
                                                 uint32_t d, uint32_t *dist, int32_t *changed) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n || dist[v] != d) return;
-    const int32_t b = label[v], q0 = ptr[v], q1 = ptr[v + 1];
-    bool any = false;
-    for (int32_t q = q0; q < q1; q += kNb) {
-        int32_t u[kNb], lu[kNb];
-        uint32_t du[kNb];
+    __shared__ int32_t list[kPer * kT];
+    __shared__ int count;
+    if (threadIdx.x == 0) count = 0;
+    const int64_t v0 = kPer * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    uint32_t dv[kPer];
+    if (v0 + kPer <= n) {
 #pragma unroll
-        for (int j = 0; j < kNb; ++j) u[j] = col[min(q + j, q1 - 1)];
-#pragma unroll
-        for (int j = 0; j < kNb; ++j) {
-            lu[j] = label[u[j]];
-            du[j] = dist[u[j]];
+        for (int j = 0; j < kPer; j += 4) {
+            const uint4 t = *reinterpret_cast<const uint4 *>(dist + v0 + j);
+            dv[j] = t.x;
+            dv[j + 1] = t.y;
+            dv[j + 2] = t.z;
+            dv[j + 3] = t.w;
         }
+    } else {
 #pragma unroll
-        for (int j = 0; j < kNb; ++j)
-            if (lu[j] == b && du[j] == kInf) {
-                dist[u[j]] = d + 1;
-                any = true;
+        for (int j = 0; j < kPer; ++j) dv[j] = v0 + j < n ? dist[v0 + j] : kInf;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+        if (dv[j] == d) list[atomicAdd(&count, 1)] = (int32_t)(v0 + j);
+    __syncthreads();
+    bool any = false;
+    for (int i = threadIdx.x; i < count; i += kT) {
+        const int32_t v = list[i], b = label[v], q0 = ptr[v], q1 = ptr[v + 1];
+        for (int32_t q = q0; q < q1; q += kNb) {
+            int32_t u[kNb], lu[kNb];
+            uint32_t du[kNb];
+#pragma unroll
+            for (int j = 0; j < kNb; ++j) u[j] = col[min(q + j, q1 - 1)];
+#pragma unroll
+            for (int j = 0; j < kNb; ++j) {
+                lu[j] = label[u[j]];
+                du[j] = dist[u[j]];
             }
+#pragma unroll
+            for (int j = 0; j < kNb; ++j)
+                if (lu[j] == b && du[j] == kInf) {
+                    dist[u[j]] = d + 1;
+                    any = true;
+                }
+        }
     }
     if (any) *changed = 1;
 }
@@ -182,12 +209,42 @@ constexpr int kLocalT = 1024;
 
 __host__ __device__ constexpr int local_lds(int len) { return (len + 31) / 32 * 32 * 4 + (len + 31) / 32 * 4; }
 
+// k_gp_adj makes that adjacency for the segments that split, one thread per
+// vertex, `per` workgroups a segment (vlist is written for these only): the
+// scattered reads need more than one CU per segment (1M vertices in segments
+// of 32 K to 8 K: 1,279 us a depth inside k_gp_local, 163 + 750 apart).  vlist
+// holds every segment as one run of positions, so a neighbour's position tells
+// its segment.
+__global__ __launch_bounds__(kT) void k_gp_adj(int32_t S, int per, const int32_t *__restrict__ seg,
+                                              const int32_t *__restrict__ segk, const int32_t *__restrict__ ptr,
+                                              const int32_t *__restrict__ col,
+                                              const int32_t *__restrict__ vlist, const int32_t *__restrict__ pos,
+                                              uint16_t *__restrict__ ladj, int2 *__restrict__ range) {
+    const int32_t b = seg[blockIdx.x / per];
+    const uint32_t base = (uint32_t)b * S, len = (uint32_t)segk[b] * S;  // the segment's positions
+    const uint32_t at = (blockIdx.x % per) * kT + threadIdx.x;
+    if (at >= len) return;
+    const int64_t i = (int64_t)base + at;
+    const int32_t v = vlist[i], q0 = ptr[v], q1 = ptr[v + 1];
+    range[i] = make_int2(q0, q1);
+    for (int32_t q = q0; q < q1; q += kNb) {
+        int32_t u[kNb];
+        uint32_t l[kNb];
+#pragma unroll
+        for (int j = 0; j < kNb; ++j) u[j] = col[min(q + j, q1 - 1)];
+#pragma unroll
+        for (int j = 0; j < kNb; ++j) l[j] = (uint32_t)pos[u[j]] - base;
+#pragma unroll
+        for (int j = 0; j < kNb; ++j)
+            if (q + j < q1) ladj[q + j] = l[j] < len ? (uint16_t)l[j] : 0xffff;
+    }
+}
+
 __global__ __launch_bounds__(kLocalT) void k_gp_local(int32_t S, const int32_t *__restrict__ seg,
-                                                     const int32_t *__restrict__ segk,
-                                                     const int32_t *__restrict__ ptr,
-                                                     const int32_t *__restrict__ col, int32_t *label,
+                                                     const int32_t *__restrict__ segk, int32_t *label,
                                                      const int32_t *__restrict__ vlist, int32_t *__restrict__ vnext,
-                                                     int32_t *pos, uint16_t *ladj, int2 *range) {
+                                                     int32_t *pos, const uint16_t *__restrict__ ladj,
+                                                     const int2 *__restrict__ range) {
     extern __shared__ uint32_t gp_lds[];
     __shared__ int sh[65];
     __shared__ int32_t ends[2], cut[3], count;
@@ -201,21 +258,7 @@ __global__ __launch_bounds__(kLocalT) void k_gp_local(int32_t S, const int32_t *
     if (tid == 0) best = ~0ull;
     __syncthreads();
     for (int i = tid; i < len; i += nt) {
-        const int32_t v = vlist[base + i], q0 = ptr[v], q1 = ptr[v + 1];
-        range[base + i] = make_int2(q0, q1);
-        for (int32_t q = q0; q < q1; q += kNb) {
-            int32_t u[kNb], lu[kNb], pu[kNb];
-#pragma unroll
-            for (int j = 0; j < kNb; ++j) u[j] = col[min(q + j, q1 - 1)];
-#pragma unroll
-            for (int j = 0; j < kNb; ++j) {
-                lu[j] = label[u[j]];
-                pu[j] = pos[u[j]];
-            }
-#pragma unroll
-            for (int j = 0; j < kNb; ++j)
-                if (q + j < q1) ladj[q + j] = lu[j] == b ? (uint16_t)(pu[j] - base) : 0xffff;
-        }
+        const int32_t v = vlist[base + i];
         const unsigned long long key = ((unsigned long long)(uint32_t)v << 32) | (uint32_t)i;
         if (key < best) atomicMin(&best, key);
     }
@@ -403,7 +446,7 @@ int graph_partition(dd_ctx *h, const int32_t *ptr, const int32_t *col, hipStream
         for (uint32_t d = 0; e == hipSuccess && d < (uint32_t)n; d += kLevelBatch) {
             k_gp_fill<<<1, kT, 0, st>>>(kLevelBatch, changed, 0);
             for (int j = 0; j < kLevelBatch; ++j)
-                k_gp_level<<<blocks(n), kT, 0, st>>>(n, ptr, col, label, d + j, dist, changed + j);
+                k_gp_level<<<blocks((n + kPer - 1) / kPer), kT, 0, st>>>(n, ptr, col, label, d + j, dist, changed + j);
             int32_t last = 0;
             if ((e = hipGetLastError()) != hipSuccess) break;
             if ((e = hipMemcpyAsync(&last, changed + kLevelBatch - 1, sizeof(int32_t), hipMemcpyDeviceToHost,
@@ -456,8 +499,11 @@ int graph_partition(dd_ctx *h, const int32_t *ptr, const int32_t *col, hipStream
             for (int32_t b = 0; b < nparts; ++b)
                 if (kh[b] > 1) segh.push_back(b);
             GCHK(hipMemcpyAsync(seg, segh.data(), sizeof(int32_t) * segh.size(), hipMemcpyHostToDevice, st));
-            k_gp_local<<<(unsigned)segh.size(), kLocalT, local_lds(kmax * S), st>>>(S, seg, segk, ptr, col, label,
-                                                                                  vlist[0], vlist[1], pos, ladj, range);
+            const int per = (int)blocks((int64_t)kmax * S);
+            k_gp_adj<<<(unsigned)(segh.size() * per), kT, 0, st>>>(S, per, seg, segk, ptr, col, vlist[0], pos, ladj,
+                                                                   range);
+            k_gp_local<<<(unsigned)segh.size(), kLocalT, local_lds(kmax * S), st>>>(S, seg, segk, label, vlist[0],
+                                                                                  vlist[1], pos, ladj, range);
             GCHK(hipGetLastError());
             GCHK(hipStreamSynchronize(st));  // seg and segk are written again for the next depth
             std::swap(vlist[0], vlist[1]);
