@@ -943,7 +943,8 @@ __device__ __forceinline__ void apply_slots_sub(
 // subdomain run side by side on one L2 and stream its factors from memory
 // once.  The runs' lengths (T / 8, one more in the first T % 8) are the
 // numbers of workgroups each XCD gets, so every item is taken once.  A single
-// right-hand side reads every factor once whatever the order.
+// right-hand side reads every factor once whatever the order.  48^3 in 16^3
+// boxes, 16 right-hand sides: 127 -> 104 us, with the correction 139 -> 115.
 __device__ __forceinline__ uint2 batch_item() {
     const uint32_t Q = gridDim.y;
     if (Q == 1) return make_uint2(blockIdx.x, 0u);

@@ -3,16 +3,17 @@
 // are cleared by the driver before they can be handed out again, 130 ms per
 // setup in a program that builds and destroys one system after another.  A
 // destroyed handle's buffers therefore stay with the library for the next
-// handle, up to a bound (kShare of the device's memory); what exceeds it, or
-// has lain unused for kIdleSeconds when the pool is next used, goes back to
-// the driver, and everything does when an allocation fails and on
-// dd_destroy(NULL).
+// handle, up to a bound (kShare of the device's memory); what exceeds it, the
+// longest unused first, or has lain unused for kIdleSeconds when the pool is
+// next used, goes back to the driver, and everything does when an allocation
+// fails and on dd_destroy(NULL).
 //
 // A block enters the pool only after the device has been idle since its last
 // possible use (dd_ctx::reclaim and the destructor synchronise the device, as
 // hipFree does), so it may be handed to any stream and thread.  One mutex
 // guards the table; no lock is held across a driver call that can wait for
 // work.
+#include <algorithm>
 #include <chrono>
 #include <map>
 #include <mutex>
@@ -121,7 +122,13 @@ void pool_free(void *q) {
             if (now - it->second.since > std::chrono::seconds(kIdleSeconds)) take_out(P, D, it, out);
             it = next;
         }
-        while (D.held > D.bound && !D.free.empty()) take_out(P, D, std::prev(D.free.end()), out);
+        // over the bound the longest unused go: the largest first would give
+        // back what was just freed whenever the pool is full of smaller blocks
+        while (D.held > D.bound && !D.free.empty())
+            take_out(P, D,
+                     std::min_element(D.free.begin(), D.free.end(),
+                                      [](const auto &a, const auto &b) { return a.second.since < b.second.since; }),
+                     out);
     }
     give_back(out);
 }

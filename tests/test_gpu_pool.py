@@ -68,3 +68,34 @@ def test_memory_given_back():
     P.ddilu.lib().dd_destroy(None)
     assert kept > 100 << 20  # the handle's buffers were still held
     assert before - torch.cuda.mem_get_info()[0] < kept // 4
+
+
+def test_full_pool_keeps_the_newest():
+    """With the pool full of smaller buffers, a larger handle's memory stays
+    for the next one of its size: the second takes nothing from the driver."""
+    gc.collect()
+    torch.cuda.empty_cache()
+    P.ddilu.lib().dd_destroy(None)
+
+    def build(p):
+        t = lambda a, d: torch.as_tensor(np.ascontiguousarray(a)).to("cuda", d).reshape(-1)  # noqa: E731
+        args = (t(p.brow_ptr, torch.int32), t(p.bcol, torch.int32), t(p.val, torch.float64))
+        return lambda: P.ddilu.dd_partition(p.nx, p.ny, p.nz, p.bs, *args, sub=(8, 8, 8))
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    small, large = build(random_blocks(56, 56, 56, seed=73)), build(random_blocks(80, 80, 80, seed=74))
+    start, bound = free(), torch.cuda.mem_get_info()[1] // 16
+    handles = []
+    while start - free() < bound and len(handles) < 200:
+        handles.append(small())
+    for h in handles:
+        h.close()
+    large().close()
+    before = free()
+    h = large()
+    assert before - free() < 64 << 20
+    h.close()
+    P.ddilu.lib().dd_destroy(None)
