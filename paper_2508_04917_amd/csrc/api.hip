@@ -482,11 +482,13 @@ static int factor_values(dd_ctx *h, hipStream_t st) {
     return DD_OK;
 }
 
-static int ensure_fp32(dd_ctx *h, hipStream_t st) {
+// The FP32 copies of the streams the handle has, with the values as they are
+// (fresh: the streams have just been rewritten).
+static int ensure_fp32(dd_ctx *h, hipStream_t st, bool fresh = false) {
     const int bb = h->bs * h->bs;
     const bool sl = h->slots || h->seg;
     const int mb = h->seg ? h->seg : h->slots;
-    if ((!sl || h->sw[0].sval32) && (!h->csr_ready || (h->sw[1].val32 && h->sw[1].d32))) return DD_OK;
+    if (!fresh && (!sl || h->sw[0].sval32) && (!h->csr_ready || (h->sw[1].val32 && h->sw[1].d32))) return DD_OK;
     for (int w = 0; w < 2; ++w) {
         if (h->csr_ready && !h->sw[w].val32) RCHK(h->alloc(&h->sw[w].val32, h->sw[w].nblk * bb));
         if (sl && !h->sw[w].sval32) RCHK(h->alloc(&h->sw[w].sval32, h->sw[w].snpos * (mb + w) * bb));
@@ -599,7 +601,9 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     if (needs_csr(h)) RCHK(ensure_csr(h, st));
     for (int w = 0; w < 2 && h->slots && !h->direct; ++w) HCHK(launch_pack_slots(h, w, st));
     if (h->seg) HCHK(launch_seg_pack(h, st));
-    if (h->sw[0].val32 || h->sw[0].sval32) HCHK(launch_cast32(h, st));
+    // the CSR streams may be new here (a variant chosen while the handle was
+    // not factored), their FP32 copies then too
+    if (h->sw[0].val32 || h->sw[0].sval32) RCHK(ensure_fp32(h, st, true));
     HCHK(hipStreamSynchronize(st));
     h->factored = 1;
     return DD_OK;

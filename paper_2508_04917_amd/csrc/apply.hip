@@ -1695,6 +1695,7 @@ static hipError_t launch_typed(dd_ctx *h, int variant, const double *r, double *
     const Sweep &L = h->sw[0], &U = h->sw[1];
     const int lds = h->S * BS * (int)sizeof(TC);
     const bool lic = BS == 3 && h->lic.active;
+    if (!h->csr_ready) return hipErrorInvalidValue;  // built by the API before the first launch
     if (variant >= 4) {
         if constexpr (sizeof(TS) == 8 && sizeof(TC) == 8)
             return launch_ablation<BS, NT>(h, variant, r, z, state, st);
@@ -1710,6 +1711,7 @@ static hipError_t launch_typed(dd_ctx *h, int variant, const double *r, double *
     }
     const TS *lv, *uv, *dv;
     factor_ptrs<TS>(h, false, &lv, &uv, &dv);
+    if (!lv || !uv || !dv) return hipErrorInvalidValue;  // the FP32 copies likewise
     if (variant == 2) {
         auto kern = k_dd_apply_pipe<BS, TS, TC, NT, 3>;
         static bool done = false;

@@ -1,0 +1,56 @@
+"""The CSR streams of the apply variants other than the slot kernel are built
+on demand.  Whatever the order of the calls that make them needed, an apply
+equals that of a fresh handle bit for bit."""
+
+import numpy as np
+import pytest
+
+from problems import random_blocks, unstructured_problem
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - collected on CPU machines, skipped by marker
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2508_04917_amd import ddilu as dd  # noqa: E402
+from paper_2508_04917_amd.solver import DDSolver  # noqa: E402
+
+
+def cu(a, dt=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), device="cuda").to(dt).reshape(-1)
+
+
+def handle(layout):
+    if layout == "slots":
+        p = random_blocks(12, 10, 6, seed=5)
+        return p, DDSolver.from_problem(p, sub=(4, 5, 3))
+    p = unstructured_problem(3000, seed=31, bs=3)
+    return p, DDSolver.from_problem(p, graph_part_rows=300)
+
+
+@pytest.mark.parametrize("layout", ["slots", "segmented"])
+@pytest.mark.parametrize("precision", [dd.DD_MIXED, dd.DD_FP32])
+@pytest.mark.parametrize("variant", [1, 2])
+def test_variant_chosen_on_an_unfactored_handle(layout, precision, variant):
+    """FP32 factors, a refactorisation that fails, a variant that reads the
+    CSR streams, then one that succeeds: their FP32 copies exist too."""
+    p, s = handle(layout)
+    _, fresh = handle(layout)
+    assert dd.dd_get_info(s.h)["apply_layout"] == (1 if layout == "slots" else 2)
+    r = cu(np.random.default_rng(3).standard_normal(p.n * p.bs))
+    dd.ilu0_factor(s.h, precision)
+    with pytest.raises(dd.DDError) as e:
+        dd.ilu0_refactor(s.h, torch.zeros_like(cu(p.val)))
+    assert e.value.code == dd.DD_EZEROPIVOT
+    dd.dd_set_apply_variant(s.h, variant)
+    dd.ilu0_refactor(s.h, cu(p.val))
+    dd.ilu0_factor(fresh.h, precision)
+    dd.dd_set_apply_variant(fresh.h, variant)
+    assert torch.equal(s.apply(r), fresh.apply(r))
+    # and after another refactorisation, with everything built
+    dd.ilu0_refactor(s.h, cu(p.val * 0.5))
+    dd.ilu0_refactor(fresh.h, cu(p.val * 0.5))
+    assert torch.equal(s.apply(r), fresh.apply(r))
+    s.close()
+    fresh.close()
