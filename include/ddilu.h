@@ -343,7 +343,14 @@ int bicgstab_solve_noalloc(dd_handle h, const double *b, double *x, double rtol,
  * They run with DD_FP64 and without the learned correction only: the apply
  * and the solve return DD_EINVAL otherwise (also for 8 when the vector and
  * one flag byte per row exceed 160 KB of LDS).  Returns DD_EINVAL for
- * values outside 0..8. */
+ * values outside 0..8.
+ *
+ * The factors in the form that variants 1, 2 and 4-8 read are made when one
+ * is first chosen: on a factored handle by this call, which then allocates,
+ * waits for its own work (on a stream of its own, also while a stream is
+ * captured) and can return DD_ENOMEM, the variant unchanged; on any other
+ * handle by the next ilu0_factor or ilu0_refactor.  Later factorisations
+ * keep that form up to date. */
 int dd_set_apply_variant(dd_handle h, int32_t variant);
 
 /* Switch per-apply timing inside bicgstab_solve on (1) or off (0): a HIP

@@ -400,25 +400,30 @@ static int ensure_csr(dd_ctx *h, hipStream_t st) {
     if (h->csr_ready) return DD_OK;
     const int bb = h->bs * h->bs;
     int32_t *cnt = nullptr;
-    RCHK(h->alloc(&cnt, h->n));
-    HCHK(launch_lu_blocks(h, st));
-    for (int w = 0; w < 2; ++w) {
-        Sweep &s = h->sw[w];
-        if (!s.prow) {
-            RCHK(h->alloc(&s.prow, h->n));
-            RCHK(h->alloc(&s.bptr, h->n + 1));
+    auto build = [&]() -> int {
+        RCHK(h->alloc(&cnt, h->n));
+        HCHK(launch_lu_blocks(h, st));
+        for (int w = 0; w < 2; ++w) {
+            Sweep &s = h->sw[w];
+            if (!s.prow) RCHK(h->alloc(&s.prow, h->n));
+            if (!s.bptr) RCHK(h->alloc(&s.bptr, h->n + 1));
+            HCHK(launch_pack_count(h, w, cnt, st));
+            HCHK(exclusive_scan(cnt, s.bptr, h->n, h->scan_tmp, st));
+            RCHK(h->alloc(&s.bcol, s.nblk));
+            RCHK(h->alloc(&s.val64, s.nblk * bb));
+            if (w == 1 && !s.d64) RCHK(h->alloc(&s.d64, h->n * bb));
+            HCHK(launch_pack_fill(h, w, st));
         }
-        HCHK(launch_pack_count(h, w, cnt, st));
-        HCHK(exclusive_scan(cnt, s.bptr, h->n, h->scan_tmp, st));
-        RCHK(h->alloc(&s.bcol, s.nblk));
-        RCHK(h->alloc(&s.val64, s.nblk * bb));
-        if (w == 1 && !s.d64) RCHK(h->alloc(&s.d64, h->n * bb));
-        HCHK(launch_pack_fill(h, w, st));
-    }
-    HCHK(hipStreamSynchronize(st));
-    release(h, cnt);
-    h->csr_ready = 1;
-    return DD_OK;
+        HCHK(hipStreamSynchronize(st));
+        return DD_OK;
+    };
+    const int rc = build();
+    h->release(cnt);
+    if (rc)
+        drop_csr(h);
+    else
+        h->csr_ready = 1;
+    return rc;
 }
 
 // The segmented layout, where the slot layout does not hold the rows.
@@ -750,17 +755,32 @@ extern "C" int dd_set_lic_fallback(dd_handle h, int32_t on) {
     return DD_OK;
 }
 
+// The CSR streams (and their FP32 copies) of a factored handle, complete on
+// return.  Built on a stream of their own, in relaxed capture mode: the call
+// that needs them may come between two launches of a capture, on this thread
+// or another one, and is no part of it.
+static int build_csr_now(dd_ctx *h) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HCHK(hipThreadExchangeStreamCaptureMode(&mode));
+    hipStream_t st = nullptr;
+    int rc = DD_OK;
+    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) rc = h->fail(DD_EHIP, "CSR streams: no stream");
+    // the factors are complete: every factorisation ends synchronised
+    if (!rc) rc = ensure_csr(h, st);
+    if (!rc && h->sw[0].sval32) rc = ensure_fp32(h, st);
+    if (!rc && hipStreamSynchronize(st) != hipSuccess) rc = h->fail(DD_EHIP, "CSR streams: synchronise");
+    if (st) (void)hipStreamDestroy(st);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return rc;
+}
+
 extern "C" int dd_set_apply_variant(dd_handle h, int32_t variant) {
     if (!h) return set_global_error(DD_EINVAL, "dd_set_apply_variant: null handle");
     if (variant < 0 || variant > 8) return h->fail(DD_EINVAL, "dd_set_apply_variant: variant must be 0..8");
     const int32_t before = h->variant;
     h->variant = variant;
     if (h->factored && needs_csr(h) && !h->csr_ready) {
-        // the factors are complete (every factorisation ends synchronised),
-        // and so are these streams before any stream can run the variant
-        int rc = ensure_csr(h, nullptr);
-        if (!rc && h->sw[0].sval32) rc = ensure_fp32(h, nullptr);
-        if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = h->fail(DD_EHIP, "dd_set_apply_variant: synchronise");
+        const int rc = build_csr_now(h);
         if (rc) {
             h->variant = before;
             return rc;

@@ -54,3 +54,34 @@ def test_variant_chosen_on_an_unfactored_handle(layout, precision, variant):
     assert torch.equal(s.apply(r), fresh.apply(r))
     s.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("precision", [dd.DD_FP64, dd.DD_MIXED])
+def test_variant_chosen_inside_a_capture(precision):
+    """Choosing a variant is no stream operation: a graph captured around it
+    holds the applies with the old and the new variant."""
+    p, s = handle("slots")
+    dd.dd_set_precision(s.h, precision)
+    r = cu(np.random.default_rng(4).standard_normal(p.n * p.bs))
+    _, ref = handle("slots")
+    dd.dd_set_precision(ref.h, precision)
+    z0 = ref.apply(r).clone()
+    dd.dd_set_apply_variant(ref.h, 1)
+    z1 = ref.apply(r)
+    a, b = torch.empty_like(r), torch.empty_like(r)
+    s.apply(r, a)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        dd.dd_trsv_apply(s.h, r, a, stream=torch.cuda.current_stream())
+        dd.dd_set_apply_variant(s.h, 1)
+        dd.dd_trsv_apply(s.h, r, b, stream=torch.cuda.current_stream())
+    for _ in range(3):
+        a.zero_()
+        b.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a, z0) and torch.equal(b, z1)
+    s.close()
+    ref.close()
