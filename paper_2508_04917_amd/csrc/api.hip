@@ -33,8 +33,6 @@ int dd_ctx::fail(int code, const char *fmt, ...) {
     return code;
 }
 
-static void release(dd_ctx *h, void *q) { h->release(q); }
-
 #define HCHK(x)                                                                             \
     do {                                                                                    \
         hipError_t e_ = (x);                                                                \
@@ -283,7 +281,7 @@ static int build_handle(dd_ctx *h, const int32_t *brow_ptr, const int32_t *bcol,
     // later SpMVs may run on other streams: the copy is complete before any
     // of them is enqueued
     PCHK(hipStreamSynchronize(st));
-    release(h, len);
+    h->release(len);
     h->reclaim();
     h->asrc = src;  // kept for ilu0_refactor
     *out = h;
@@ -368,8 +366,7 @@ static int build_levels(dd_ctx *h, hipStream_t st, int32_t *stats, int32_t *tmp_
     HCHK(hipStreamSynchronize(st));
     for (int w = 0; w < 2; ++w) {
         Levels &L = h->lev[w];
-        if (L.ptr) release(h, L.ptr);
-        L.ptr = nullptr;
+        h->release(L.ptr);
         RCHK(h->alloc(&L.ptr, total[w]));
         L.ptr_len = total[w];
         L.max_levels = got[2 + w];
@@ -383,8 +380,11 @@ static int build_levels(dd_ctx *h, hipStream_t st, int32_t *stats, int32_t *tmp_
 static void drop_csr(dd_ctx *h) {
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
-        for (void *q : {(void *)s.bcol, (void *)s.val64, (void *)s.val32, (void *)s.uraw}) release(h, q);
-        s.bcol = nullptr; s.val64 = nullptr; s.val32 = nullptr; s.uraw = nullptr;
+        h->release(s.bcol);
+        h->release(s.val64);
+        h->release(s.val32);
+        h->release(s.uraw);
+        s.uraw_ready = 0;
     }
     h->csr_ready = 0;
 }
@@ -467,8 +467,9 @@ static int build_slots(dd_ctx *h, int32_t *stats, hipStream_t st) {
 static void drop_slots(dd_ctx *h) {
     for (int w = 0; w < 2; ++w) {
         Sweep &s = h->sw[w];
-        for (void *q : {(void *)s.desc, (void *)s.sval64, (void *)s.sval32}) release(h, q);
-        s.desc = nullptr; s.sval64 = nullptr; s.sval32 = nullptr;
+        h->release(s.desc);
+        h->release(s.sval64);
+        h->release(s.sval32);
         s.snpos = 0;
     }
     h->slots = h->seg = h->direct = 0;
@@ -509,6 +510,7 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
         return h->fail(DD_EINVAL, "ilu0_factor: bad precision");
     hipStream_t st = as_stream(hip_stream);
     const int bb = h->bs * h->bs;
+    ReclaimAtExit at_exit{h};
     h->factored = 0;
     h->patterned = 0;
     h->lic.adj_ready = 0;  // the adjoint apply's streams hold the old factors
@@ -526,23 +528,27 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
     if (status[1] != 0x7fffffff) {
-        release(h, tbeg); release(h, tlen);
+        h->release(tbeg);
+        h->release(tlen);
         return h->fail(DD_EZEROPIVOT, "block row %d has no diagonal block", status[1]);
     }
     h->nnzt = total;
     h->nlow = h->nupp = (total - h->n) / 2;  // refined below
-    if (h->tcol) { release(h, h->tcol); release(h, h->lu); }
+    // what an earlier factorisation left goes back before its successor is
+    // allocated, so that a handle never holds both
+    h->release(h->tcol);
+    h->release(h->lu);
+    h->release(h->tsrc);
+    drop_csr(h);
+    drop_slots(h);
+    h->reclaim();
     RCHK(h->alloc(&h->tcol, total));
     RCHK(h->alloc(&h->lu, (int64_t)total * bb));
     if (!h->tdiag) RCHK(h->alloc(&h->tdiag, h->n));
     if (!h->invd) RCHK(h->alloc(&h->invd, h->n * bb));
-    if (h->tsrc) release(h, h->tsrc);
-    h->tsrc = nullptr;
     RCHK(h->alloc(&tsrc, total));
     HCHK(launch_drop_rows(h, tbeg, tsrc, st));
     h->tsrc = tsrc;  // kept for ilu0_refactor
-    drop_csr(h);
-    drop_slots(h);
     // level sets (Section 4.2.1) for both factors
     RCHK(build_levels(h, st, h->status + 8, tlen));
     h->nlow = h->sw[0].nblk;
@@ -552,8 +558,8 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     if (h->slots) RCHK(build_slots(h, h->status + 16, st));
     HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
-    release(h, tbeg);
-    release(h, tlen);
+    h->release(tbeg);
+    h->release(tlen);
     h->max_level_width = status[8 + 4];
     h->direct = h->slots && !status[16];
     h->reach = status[16 + 1];
@@ -571,7 +577,6 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     h->precision = precision;
     if (precision != DD_FP64) RCHK(ensure_fp32(h, st));
     HCHK(hipStreamSynchronize(st));
-    h->reclaim();
     h->factored = 1;
     h->patterned = 1;
     return DD_OK;
@@ -588,7 +593,7 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     h->lic.active = 0;
     h->lic.ready = 0;
     h->gfactored = 0;
-    if (h->sw[1].uraw) { release(h, h->sw[1].uraw); h->sw[1].uraw = nullptr; }
+    h->sw[1].uraw_ready = 0;
     // values of the reordered matrix, its sliced ELL copy and the dropped pattern
     HCHK(launch_values(h, val, h->asrc, st));
     // block ILU0 on the kept level sets
@@ -657,10 +662,11 @@ extern "C" int dd_get_factors(dd_handle h, int32_t *ptr, int32_t *col, double *f
 static int prepare_variant(dd_ctx *h, const char *who, hipStream_t st) {
     if (const char *why = variant_unsupported(h, h->variant)) return h->fail(DD_EINVAL, "%s: %s", who, why);
     Sweep &U = h->sw[1];
-    if (h->variant == 7 && !U.uraw) {
-        RCHK(h->alloc(&U.uraw, U.nblk * h->bs * h->bs));
+    if (h->variant == 7 && !U.uraw_ready) {
+        if (!U.uraw) RCHK(h->alloc(&U.uraw, U.nblk * h->bs * h->bs));
         HCHK(launch_lu_blocks(h, st));
         HCHK(launch_pack_unscaled(h, st));
+        U.uraw_ready = 1;
     }
     return DD_OK;
 }
@@ -738,7 +744,7 @@ extern "C" int bicgstab_solve_noalloc(dd_handle h, const double *b, double *x, d
     if (h->pc_kind == 0) {
         if (const char *why = variant_unsupported(h, h->variant))
             return h->fail(DD_EINVAL, "bicgstab_solve_noalloc: %s", why);
-        if (h->variant == 7 && !h->sw[1].uraw)
+        if (h->variant == 7 && !h->sw[1].uraw_ready)
             return h->fail(DD_ESTATE,
                            "bicgstab_solve_noalloc: apply variant 7 needs its unscaled factors, which the first "
                            "dd_trsv_apply or bicgstab_solve with that variant allocates");

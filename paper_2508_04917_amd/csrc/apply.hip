@@ -1668,7 +1668,7 @@ static hipError_t launch_ablation(dd_ctx *h, int variant, const double *r, doubl
             auto k = k_abl_ilu0<BS, NT>;
             static bool d = false;
             if ((e = allow_full_lds(k, d)) != hipSuccess) return e;
-            if (!U.uraw) return hipErrorInvalidValue;  // built by the API before the first launch
+            if (!U.uraw_ready) return hipErrorInvalidValue;  // built by the API before the first launch
             k<<<g, NT, lds, st>>>(r, z, h->S, LL.off, LL.ptr, L.prow, L.bptr, L.bcol, L.val64, UL.off, UL.ptr,
                                   U.prow, U.bptr, U.bcol, U.uraw, U.d64, state);
             break;

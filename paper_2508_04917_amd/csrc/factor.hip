@@ -1037,8 +1037,10 @@ int build_seg_layout(dd_ctx *h, hipStream_t st) {
     if (e != hipSuccess) return h->fail(DD_EHIP, "segmented layout: %s", hipGetErrorString(e));
     for (int w = 0; w < 2 && !rc; ++w) {
         Sweep &s = h->sw[w];
-        for (void *q : {(void *)s.pmap, (void *)s.wtab, (void *)s.winfo, (void *)npos[w]}) h->release(q);
-        s.pmap = nullptr; s.wtab = nullptr; s.winfo = nullptr;
+        h->release(s.pmap);
+        h->release(s.wtab);
+        h->release(s.winfo);
+        h->release(npos[w]);
         s.snpos = tot[w];
         rc = h->alloc(&s.pmap, tot[w]);
         if (!rc) rc = h->alloc(&s.wtab, tot[w] / (rpw - kSegMax + 1) + nsub + h->lev[w].ptr_len + 1);

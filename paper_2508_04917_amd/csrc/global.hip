@@ -436,7 +436,9 @@ static int global_levels(dd_ctx *h, hipStream_t st) {
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) rc = h->fail(DD_EHIP, "global levels: %s", hipGetErrorString(e));
     }
-    for (void *q : {(void *)cnt, (void *)cur, (void *)tmp}) h->release(q);
+    h->release(cnt);
+    h->release(cur);
+    h->release(tmp);
     return rc;
 }
 
@@ -480,8 +482,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
     int32_t *linv = nullptr;
     rc = h->alloc(&linv, h->n);
     for (int w = 0; w < 2 && !rc; ++w) {
-        if (h->ghrow[w]) h->release(h->ghrow[w]);
-        h->ghrow[w] = nullptr;
+        h->release(h->ghrow[w]);
         rc = h->alloc(&h->ghrow[w], hp[w].back());
         if (!rc && !h->gdesc[w]) rc = h->alloc(&h->gdesc[w], h->n);
         if (!rc && !h->gsval[w]) rc = h->alloc(&h->gsval[w], h->n * (kMaxSlots + w) * bb);
@@ -535,6 +536,7 @@ static int global_slots(dd_ctx *h, hipStream_t st) {
 int global_factor(dd_ctx *h, hipStream_t st) {
     const int bb = h->bs * h->bs, T = 256;
     const unsigned g = (unsigned)((h->n + T - 1) / T);
+    ReclaimAtExit at_exit{h};
     int32_t init_status[8] = {0, 0x7fffffff, 0x7fffffff, 0, 0, 0, 0, 0}, status[8];
     GCHK(hipMemcpyAsync(h->status, init_status, sizeof(init_status), hipMemcpyHostToDevice, st));
     // the pattern's part, once per handle (again when the decomposed sweeps,
@@ -579,7 +581,6 @@ int global_factor(dd_ctx *h, hipStream_t st) {
     GCHK(hipStreamSynchronize(st));
     if (status[2] != 0x7fffffff)
         return h->fail(DD_EZEROPIVOT, "global ILU0: singular pivot at reordered block row %d", status[2]);
-    h->reclaim();
     h->gfactored = 1;
     return DD_OK;
 }

@@ -29,6 +29,7 @@ struct Sweep {
     float *val32 = nullptr;     // FP32 copy (built on demand)
     double *d64 = nullptr;      // upper only: inv_D per position [n*bb]
     double *uraw = nullptr;     // upper only, built on demand: U blocks without the inv_D scaling [nblk*bb]
+    int32_t uraw_ready = 0;     // uraw holds the present factors'
     float *d32 = nullptr;
     int64_t nblk = 0;
     int32_t max_row = 0;        // most blocks of any row in this sweep
@@ -217,12 +218,24 @@ struct dd_ctx {
         if (!rc) *p = static_cast<T *>(q);
         return rc;
     }
-    void release(void *q);  // to the pool at the next reclaim()
-    void reclaim();         // waits for the device when something was released
+    // to the pool at the next reclaim(); the pointer is cleared
+    template <typename T>
+    void release(T *&p) {
+        retire(p);
+        p = nullptr;
+    }
+    void retire(void *q);
+    void reclaim();  // waits for the device when something was released
     ~dd_ctx();
 };
 
 namespace ddilu {
+
+// Every way out of a call that releases buffers gives them back.
+struct ReclaimAtExit {
+    dd_ctx *h;
+    ~ReclaimAtExit() { h->reclaim(); }
+};
 
 // device memory kept between handles (pool.hip)
 hipError_t pool_alloc(void **out, size_t bytes);

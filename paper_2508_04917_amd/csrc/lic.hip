@@ -588,6 +588,7 @@ int lic_setup(dd_ctx *h, hipStream_t st) {
     const unsigned g = (unsigned)((h->n + T - 1) / T);
     Lic &L = h->lic;
     hipError_t e;
+    ReclaimAtExit at_exit{h};
     const int32_t st67[2] = {0, 0};
     e = hipMemcpyAsync(h->status + 6, st67, 2 * sizeof(int32_t), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return h->fail(DD_EHIP, "memcpy: %s", hipGetErrorString(e));
@@ -613,11 +614,15 @@ int lic_setup(dd_ctx *h, hipStream_t st) {
     const int maxrank = sym[1];
     if (maxrank > 8) return h->fail(DD_EINVAL, "the learned correction supports at most 8 cut faces per row");
     L.nf = nf;
-    for (void *q : {(void *)L.fI, (void *)L.fJ, (void *)L.fq, (void *)L.X, (void *)L.C, (void *)L.lrec,
-                    (void *)L.lperm, (void *)L.Cr})
-        if (q) {
-            h->release(q);
-        }
+    L.ready = L.active = 0;  // until the faces' arrays are there again
+    h->release(L.fI);
+    h->release(L.fJ);
+    h->release(L.fq);
+    h->release(L.X);
+    h->release(L.C);
+    h->release(L.lrec);
+    h->release(L.lperm);
+    h->release(L.Cr);
     rc = h->alloc(&L.fI, nf);
     if (!rc) rc = h->alloc(&L.fJ, nf);
     if (!rc) rc = h->alloc(&L.fq, nf);
@@ -651,8 +656,9 @@ int lic_setup(dd_ctx *h, hipStream_t st) {
     // the adjoint apply's streams are packed on first use (training only)
     L.adj_ready = 0;
     e = hipStreamSynchronize(st);
-    for (void *q : {(void *)cnt, (void *)flag, (void *)bpos}) h->release(q);
-    h->reclaim();
+    h->release(cnt);
+    h->release(flag);
+    h->release(bpos);
     if (e != hipSuccess) return h->fail(DD_EHIP, "lic setup: %s", hipGetErrorString(e));
     L.ready = 1;
     L.active = 0;
@@ -716,8 +722,11 @@ int lic_loss_grad_run(dd_ctx *h, const float *params, int Q, const double *R, co
     int rc = lic_coeffs_from_params(h, params, true, st);
     if (rc) return rc;
     if (L.work_q < Q) {
-        for (void *q : {(void *)L.Z, (void *)L.G, (void *)L.A, (void *)L.rpart})
-            h->release(q);
+        L.work_q = 0;
+        h->release(L.Z);
+        h->release(L.G);
+        h->release(L.A);
+        h->release(L.rpart);
         h->reclaim();
         rc = h->alloc(&L.Z, Q * m);
         if (!rc) rc = h->alloc(&L.G, Q * m);

@@ -148,7 +148,7 @@ void pool_trim(int device) {
 
 }  // namespace ddilu
 
-void dd_ctx::release(void *q) {
+void dd_ctx::retire(void *q) {
     if (!q) return;
     auto it = std::find(allocs.begin(), allocs.end(), q);
     if (it == allocs.end()) return;

@@ -535,9 +535,8 @@ int build_wave_chunks(dd_ctx *h, int which, hipStream_t st) {
     Sweep &w = h->sw[which];
     const Levels &L = h->lev[which];
     const int rpw = kWave / h->bs;
-    for (void *q : {(void *)w.wtab, (void *)w.winfo}) h->release(q);
-    w.wtab = nullptr;
-    w.winfo = nullptr;
+    h->release(w.wtab);
+    h->release(w.winfo);
     int rc = h->alloc(&w.wtab, w.snpos / rpw + h->nsub + L.ptr_len + 1);
     if (!rc) rc = h->alloc(&w.winfo, h->nsub);
     if (rc) return rc;
