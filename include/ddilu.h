@@ -492,8 +492,11 @@ int lic_train(dd_handle *hs, int32_t nprob, const double *const *R,
 const char *dd_last_error(dd_handle h);
 
 /* Destroys the handle.  Its device buffers stay with the library for later
- * handles, at most a sixteenth of the device's memory in all; dd_destroy(NULL)
- * returns all such memory to the driver. */
+ * handles, at most a sixteenth of the device's memory in all.  Buffers unused
+ * for 60 s go back to the driver at the library's next call that allocates or
+ * frees device memory, all of them when such an allocation fails;
+ * dd_destroy(NULL) returns them at once (a program that calls the library no
+ * more and wants the memory for others calls it). */
 void dd_destroy(dd_handle h);
 
 #ifdef __cplusplus

@@ -3,10 +3,12 @@
 // are cleared by the driver before they can be handed out again, 130 ms per
 // setup in a program that builds and destroys one system after another.  A
 // destroyed handle's buffers therefore stay with the library for the next
-// handle, up to a bound (kShare of the device's memory); what exceeds it, the
-// longest unused first, or has lain unused for kIdleSeconds when the pool is
-// next used, goes back to the driver, and everything does when an allocation
-// fails and on dd_destroy(NULL).
+// handle, up to a bound (kShare of the device's memory).  What goes back to the
+// driver: over the bound the longest unused; what has lain unused for
+// kIdleSeconds, whenever the library allocates or frees device memory (there
+// is no thread that looks while it is not called); everything when an
+// allocation of the library's fails and on dd_destroy(NULL), which a program
+// calls that wants the memory for others.
 //
 // A block enters the pool only after the device has been idle since its last
 // possible use (dd_ctx::reclaim and the destructor synchronise the device, as
@@ -62,6 +64,15 @@ void take_out(Pool &P, Device &D, std::multimap<size_t, Block>::iterator it, std
     D.free.erase(it);
 }
 
+void take_expired(Pool &P, Device &D, std::vector<void *> &out) {
+    const Clock::time_point now = Clock::now();
+    for (auto it = D.free.begin(); it != D.free.end();) {
+        const auto next = std::next(it);
+        if (now - it->second.since > std::chrono::seconds(kIdleSeconds)) take_out(P, D, it, out);
+        it = next;
+    }
+}
+
 void give_back(const std::vector<void *> &v) {
     for (void *q : v) (void)hipFree(q);
 }
@@ -73,17 +84,24 @@ hipError_t pool_alloc(void **out, size_t bytes) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const size_t need = rounded(bytes);
+    std::vector<void *> old;
+    void *found = nullptr;
     Pool &P = pool();
     {
         std::lock_guard<std::mutex> lock(P.mu);
         Device &D = P.dev[dev];
         auto it = D.free.lower_bound(need);
         if (it != D.free.end() && it->first - need <= need / 4) {  // a quarter more than asked at most
-            *out = it->second.p;
+            found = it->second.p;
             D.held -= it->first;
             D.free.erase(it);
-            return hipSuccess;
         }
+        take_expired(P, D, old);
+    }
+    give_back(old);
+    if (found) {
+        *out = found;
+        return hipSuccess;
     }
     e = hipMalloc(out, need);
     if (e != hipSuccess) {
@@ -114,14 +132,9 @@ void pool_free(void *q) {
             if (hipMemGetInfo(&avail, &total) != hipSuccess) total = 0;
             D.bound = std::max<size_t>(total / kShare, 1);
         }
-        const Clock::time_point now = Clock::now();
-        D.free.insert({s->second.first, Block{q, now}});
+        D.free.insert({s->second.first, Block{q, Clock::now()}});
         D.held += s->second.first;
-        for (auto it = D.free.begin(); it != D.free.end();) {
-            const auto next = std::next(it);
-            if (now - it->second.since > std::chrono::seconds(kIdleSeconds)) take_out(P, D, it, out);
-            it = next;
-        }
+        take_expired(P, D, out);
         // over the bound the longest unused go: the largest first would give
         // back what was just freed whenever the pool is full of smaller blocks
         while (D.held > D.bound && !D.free.empty())

@@ -364,8 +364,13 @@ def dd_set_residual_history(h: Handle, hist):
         _check(lib().dd_set_residual_history(h.ptr, _ptr(hist), hist.numel()), h)
 
 
-def dd_destroy(h: Handle):
-    h.close()
+def dd_destroy(h: Handle | None):
+    """Destroy a handle; None: device memory that the library keeps from
+    destroyed handles goes back to the driver."""
+    if h is None:
+        lib().dd_destroy(None)
+    else:
+        h.close()
 
 
 # ------------------------------------------------------------- global ILU0
