@@ -742,7 +742,14 @@ __device__ __forceinline__ void slot_claim(SlotRegs<BS, TS, MB, UPPER> &R) {
 // of the same wavefront, in segment order through cross-lane reads, and
 // alone writes the row.  All lanes take part in the reads (those without a
 // position hold zero), so every value read is defined.
-template <int BS, typename TS, typename TC, int MB, bool UPPER, bool SEG = false>
+//
+// EXACT: an empty slot leaves the sum alone whatever y_I holds; otherwise
+// its zero block makes NaN of an infinite value in y_I.  For the sweeps that
+// take the place of kernels without that padding (the global ILU0, levels
+// wider than a pass).  Not for all: behind the level chain's write the test
+// still costs 1.6% where the chain is the bound (105x132x78, FP32 factors,
+// learned correction 119.4 -> 121.4 us; 64^3 and 160^3 FP64 no difference).
+template <int BS, typename TS, typename TC, int MB, bool UPPER, bool SEG = false, bool EXACT = false>
 __device__ __forceinline__ void slot_compute(TC *__restrict__ y, const SlotRegs<BS, TS, MB, UPPER> &R, int c) {
     using SR = SlotRegs<BS, TS, MB, UPPER>;
     using RR = RawRun<SR::NB>;
@@ -786,16 +793,20 @@ __device__ __forceinline__ void slot_compute(TC *__restrict__ y, const SlotRegs<
     }
     __builtin_amdgcn_sched_barrier(0);
     const bool cont = SEG && (((desc >> 15) & 1u) != 0 || !R.ok);
-    TC acc;
-    if constexpr (UPPER) {
-        acc = 0;
+    auto own = [&]() -> TC {  // the sum without the slots
+        TC a;
+        if constexpr (UPPER) {
+            a = 0;
 #pragma unroll
-        for (int d = 0; d < BS; ++d) acc += static_cast<TC>(vals[MB * BS + d]) * yi[d];
-        if constexpr (SEG)
-            if (cont) acc = -acc;
-    } else {
-        acc = cont ? TC(0) : yi[0];
-    }
+            for (int d = 0; d < BS; ++d) a += static_cast<TC>(vals[MB * BS + d]) * yi[d];
+            if constexpr (SEG)
+                if (cont) a = -a;
+        } else {
+            a = cont ? TC(0) : yi[0];
+        }
+        return a;
+    };
+    TC acc = own();
 #pragma unroll
     for (int k = 0; k < MB; ++k)
 #pragma unroll
@@ -817,6 +828,17 @@ __device__ __forceinline__ void slot_compute(TC *__restrict__ y, const SlotRegs<
         // all lanes of this row read y_I above (same wavefront)
         __asm__ volatile("" ::: "memory");
         y[I * BS + c] = acc;
+        if constexpr (EXACT) {
+            if (__builtin_expect(acc != acc, 0)) {  // NaN: summed again without the empty slots
+                acc = own();
+#pragma unroll
+                for (int k = 0; k < MB; ++k)
+                    if ((int)((desc >> (16 * (k + 1))) & FM) != (int)FM)
+#pragma unroll
+                        for (int d = 0; d < BS; ++d) acc -= static_cast<TC>(vals[k * BS + d]) * yj[k][d];
+                y[I * BS + c] = acc;
+            }
+        }
     }
 }
 
@@ -832,7 +854,7 @@ __device__ __forceinline__ int2 wave_entries(const int2 *__restrict__ tab, int n
 // chunk k: in between it only joins the barriers.  ent: the wavefront's
 // first 64 table entries, one per lane (wave_entries); a step reads its own
 // by a lane read, so no memory access stands in the level chain.
-template <int BS, typename TS, typename TC, int MB, int PD, bool UPPER, bool SEG = false>
+template <int BS, typename TS, typename TC, int MB, int PD, bool UPPER, bool SEG = false, bool EXACT = false>
 __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, int64_t pcount,
                                             const int2 *__restrict__ tab, int n, int nlev, int2 ent,
                                             const uint64_t *__restrict__ desc, const TS *__restrict__ sval, int wave,
@@ -885,7 +907,7 @@ __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, i
             for (; cur < l; ++cur) __syncthreads();
             vm_wait<PD * SR::NLOAD>();  // set u is the oldest of the PD + 1 in flight
             slot_claim(R[u]);
-            slot_compute<BS, TS, TC, MB, UPPER, SEG>(y, R[u], c);
+            slot_compute<BS, TS, TC, MB, UPPER, SEG, EXACT>(y, R[u], c);
         }
     }
     // nothing may still be loading into these registers once they are free
@@ -905,7 +927,7 @@ struct SlotTabs {
 // One subdomain's apply with the slot layout: r's slice into LDS (plus the
 // learned correction), the lower sweep, the upper sweep with the diagonal
 // scaling, and the slice back to z.
-template <int BS, typename TS, typename TC, int MB, int PD, bool LIC, bool SEG = false>
+template <int BS, typename TS, typename TC, int MB, int PD, bool LIC, bool SEG = false, bool EXACT = false>
 __device__ __forceinline__ void apply_slots_sub(
     TC *__restrict__ y, int s, const double *__restrict__ r, double *__restrict__ z, int S, const SlotTabs &tabs,
     const uint64_t *__restrict__ Ldesc, const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc,
@@ -928,10 +950,10 @@ __device__ __forceinline__ void apply_slots_sub(
     if constexpr (LIC) lic_finish<BS, TC>(y, r, lst, lpass, la, tid, nt);
     const int64_t lb = SEG ? (int64_t)Lgpos[s] : base, ub = SEG ? (int64_t)Ugpos[s] : base;
     const int64_t lc = SEG ? Lgpos[s + 1] - lb : S, uc = SEG ? Ugpos[s + 1] - ub : S;
-    sweep_slots<BS, TS, TC, MB, PD, false, SEG>(y, lb, lc, tabs.ltab + li.x, li.y, li.z, le, Ldesc, Lval, wave, nw,
-                                                lane);
-    sweep_slots<BS, TS, TC, MB, PD, true, SEG>(y, ub, uc, tabs.utab + ui.x, ui.y, ui.z, ue, Udesc, Uval, wave, nw,
-                                               lane);
+    sweep_slots<BS, TS, TC, MB, PD, false, SEG, EXACT>(y, lb, lc, tabs.ltab + li.x, li.y, li.z, le, Ldesc, Lval,
+                                                       wave, nw, lane);
+    sweep_slots<BS, TS, TC, MB, PD, true, SEG, EXACT>(y, ub, uc, tabs.utab + ui.x, ui.y, ui.z, ue, Udesc, Uval, wave,
+                                                      nw, lane);
     double *zs = z + base * BS;
     store_slice<TC, !LIC>(zs, y, S * BS, tid, nt);
 }
@@ -967,6 +989,20 @@ __global__ __launch_bounds__(NT) void k_dd_apply_slots(
                                                   tabs, Ldesc, Lval, Udesc, Uval, la, stopped, Lgpos, Ugpos);
 }
 
+// The same where levels are wider than a pass of 1,024 lanes (launch_slots).
+template <int BS, typename TS, typename TC, int NT, int MB, int PD, bool LIC>
+__global__ __launch_bounds__(NT) void k_dd_apply_slots_wide(
+    const double *__restrict__ r, double *__restrict__ z, int S, SlotTabs tabs, const uint64_t *__restrict__ Ldesc,
+    const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc, const TS *__restrict__ Uval,
+    const int32_t *__restrict__ state, LicArgs la, int64_t vstride) {
+    const int stopped = state != nullptr ? *state : 0;
+    extern __shared__ unsigned char dd_smem[];
+    const uint2 item = batch_item();
+    const int64_t off = (int64_t)item.y * vstride;
+    apply_slots_sub<BS, TS, TC, MB, PD, LIC, false, true>(reinterpret_cast<TC *>(dd_smem), (int)item.x, r + off,
+                                                          z + off, S, tabs, Ldesc, Lval, Udesc, Uval, la, stopped);
+}
+
 // ------------------------------------------------------------------------
 // One sweep of the global (undecomposed) ILU0 over the subdomains of one level
 // of the subdomain graph and one right-hand side: the subdomain's slice
@@ -996,8 +1032,8 @@ __global__ __launch_bounds__(512) void k_dd_apply_slots_global(
     for (int i = tid; i < hn; i += nt) y[S * BS + i] = z[rhs + (int64_t)hrow[h0 + i / BS] * BS + i % BS];
     load_slice<double, true>(y, src + rhs + base * BS, S * BS, tid, nt);
     __syncthreads();
-    sweep_slots<BS, double, double, kMaxSlots, DDILU_PD64, UPPER>(y, base, S, wtab + wi.x, wi.y, wi.z, we, desc, sval,
-                                                                  wave, nw, lane);
+    sweep_slots<BS, double, double, kMaxSlots, DDILU_PD64, UPPER, false, true>(y, base, S, wtab + wi.x, wi.y, wi.z,
+                                                                               we, desc, sval, wave, nw, lane);
     store_slice<double, true>(z + rhs + base * BS, y, S * BS, tid, nt);
 }
 
@@ -1461,15 +1497,35 @@ static SlotTabs slot_tabs(const dd_ctx *h) {
     return SlotTabs{h->sw[0].wtab, h->sw[1].wtab, h->sw[0].winfo, h->sw[1].winfo};
 }
 
+constexpr int kSlotLanes = 512;  // most lanes of the plain slot kernels (slot_threads)
+
+// Rows of a pass of 1,024 lanes: what a level may hold at most where the
+// apply and the product run as one launch and in the adjoint apply.
+static int one_pass_rows(const dd_ctx *h) { return (kWave / h->bs) * (1024 / kWave); }
+
+// Levels wider than that ran in the plain loop before the levels were cut
+// into chunks: they take the kernel whose empty slots are exact.
 template <int BS, typename TS, typename TC, int NT, int MB, bool LIC>
 static hipError_t launch_slots(dd_ctx *h, const double *r, double *z, const int32_t *state, hipStream_t st,
                                const TS *lv, const TS *uv, int nrhs) {
     constexpr int PD = sizeof(TS) == 8 ? DDILU_PD64 : DDILU_PD32;
+    const int lds = h->S * BS * (int)sizeof(TC);
+    if constexpr (NT == kSlotLanes) {
+        if (h->max_level_width > one_pass_rows(h)) {
+            auto wide = k_dd_apply_slots_wide<BS, TS, TC, NT, MB, PD, LIC>;
+            static bool done = false;
+            hipError_t e = allow_full_lds(wide, done);
+            if (e != hipSuccess) return e;
+            launch_timed(h, wide, dim3(h->nsub, nrhs), NT, lds, st, r, z, h->S, slot_tabs(h),
+                         (const uint64_t *)h->sw[0].desc, lv, (const uint64_t *)h->sw[1].desc, uv, state, lic_args(h),
+                         (int64_t)h->n * BS);
+            return hipGetLastError();
+        }
+    }
     auto kern = k_dd_apply_slots<BS, TS, TC, NT, MB, PD, LIC>;
     static bool done = false;
     hipError_t e = allow_full_lds(kern, done);
     if (e != hipSuccess) return e;
-    const int lds = h->S * BS * (int)sizeof(TC);
     launch_timed(h, kern, dim3(h->nsub, nrhs), NT, lds, st, r, z, h->S, slot_tabs(h),
                  (const uint64_t *)h->sw[0].desc, lv, (const uint64_t *)h->sw[1].desc, uv, state, lic_args(h),
                  (int64_t)h->n * BS, (const int32_t *)nullptr, (const int32_t *)nullptr);
@@ -1528,10 +1584,8 @@ static hipError_t launch_slots_mb(dd_ctx *h, const double *r, double *z, const i
 constexpr int kFusedStaticLds = 512;  // the kernel's ticket and partial sums (bound)
 
 int fused_unsupported(const dd_ctx *h) {
-    constexpr int kMaxNT = 1024;
-    const int rpp = (kWave / h->bs) * (kMaxNT / kWave);
     if (h->pc_kind != 0 || h->profile) return 1;
-    if (!(h->variant == 0 || h->variant == 3) || !h->slots || h->max_level_width > rpp) return 2;
+    if (!(h->variant == 0 || h->variant == 3) || !h->slots || h->max_level_width > one_pass_rows(h)) return 2;
     if (h->nsub > h->spmv_part_stride) return 3;
     if (apply_lds_bytes(h, h->precision) > 163840 - kFusedStaticLds) return 4;
     return 0;
@@ -1769,7 +1823,7 @@ static hipError_t launch_slots_nt(dd_ctx *h, const double *r, double *z, const i
         case 64: return launch_slots_mb<BS, TS, TC, 64, LIC>(h, r, z, state, st, lv, uv, nrhs);
         case 128: return launch_slots_mb<BS, TS, TC, 128, LIC>(h, r, z, state, st, lv, uv, nrhs);
         case 256: return launch_slots_mb<BS, TS, TC, 256, LIC>(h, r, z, state, st, lv, uv, nrhs);
-        default: return launch_slots_mb<BS, TS, TC, 512, LIC>(h, r, z, state, st, lv, uv, nrhs);
+        default: return launch_slots_mb<BS, TS, TC, kSlotLanes, LIC>(h, r, z, state, st, lv, uv, nrhs);
     }
 }
 
@@ -1817,7 +1871,7 @@ hipError_t launch_apply_batch(dd_ctx *h, const double *r, double *z, int nrhs, h
 // one pass of 1,024 lanes.
 hipError_t launch_apply_adjoint(dd_ctx *h, const double *g, double *a, int nrhs, hipStream_t st) {
     if (h->bs != 3 || !h->slots || !h->lic.ready || !h->lic.adj_val[1]) return hipErrorInvalidValue;
-    if (h->max_level_width > (kWave / 3) * (1024 / kWave)) return hipErrorInvalidValue;
+    if (h->max_level_width > one_pass_rows(h)) return hipErrorInvalidValue;
     const double *lv = h->lic.adj_val[0], *uv = h->lic.adj_val[1];
     return launch_slots_nt<3, double, double, false>(h, g, a, nullptr, st, lv, uv, nrhs);
 }
