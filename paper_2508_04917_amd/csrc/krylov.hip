@@ -1153,7 +1153,9 @@ static int run_typed(dd_ctx *h, const KrylovWork &W, const double *b, double *x,
                         const int itk = chunk_first + k;
                         if (itk > hk.iters) break;
                         for (int a = 0; a < 2; ++a) {
-                            if (a == 1 && itk == hk.iters && hk.state != ST_RUN && hk.half) continue;
+                            // a half step found converged before the second apply (see early) ends
+                            // the iteration there
+                            if (a == 1 && early && itk == hk.iters && hk.state != ST_RUN && hk.half) continue;
                             float ms = 0.f;
                             KCHK(hipEventElapsedTime(&ms, h->events[4 * k + 2 * a], h->events[4 * k + 2 * a + 1]));
                             apply_ms += ms;

@@ -65,3 +65,17 @@ def test_first_residuals(nz):
     assert info["iters"] == k
     assert np.allclose(hist.cpu().numpy(), ref.history, rtol=1e-8, atol=0)
     s.close()
+
+
+@pytest.mark.parametrize("ny,nz", [(32, 32), (32, 33), (256, 128)], ids=["256_partials", "264_partials", "2^21_values"])
+def test_applies_of_a_half_step_exit(ny, nz):
+    """The second apply of the last iteration counts where it runs: below 2^21
+    values the half step is tested after it."""
+    p = lines(ny, nz)
+    s = DDSolver.from_problem(p, sub=(64, 1, 1))
+    b = torch.as_tensor(p.b, device="cuda")
+    dd.dd_set_profiling(s.h, True)
+    _, info = dd.bicgstab_solve(s.h, b, torch.zeros_like(b), rtol=1e-8, maxit=50)
+    assert info["iters"] == 1 and info["applies"] == (1 if p.n >= 1 << 21 else 2)
+    assert info["apply_seconds"] > 0
+    s.close()
