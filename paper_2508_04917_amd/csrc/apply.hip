@@ -1549,6 +1549,30 @@ static int slot_threads(const dd_ctx *h, int nrhs) {
     return waves * kWave;
 }
 
+// The same for the segmented layout, whose levels are counted in positions (a
+// row takes one for each of its segments): enough wavefronts for the widest
+// level, at most 8 and, where half the CUs have no workgroup, 16; at most as
+// many as keep the workgroups a CU can take resident (it holds 16 wavefronts
+// of this kernel).  Counted in rows, as above, a box of a 27-point operator
+// got a seventh of what its levels ask for.  Measured, us per apply with 1 / 2
+// / 4 / 8 / 16 wavefronts (before the chunks always 16; then by rows): 27-point
+// 64^3 3x3 in 8^3 boxes 154 / 104 / 86 / 84 / 113 (132; 154), scalar in 16^3
+// 363 / 218 / 139 / 98 / 96 (113; 218), 96^3 scalar in 24^3 1193 / 654 / 368 /
+// 246 / 194 (214; 368), 64^3 3x3 in 4^3 68 / 74 / 93 / 165 / 335 (408; 70);
+// 491,520 3x3 rows of a nearest-neighbour graph in parts of 1,920 rows 135 /
+// 82 / 62 / 61 / 63 (67; 62), of 240 46 / 45 / 48 / 63 / 110 (122; 64), of 60
+// 43 / 46 / 73 / 142 / 303 (334; 74).
+static int seg_threads(const dd_ctx *h, int nrhs, int lds) {
+    const int rpw = kWave / h->bs;
+    const int64_t boxes = h->nsub * (int64_t)nrhs;
+    const int64_t resident = std::max<int64_t>(1, std::min<int64_t>((boxes + 255) / 256, 163840 / lds));
+    const int64_t most = resident > 1 ? std::min<int64_t>(8, 16 / resident) : (boxes <= 128 ? 16 : 8);
+    const int64_t widest = h->max_level_width * std::max(h->sw[0].snpos, h->sw[1].snpos) / h->n;
+    int waves = 1;
+    while (2 * waves <= most && waves * rpw < widest) waves *= 2;
+    return waves * kWave;
+}
+
 // The segmented slot layout (rows of more than three blocks); MB = the
 // layout's blocks per segment (2 or 3).
 template <int BS, typename TS, typename TC>
@@ -1560,7 +1584,7 @@ static hipError_t launch_seg(dd_ctx *h, const double *r, double *z, const int32_
         if (e != hipSuccess) return e;
         const int lds = h->S * BS * (int)sizeof(TC);
         const Sweep &L = h->sw[0], &U = h->sw[1];
-        launch_timed(h, kern, dim3(h->nsub, nrhs), slot_threads(h, nrhs), lds, st, r, z, h->S,
+        launch_timed(h, kern, dim3(h->nsub, nrhs), seg_threads(h, nrhs, lds), lds, st, r, z, h->S,
                      slot_tabs(h), (const uint64_t *)L.desc, lv, (const uint64_t *)U.desc, uv, state, lic_args(h),
                      (int64_t)h->n * BS, (const int32_t *)L.gpos, (const int32_t *)U.gpos);
         return hipGetLastError();
