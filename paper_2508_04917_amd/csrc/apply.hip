@@ -854,7 +854,7 @@ __device__ __forceinline__ int2 wave_entries(const int2 *__restrict__ tab, int n
 // chunk k: in between it only joins the barriers.  ent: the wavefront's
 // first 64 table entries, one per lane (wave_entries); a step reads its own
 // by a lane read, so no memory access stands in the level chain.
-template <int BS, typename TS, typename TC, int MB, int PD, bool UPPER, bool SEG = false, bool EXACT = false>
+template <int BS, typename TS, typename TC, int MB, int PD, bool UPPER, bool SEG = false, bool EXACT = false, bool ONE = false>
 __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, int64_t pcount,
                                             const int2 *__restrict__ tab, int n, int nlev, int2 ent,
                                             const uint64_t *__restrict__ desc, const TS *__restrict__ sval, int wave,
@@ -893,21 +893,41 @@ __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, i
     // The next fetch goes into the set the step before freed, after the first
     // barrier, where a wavefront that skips levels has nothing else to do.
     // Past the last chunk the fetches are empty (offsets beyond the slice),
-    // so that every wait counts the same.
-    for (int i0 = 0; i0 < steps; i0 += PD + 1) {
+    // so that every wait counts the same (drain: left out, and the wait is for
+    // everything in flight).
+    auto step = [&](int u, auto drain) {
+        const int l = lev[u];
+        if (cur < l) {
+            __syncthreads();
+            ++cur;
+        }
+        if (!drain || next < steps)
+            fetch((u + PD) % (PD + 1));
+        else
+            ++next;
+        for (; cur < l; ++cur) __syncthreads();
+        if (drain && next > steps)
+            vm_wait_all();
+        else
+            vm_wait<PD * SR::NLOAD>();  // set u is the oldest of the PD + 1 in flight
+        slot_claim(R[u]);
+        slot_compute<BS, TS, TC, MB, UPPER, SEG, EXACT>(y, R[u], c);
+    };
+    int i0 = 0;
+    // ONE (workgroups of one wavefront: small boxes, many to a CU): the steps
+    // whose fetches are all real, then those that drain.  At 4^3 a sixth of a
+    // sweep's fetches would be empty: 64^3 3x3 26.3 -> 25.2 us, scalar 13.4 ->
+    // 12.3 (before the chunks 25.5 and 12.4).  With more wavefronts a chain of
+    // few steps waits longer in the draining ones (scalar 16^3 8.6 -> 9.6).
+    if constexpr (ONE)
+        for (; i0 + 2 * PD + 1 <= steps; i0 += PD + 1)
+#pragma unroll
+            for (int u = 0; u <= PD; ++u) step(u, std::false_type{});
+    for (; i0 < steps; i0 += PD + 1) {
 #pragma unroll
         for (int u = 0; u <= PD; ++u) {
             if (i0 + u >= steps) break;
-            const int l = lev[u];
-            if (cur < l) {
-                __syncthreads();
-                ++cur;
-            }
-            fetch((u + PD) % (PD + 1));
-            for (; cur < l; ++cur) __syncthreads();
-            vm_wait<PD * SR::NLOAD>();  // set u is the oldest of the PD + 1 in flight
-            slot_claim(R[u]);
-            slot_compute<BS, TS, TC, MB, UPPER, SEG, EXACT>(y, R[u], c);
+            step(u, std::bool_constant<ONE>{});
         }
     }
     // nothing may still be loading into these registers once they are free
@@ -927,7 +947,7 @@ struct SlotTabs {
 // One subdomain's apply with the slot layout: r's slice into LDS (plus the
 // learned correction), the lower sweep, the upper sweep with the diagonal
 // scaling, and the slice back to z.
-template <int BS, typename TS, typename TC, int MB, int PD, bool LIC, bool SEG = false, bool EXACT = false>
+template <int BS, typename TS, typename TC, int MB, int PD, bool LIC, bool SEG = false, bool EXACT = false, bool ONE = false>
 __device__ __forceinline__ void apply_slots_sub(
     TC *__restrict__ y, int s, const double *__restrict__ r, double *__restrict__ z, int S, const SlotTabs &tabs,
     const uint64_t *__restrict__ Ldesc, const TS *__restrict__ Lval, const uint64_t *__restrict__ Udesc,
@@ -950,10 +970,10 @@ __device__ __forceinline__ void apply_slots_sub(
     if constexpr (LIC) lic_finish<BS, TC>(y, r, lst, lpass, la, tid, nt);
     const int64_t lb = SEG ? (int64_t)Lgpos[s] : base, ub = SEG ? (int64_t)Ugpos[s] : base;
     const int64_t lc = SEG ? Lgpos[s + 1] - lb : S, uc = SEG ? Ugpos[s + 1] - ub : S;
-    sweep_slots<BS, TS, TC, MB, PD, false, SEG, EXACT>(y, lb, lc, tabs.ltab + li.x, li.y, li.z, le, Ldesc, Lval,
-                                                       wave, nw, lane);
-    sweep_slots<BS, TS, TC, MB, PD, true, SEG, EXACT>(y, ub, uc, tabs.utab + ui.x, ui.y, ui.z, ue, Udesc, Uval, wave,
-                                                      nw, lane);
+    sweep_slots<BS, TS, TC, MB, PD, false, SEG, EXACT, ONE>(y, lb, lc, tabs.ltab + li.x, li.y, li.z, le, Ldesc, Lval,
+                                                            wave, nw, lane);
+    sweep_slots<BS, TS, TC, MB, PD, true, SEG, EXACT, ONE>(y, ub, uc, tabs.utab + ui.x, ui.y, ui.z, ue, Udesc, Uval,
+                                                           wave, nw, lane);
     double *zs = z + base * BS;
     store_slice<TC, !LIC>(zs, y, S * BS, tid, nt);
 }
@@ -985,8 +1005,9 @@ __global__ __launch_bounds__(NT) void k_dd_apply_slots(
     extern __shared__ unsigned char dd_smem[];
     const uint2 item = batch_item();
     const int64_t off = (int64_t)item.y * vstride;  // a batch's right-hand sides lie one after another
-    apply_slots_sub<BS, TS, TC, MB, PD, LIC, SEG>(reinterpret_cast<TC *>(dd_smem), (int)item.x, r + off, z + off, S,
-                                                  tabs, Ldesc, Lval, Udesc, Uval, la, stopped, Lgpos, Ugpos);
+    apply_slots_sub<BS, TS, TC, MB, PD, LIC, SEG, false, NT == kWave>(
+        reinterpret_cast<TC *>(dd_smem), (int)item.x, r + off, z + off, S, tabs, Ldesc, Lval, Udesc, Uval, la, stopped,
+        Lgpos, Ugpos);
 }
 
 // The same where levels are wider than a pass of 1,024 lanes (launch_slots).
@@ -1541,10 +1562,14 @@ static hipError_t launch_slots(dd_ctx *h, const double *r, double *z, const int3
 // 252; 64^3 in 8x8x16 (64 rows) 34.0 / 32.3 / 33.2 / 36.2; 48^3 in 8^3 (48
 // rows) 15.6 / 14.4 / 16.2 / 19.6; scalar 16^3 in 8^3 (48 rows, one chunk)
 // 8.9 / 9.0 / 9.4 / 11.3 and 11.7 with 1; 64^3 in 4^3 (12 rows, 16 workgroups
-// per CU) 42 / 52 / 85 / 170 and 37 with 1.
+// per CU) 42 / 52 / 85 / 170 and 37 with 1.  One wavefront each where a CU
+// takes 16 workgroups, which fill its wavefronts: 96^3 in 6^3 boxes (27 rows)
+// with 2 / 1 97.2 / 94.7, with FP32 factors 46.9 / 43.1.
 static int slot_threads(const dd_ctx *h, int nrhs) {
     const int rpw = kWave / h->bs;
-    int waves = h->nsub * (int64_t)nrhs <= 256 ? 2 : 1;
+    const int64_t boxes = h->nsub * (int64_t)nrhs;
+    if ((boxes + 255) / 256 >= 16 && h->S * h->bs * 8 * 16 <= 163840) return kWave;
+    int waves = boxes <= 256 ? 2 : 1;
     while (waves < 8 && waves * rpw <= h->max_level_width) waves *= 2;
     return waves * kWave;
 }

@@ -56,3 +56,30 @@ def test_apply(name):
     s.set_precision(P.ddilu.DD_MIXED)
     check_close(s.apply(rd).cpu().numpy(), st.apply_fp32_factors(r, round_input=False), st.bs, 1e-10, what=name + " mixed")
     s.close()
+
+
+@pytest.mark.parametrize("bs", [3, 1])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 70])
+def test_one_wavefront(k, bs):
+    """Workgroups of one wavefront: 272 boxes of a line of k rows, one chunk a
+    level, whatever remainder the prefetch depth leaves."""
+    p = random_blocks(k, 17, 16, seed=37) if bs == 3 else laplacian_scalar(k, 17, 16, seed=37)
+    s = DDSolver.from_problem(p, sub=(k, 1, 1))
+    st = O.setup(p, (k, 1, 1))
+    r = np.random.default_rng(8).standard_normal(st.n * st.bs)
+    rd = torch.as_tensor(r, device="cuda")
+    check_close(s.apply(rd).cpu().numpy(), st.apply(r), st.bs, 1e-12, what=f"line {k}", scale=dd_scale(st, r))
+    s.set_precision(P.ddilu.DD_MIXED)
+    check_close(s.apply(rd).cpu().numpy(), st.apply_fp32_factors(r, round_input=False), st.bs, 1e-10, what=f"line {k} mixed")
+    s.close()
+
+
+def test_sixteen_boxes_a_cu():
+    """Levels of more rows than a wavefront takes, on one wavefront a box."""
+    p = pairs(44, 64, 61, seed=38)
+    s = DDSolver.from_problem(p, sub=(44, 1, 1))
+    st = O.setup(p, (44, 1, 1))
+    r = np.random.default_rng(9).standard_normal(st.n * st.bs)
+    rd = torch.as_tensor(r, device="cuda")
+    check_close(s.apply(rd).cpu().numpy(), st.apply(r), st.bs, 1e-12, what="pairs", scale=dd_scale(st, r))
+    s.close()
