@@ -648,10 +648,7 @@ extern "C" int dd_get_factors(dd_handle h, int32_t *ptr, int32_t *col, double *f
     hipStream_t st = as_stream(hip_stream);
     if (ptr) HCHK(hipMemcpyAsync(ptr, h->tptr, (h->n + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
     if (col) HCHK(hipMemcpyAsync(col, h->tcol, h->nnzt * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
-    if (f) {
-        HCHK(launch_lu_blocks(h, st));
-        HCHK(launch_export_factors(h, f, st));
-    }
+    if (f) HCHK(launch_export_factors(h, f, st));
     return DD_OK;
 }
 

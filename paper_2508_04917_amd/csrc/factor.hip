@@ -798,7 +798,7 @@ hipError_t launch_bilu0_slots(dd_ctx *h, hipStream_t st) {
 
 // L and U in the dropped pattern, from the streams and the matrix (the
 // patterns of k_bilu0_slots leave U's off-diagonal blocks as A's): for the
-// CSR streams, the adjoint streams and the export.  Their diagonal blocks are
+// CSR streams and the adjoint streams.  Their diagonal blocks are
 // inv_D's, so lu's are not written.  Written with every factorisation, the
 // copy was 1.1 of its 2.3 GB of stores (2,097,152 3x3 rows).
 template <int BS>
@@ -827,6 +827,39 @@ hipError_t launch_lu_blocks(dd_ctx *h, hipStream_t st) {
         k_lu_blocks<3><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->aval, h->sw[0].sval64, h->lu);
     else
         k_lu_blocks<1><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->aval, h->sw[0].sval64, h->lu);
+    return hipGetLastError();
+}
+
+// The factors in the dropped pattern (see dd_get_factors) from the streams,
+// which hold them in that form; one thread per value a row can have, so a
+// row's blocks are written as one run.  64^3 3x3 blocks: 334 us with L and U made
+// first (k_lu_blocks, k_export), 112 with L and U at hand, 79 like this.
+template <int BS>
+__global__ __launch_bounds__(256) void k_export_slots(int64_t n, int MB, const int4 *__restrict__ rec,
+                                                     const double *__restrict__ lval,
+                                                     const double *__restrict__ uval, double *__restrict__ f) {
+    constexpr int BB = BS * BS;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int row = (2 * MB + 1) * BB;
+    const int64_t p = t / row;
+    if (p >= n) return;
+    const int q = (int)(t - p * row), j = q / BB, e = q - j * BB;
+    const int4 r = rec[2 * p];
+    const int nlow = r.w & 0xff, nupp = r.w >> 8 & 0xff;
+    if (j >= nlow + 1 + nupp) return;
+    // lower blocks, inv_D (the upper stream's last slot), upper blocks
+    const int k = j == nlow ? MB : j - nlow - 1;
+    f[(int64_t)r.y * BB + q] = j < nlow ? lval[(p * BS + e / BS) * MB * BS + j * BS + e % BS]
+                                        : uval[((int64_t)r.z * BS + e / BS) * (MB + 1) * BS + k * BS + e % BS];
+}
+
+hipError_t launch_export_slots(dd_ctx *h, double *f, hipStream_t st) {
+    const int64_t threads = h->n * (2 * h->slots + 1) * h->bs * h->bs;
+    const unsigned g = (unsigned)((threads + 255) / 256);
+    if (h->bs == 3)
+        k_export_slots<3><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->sw[0].sval64, h->sw[1].sval64, f);
+    else
+        k_export_slots<1><<<g, 256, 0, st>>>(h->n, h->slots, h->frec, h->sw[0].sval64, h->sw[1].sval64, f);
     return hipGetLastError();
 }
 

@@ -285,6 +285,7 @@ hipError_t launch_seg_pack(dd_ctx *h, hipStream_t st);
 // the wave-chunk table of a sweep of the slot layout
 int build_wave_chunks(dd_ctx *h, int which, hipStream_t st);
 hipError_t launch_export_factors(dd_ctx *h, double *f, hipStream_t st);
+hipError_t launch_export_slots(dd_ctx *h, double *f, hipStream_t st);  // where launch_bilu0_slots factored
 // out[k] = val[src[k]] for nblk blocks of bb values
 hipError_t launch_gather_blocks(int64_t nblk, int bb, const int32_t *src, const double *val, double *out,
                                 hipStream_t st);

@@ -598,6 +598,7 @@ __global__ void k_export(int64_t n, const int32_t *tptr, const int32_t *tcol, co
 }
 
 hipError_t launch_export_factors(dd_ctx *h, double *f, hipStream_t st) {
+    if (h->direct) return launch_export_slots(h, f, st);
     const int T = 256;
     const unsigned g = (unsigned)((h->n + T - 1) / T);
     if (h->bs == 3)
