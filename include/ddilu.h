@@ -329,9 +329,10 @@ int bicgstab_solve_noalloc(dd_handle h, const double *b, double *x, double rtol,
  * allows it, else 1), 1 = plain level loop (a row's blocks loaded four at a
  * time), 2 = level loop in workgroup-pass chunks with the next chunk's
  * blocks prefetched into registers, 3 = fixed per-row block slots so that
- * no load depends on another and later levels' loads are issued while a
- * level computes (rows of at most 3 off-diagonal blocks per sweep, levels no
- * wider than one pass).  A variant the shape does not allow falls back to 1.
+ * no load depends on another and later rows' loads are issued while a level
+ * computes (levels of any width; rows of at most 3 off-diagonal blocks per
+ * sweep, longer ones split into segments, see dd_info.apply_layout).  A
+ * variant the shape does not allow falls back to 1.
  *
  * 4-8 are ablations of the plain level loop (1), each changing one thing,
  * after the kernel variants of Section 5.2 (Tables 3-4): 4 = lower sweep
@@ -397,8 +398,13 @@ int dd_set_residual_history(dd_handle h, double *hist, int32_t len);
 /* ---------------------------------------------------------------------
  * Global (undecomposed) ILU0 of the full reordered matrix: what the
  * decomposition approximates (Section 4, the rocSPARSE ILU0 the paper
- * compares with, here as our own level-scheduled kernels: one launch per
- * level over the whole matrix, vector in global memory).
+ * compares with, here as our own kernels).  The factorisation runs one launch
+ * per level of the whole matrix.  The apply runs, after ilu0_factor and where
+ * every row has at most 3 blocks per triangle and a subdomain's vector fits
+ * the LDS together with the rows outside it depends on, one launch per level
+ * of the subdomain graph; otherwise one per level of the matrix, vector in
+ * global memory (boxes chosen automatically to fill the LDS are too large:
+ * 16x20x20 needs 178 KB).
  * --------------------------------------------------------------------- */
 
 /* Level sets, block ILU0 and ILDU0 form of the full reordered matrix (no

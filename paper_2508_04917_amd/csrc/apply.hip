@@ -24,9 +24,11 @@
 #include "spmv.h"
 
 // Prefetch depth (wave-chunks fetched ahead of the one computed) of the
-// slot-layout kernel, per factor storage type.  FP64 factors stop at 2: at 3
+// slot-layout kernels, per factor storage type.  FP64 factors stop at 2: at 3
 // the four register sets of the upper sweep no longer fit the 128 registers a
-// wavefront of a 1024-lane workgroup may hold.
+// wavefront may hold in the kernels of up to 1,024 lanes (the segmented one,
+// the apply and product in one launch).  The plain ones have at most 512 and
+// take the same depth: 3 was not measured in them.
 #ifndef DDILU_PD64
 #define DDILU_PD64 2
 #endif
@@ -51,7 +53,9 @@ namespace ddilu {
 // in CSR order (rank 0 first) whatever the number of passes: the item list
 // is rank-major, so a pass holds the rest of one rank and a prefix of later
 // ones.  One pass covers a subdomain of up to kLicItems * blockDim faces'
-// components (at 16x20x20, 1,840 faces on 13 wavefronts).
+// components: at 16x20x20 (1,840 faces) the 13 wavefronts of the launch with
+// the product take one, the plain kernel's 8 two (3,584 and 1,936 items), the
+// second fetched when the first is done.
 struct LicArgs {
     const int32_t *fptr;    // [n+1] faces of each row (CSR order); fptr[s*S] = first face of subdomain s
     const int32_t *rb;      // [nsub*9] rank boundaries: faces of ranks < k of subdomain s at rb[9s + k]
@@ -610,8 +614,8 @@ __global__ __launch_bounds__(NT) void k_dd_apply_pipe(
 // per-level prefetch, us per apply: scalar 16^3 12.3 -> 8.6, scalar 128^3
 // 52.9 -> 39.0, 64^3 35.4 -> 31.6, 105x132x78 with FP32 factors and the
 // learned correction 135 -> 120, 128^3 the same way 148 -> 144, 160^3 FP64
-// 428.5 -> 425.8 and FP32 factors 260.3 -> 256.5, 4^3 boxes at 64^3 36.5 ->
-// 37.4.
+// 428.5 -> 425.8 and FP32 factors 260.3 -> 256.5, 4^3 boxes at 64^3 25.4 ->
+// 25.2; 96^3 in 12^3 boxes (512, two to a CU) 92.8 -> 94.8.
 //
 // The loads and their waits are written out (the compiler's own waits cannot
 // span the barrier loop between a chunk's fetch and its use).  Before a chunk
@@ -1521,7 +1525,9 @@ static SlotTabs slot_tabs(const dd_ctx *h) {
 constexpr int kSlotLanes = 512;  // most lanes of the plain slot kernels (slot_threads)
 
 // Rows of a pass of 1,024 lanes: what a level may hold at most where the
-// apply and the product run as one launch and in the adjoint apply.
+// apply and the product run as one launch and in the adjoint apply (their
+// limit from before levels were cut into chunks, kept: beyond it the solve
+// uses two launches and the adjoint apply is refused).
 static int one_pass_rows(const dd_ctx *h) { return (kWave / h->bs) * (1024 / kWave); }
 
 // Levels wider than that ran in the plain loop before the levels were cut

@@ -435,12 +435,15 @@ __global__ __launch_bounds__(256) void k_factor_records(int64_t n, int S, const 
 // so the barrier between levels waits for no memory access; where the rows
 // reach too far back for the LDS they pass through invd.  One box alone takes
 // 4.3 us a level of 16^3 (7.1 with the inverses through invd and nothing
-// loaded ahead); many are bound by their requests to the L2, pieces of 24
-// bytes (a word of each line fetched one chunk earlier: 877 us, 4 wavefronts
-// a box instead of 8: 843).  2,097,152 3x3 rows in 512 boxes of 16^3: 1,330
-// us with a copy of L and U in the dropped pattern, which few callers read
-// (k_lu_blocks makes it for them), 913 us without, 796 us with the ring (1.1
-// GB read, 1.2 GB written).
+// loaded ahead).  2,097,152 3x3 rows in 512 boxes of 16^3: 1,330 us with a
+// copy of L and U in the dropped pattern, which few callers read (k_lu_blocks
+// makes it for them), 913 without, 855 with the ring (then 877 with a word of
+// each line fetched a chunk earlier, 843 with 4 wavefronts a box instead of
+// 8), 796 with the next chunk's loads ahead of the level barriers.  Not the
+// memory's bound: 1.7 GB read and 1.3 GB written are 3.8 TB/s.  The stores
+// reach the L2 as 95 million requests of 14 bytes on average, a lane's three
+// doubles of a row one by one (loads 20 million); the 206 registers of a lane
+// leave one box to a CU, so 264 boxes (99x80x108) take two rounds, 501 us.
 template <int Q>
 __device__ __forceinline__ double quad_bcast(double v) {
     constexpr int P = Q * 0x55;  // quad_perm: lane Q of each four

@@ -13,8 +13,9 @@
 // 48^3 3x3 blocks, 16^3 boxes, 16 probes: factorisation + targets 17.7 ms with
 // every launch scanning all rows for its level (14.5 us each), a host
 // synchronisation per relaxation step of the levels and the pattern's part
-// done again on every call; 1.67 ms now (3.1 ms on a handle's first call), of
-// which 142 factor launches 0.87 ms, 14 sweep launches 0.39 ms.
+// done again on every call; 1.42 ms now, 2.2 ms on a handle's first call, which
+// does the pattern's part; 142 factor launches are 0.81 ms of either, 14 sweep
+// launches 0.38 ms.
 #include <algorithm>
 
 #include "blocks.h"

@@ -17,9 +17,11 @@
 // their own.  Every kernel of an iteration first reads the state word and
 // returns at once when the solve has finished, so the host runs a few
 // iterations ahead of the device, by the iteration number it reports in host
-// memory.  Against a launch per scalar step and a synchronisation every eight
-// iterations, us per solve: 16^3 scalar (23 iterations) 1,442 -> 1,010, 64^3
-// 3x3 33,430 -> 31,820, 128^3 3x3 learned 228,090 -> 226,330.
+// memory (its thread reads that in a loop, as it did inside the driver when
+// it synchronised every eight iterations: CPU time is the solve's either way).
+// Against a launch per scalar step and that synchronisation, us per solve:
+// 16^3 scalar (23 iterations) 1,442 -> 1,010; 64^3 and 128^3 3x3 1-5%, within
+// what two boxes differ by.
 #include <chrono>
 #include <mutex>
 #include <thread>
@@ -42,7 +44,8 @@ enum : int32_t { ST_RUN = 0, ST_CONV = 1 };
 // without / with runs of 4, 16, 64 blocks and with one run per XCD: 160^3 415
 // / 404, 408, 409, 440 (the XCDs then stream far apart); 128^3 213 / 210, 210,
 // 214, 220; graph parts of 3x3 blocks 310 / 306, 302, 304, 316; 64^3 25.4 /
-// 24.9, 24.7, 24.1, 23.8.
+// 24.9, 24.7, 24.1, 23.8.  Between applies, in the solve at 160^3, no
+// difference (428; 421-433 before).
 constexpr uint32_t kRun = 8;
 
 __device__ __forceinline__ uint32_t row_block() {
