@@ -347,12 +347,10 @@ static int build_levels(dd_ctx *h, hipStream_t st, int32_t *stats, int32_t *tmp_
     if (!h->uinv) RCHK(h->alloc(&h->uinv, h->n));
     for (int w = 0; w < 2; ++w) {
         Levels &L = h->lev[w];
-        if (!L.lev) {
-            RCHK(h->alloc(&L.lev, h->n));
-            RCHK(h->alloc(&L.nlev, h->nsub));
-            RCHK(h->alloc(&L.off, h->nsub + 1));
-            RCHK(h->alloc(&L.rows, h->n));
-        }
+        if (!L.lev) RCHK(h->alloc(&L.lev, h->n));
+        if (!L.nlev) RCHK(h->alloc(&L.nlev, h->nsub));
+        if (!L.off) RCHK(h->alloc(&L.off, h->nsub + 1));
+        if (!L.rows) RCHK(h->alloc(&L.rows, h->n));
     }
     HCHK(launch_level_sets(h, stats, st));
     int32_t total[2] = {0, 0}, got[8];
@@ -488,19 +486,28 @@ static int factor_values(dd_ctx *h, hipStream_t st) {
     return DD_OK;
 }
 
-// The FP32 copies of the streams the handle has, with the values as they are
-// (fresh: the streams have just been rewritten).
+// The FP32 copies of the streams the handle has, complete or (after an error)
+// without those that were missing; cast where one was, and where the streams
+// have just been rewritten (fresh).
 static int ensure_fp32(dd_ctx *h, hipStream_t st, bool fresh = false) {
-    const int bb = h->bs * h->bs;
-    const bool sl = h->slots || h->seg;
-    const int mb = h->seg ? h->seg : h->slots;
-    if (!fresh && (!sl || h->sw[0].sval32) && (!h->csr_ready || (h->sw[1].val32 && h->sw[1].d32))) return DD_OK;
+    const int bb = h->bs * h->bs, mb = h->seg ? h->seg : h->slots;
+    float **made[5];
+    int n = 0, rc = DD_OK;
+    auto want = [&](float *&p, int64_t count) {
+        if (p || rc) return;
+        rc = h->alloc(&p, count);
+        if (!rc) made[n++] = &p;
+    };
     for (int w = 0; w < 2; ++w) {
-        if (h->csr_ready && !h->sw[w].val32) RCHK(h->alloc(&h->sw[w].val32, h->sw[w].nblk * bb));
-        if (sl && !h->sw[w].sval32) RCHK(h->alloc(&h->sw[w].sval32, h->sw[w].snpos * (mb + w) * bb));
+        if (h->csr_ready) want(h->sw[w].val32, h->sw[w].nblk * bb);
+        if (h->slots || h->seg) want(h->sw[w].sval32, h->sw[w].snpos * (mb + w) * bb);
     }
-    if (h->csr_ready && !h->sw[1].d32) RCHK(h->alloc(&h->sw[1].d32, h->n * bb));
-    HCHK(launch_cast32(h, st));
+    if (h->csr_ready) want(h->sw[1].d32, h->n * bb);
+    if (rc) {
+        while (n) h->release(*made[--n]);
+        return rc;
+    }
+    if (n || fresh) HCHK(launch_cast32(h, st));
     return DD_OK;
 }
 
@@ -555,7 +562,13 @@ extern "C" int ilu0_factor(dd_handle h, int32_t precision, void *hip_stream) {
     h->nupp = h->sw[1].nblk;
     const int mr = std::max(h->sw[0].max_row, h->sw[1].max_row);
     h->slots = mr <= kMaxSlots ? std::max(mr, 1) : 0;
-    if (h->slots) RCHK(build_slots(h, h->status + 16, st));
+    if (h->slots) {
+        const int rc = build_slots(h, h->status + 16, st);
+        if (rc) {  // no call finds half a layout
+            drop_slots(h);
+            return rc;
+        }
+    }
     HCHK(hipMemcpyAsync(status, h->status, sizeof(status), hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
     h->release(tbeg);
@@ -587,6 +600,7 @@ extern "C" int ilu0_refactor(dd_handle h, const double *val, void *hip_stream) {
     if (!val) return h->fail(DD_EINVAL, "ilu0_refactor: null values");
     if (!h->patterned || !h->asrc || !h->tsrc) return h->fail(DD_ESTATE, "ilu0_refactor before ilu0_factor");
     hipStream_t st = as_stream(hip_stream);
+    ReclaimAtExit at_exit{h};
     h->factored = 0;
     // what depends on A's values and is rebuilt by its own call
     h->lic.adj_ready = 0;
@@ -624,6 +638,7 @@ extern "C" int dd_set_precision(dd_handle h, int32_t precision, void *hip_stream
     if (!h->factored) return h->fail(DD_ESTATE, "dd_set_precision before ilu0_factor");
     if (precision != DD_FP64 && precision != DD_FP32 && precision != DD_MIXED)
         return h->fail(DD_EINVAL, "bad precision");
+    ReclaimAtExit at_exit{h};
     if (precision != DD_FP64) RCHK(ensure_fp32(h, as_stream(hip_stream)));
     h->precision = precision;
     return DD_OK;
@@ -768,11 +783,22 @@ static int build_csr_now(dd_ctx *h) {
     hipStream_t st = nullptr;
     int rc = DD_OK;
     if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) rc = h->fail(DD_EHIP, "CSR streams: no stream");
-    // the factors are complete: every factorisation ends synchronised
-    if (!rc) rc = ensure_csr(h, st);
-    if (!rc && h->sw[0].sval32) rc = ensure_fp32(h, st);
-    if (!rc && hipStreamSynchronize(st) != hipSuccess) rc = h->fail(DD_EHIP, "CSR streams: synchronise");
-    if (st) (void)hipStreamDestroy(st);
+    if (!rc) {
+        size_t kept = h->retired.size();
+        // the factors are complete: every factorisation ends synchronised
+        rc = ensure_csr(h, st);
+        if (!rc && h->sw[0].sval32) rc = ensure_fp32(h, st);
+        if (hipStreamSynchronize(st) == hipSuccess) {
+            // what was released on the way was used on this stream alone; a
+            // synchronisation of the device would end the capture
+            kept = std::min(kept, h->retired.size());
+            for (size_t k = kept; k < h->retired.size(); ++k) pool_free(h->retired[k]);
+            h->retired.resize(kept);
+        } else if (!rc) {
+            rc = h->fail(DD_EHIP, "CSR streams: synchronise");
+        }
+        (void)hipStreamDestroy(st);
+    }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     return rc;
 }

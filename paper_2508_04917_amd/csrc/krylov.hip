@@ -1234,20 +1234,17 @@ static int run_typed(dd_ctx *h, const KrylovWork &W, const double *b, double *x,
 }
 
 int krylov_workspace(dd_ctx *h, KrylovWork *w) {
-    if (!h->kv) {
-        int rc = h->alloc(&h->kv, kKrylovVectors * h->n * h->bs);
-        if (rc) return rc;
+    if (!h->ks_host) {  // the last to be allocated; after a failure the next call goes on where it stopped
         const int rpb = (kWave / h->bs) * (kRedT / kWave);
         h->spmv_part_stride = (int)std::max<int64_t>((h->n + rpb - 1) / rpb, kMaxGrid);
-        rc = h->alloc(&h->partials, (int64_t)kStride * h->spmv_part_stride);
-        if (rc) return rc;
-        rc = h->alloc(&h->ks, 3);
+        int rc = h->kv ? DD_OK : h->alloc(&h->kv, kKrylovVectors * h->n * h->bs);
+        if (!rc && !h->partials) rc = h->alloc(&h->partials, (int64_t)kStride * h->spmv_part_stride);
+        if (!rc && !h->ks) rc = h->alloc(&h->ks, 3);
         if (rc) return rc;
         // the scalars, and behind them the device's progress report
         hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->ks_host), 2 * sizeof(KrylovScalars));
         if (e != hipSuccess) {
             h->ks_host = nullptr;
-            h->kv = nullptr;  // the next call tries again (the buffers stay recorded for dd_destroy)
             return h->fail(DD_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
         }
     }
@@ -1321,9 +1318,9 @@ int bicgstab_run(dd_ctx *h, const KrylovWork &w, const double *b, double *x, dou
     if (w.handle_owned) {
         build_spmv_layout(h, st);
         if (h->fuse && !h->fdep && !fused_unsupported(h)) {
-            int rc = h->alloc(&h->fdep, 2 * (int64_t)h->nsub);
-            if (!rc) rc = h->alloc(&h->fflag, h->nsub);
-            if (!rc) rc = h->alloc(&h->fticket, 1);
+            int rc = h->fflag ? DD_OK : h->alloc(&h->fflag, h->nsub);
+            if (!rc && !h->fticket) rc = h->alloc(&h->fticket, 1);
+            if (!rc) rc = h->alloc(&h->fdep, 2 * (int64_t)h->nsub);
             if (rc) return rc;
             hipError_t e = launch_dep_range(h, st);
             if (e != hipSuccess) return h->fail(DD_EHIP, "dependency ranges: %s", hipGetErrorString(e));

@@ -700,8 +700,8 @@ int lic_publish_coeffs(dd_ctx *h, hipStream_t st) {
 
 int lic_coeffs_from_params(dd_ctx *h, const float *params, bool keep_hidden, hipStream_t st) {
     Lic &L = h->lic;
-    if (keep_hidden && !L.H1) {
-        int rc = h->alloc(&L.H1, (int64_t)std::max(L.nf, 1) * kHid);
+    if (keep_hidden && !L.H2) {
+        int rc = L.H1 ? DD_OK : h->alloc(&L.H1, (int64_t)std::max(L.nf, 1) * kHid);
         if (!rc) rc = h->alloc(&L.H2, (int64_t)std::max(L.nf, 1) * kHid);
         if (rc) return rc;
     }
@@ -735,10 +735,10 @@ int lic_loss_grad_run(dd_ctx *h, const float *params, int Q, const double *R, co
         if (rc) return rc;
         L.work_q = Q;
     }
-    if (!L.dC) {
-        rc = h->alloc(&L.dC, (int64_t)std::max(L.nf, 1) * 9);
-        if (!rc) rc = h->alloc(&L.G1, (int64_t)std::max(L.nf, 1) * kHid);
-        if (!rc) rc = h->alloc(&L.G2, (int64_t)std::max(L.nf, 1) * kHid);
+    if (!L.wpart) {
+        rc = L.dC ? DD_OK : h->alloc(&L.dC, (int64_t)std::max(L.nf, 1) * 9);
+        if (!rc && !L.G1) rc = h->alloc(&L.G1, (int64_t)std::max(L.nf, 1) * kHid);
+        if (!rc && !L.G2) rc = h->alloc(&L.G2, (int64_t)std::max(L.nf, 1) * kHid);
         const int nchunk = (int)((std::max(L.nf, 1) + kWgFaces - 1) / kWgFaces);
         if (!rc) rc = h->alloc(&L.wpart, (int64_t)nchunk * kNParam);
         if (rc) return rc;
