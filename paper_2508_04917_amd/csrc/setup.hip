@@ -561,7 +561,7 @@ hipError_t launch_cast32(dd_ctx *h, hipStream_t st) {
         if (m) k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, s.val64, s.val32);
     }
     const int64_t m = h->n * bb;
-    if (h->sw[1].d32) k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, h->sw[1].d64, h->sw[1].d32);
+    if (h->csr_ready && h->sw[1].d32) k_cast32<<<(unsigned)((m + T - 1) / T), T, 0, st>>>(m, h->sw[1].d64, h->sw[1].d32);
     if (h->slots || h->seg) {
         const int mb = h->seg ? h->seg : h->slots;
         for (int w = 0; w < 2; ++w) {
