@@ -209,6 +209,7 @@ struct dd_ctx {
     std::string err;
 
     int fail(int code, const char *fmt, ...);
+    hipError_t try_alloc(void **p, size_t bytes);  // for memory the call can do without: no error is recorded
     int alloc_bytes(void **p, size_t bytes);
     // device memory of count elements, recorded for dd_destroy
     template <typename T>

@@ -307,7 +307,7 @@ void build_spmv_layout(dd_ctx *h, hipStream_t st) {
     h->sell_spp = spp;
     auto grab = [&](size_t bytes) -> void * {
         void *p = nullptr;  // released with the handle, used or not
-        return h->alloc_bytes(&p, bytes) == DD_OK ? p : nullptr;
+        return h->try_alloc(&p, bytes) == hipSuccess ? p : nullptr;
     };
     int64_t nslots = nslice * kUnroll * rpw;
     if (parts || h->max_row_a > kUnroll) {

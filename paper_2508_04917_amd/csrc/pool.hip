@@ -184,15 +184,20 @@ void dd_ctx::reclaim() {
     retired.clear();
 }
 
-int dd_ctx::alloc_bytes(void **p, size_t bytes) {
+hipError_t dd_ctx::try_alloc(void **p, size_t bytes) {
     if (device < 0) (void)hipGetDevice(&device);
     hipError_t e = ddilu::pool_alloc(p, bytes);
     if (e != hipSuccess && !retired.empty()) {
         reclaim();
         e = ddilu::pool_alloc(p, bytes);
     }
+    if (e == hipSuccess) allocs.push_back(*p);
+    return e;
+}
+
+int dd_ctx::alloc_bytes(void **p, size_t bytes) {
+    const hipError_t e = try_alloc(p, bytes);
     if (e != hipSuccess) return fail(DD_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-    allocs.push_back(*p);
     return DD_OK;
 }
 

@@ -42,7 +42,10 @@ hipError_t hipMemGetInfo(size_t *f, size_t *t) {
 const char *hipGetErrorString(hipError_t) { return ""; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipHostFree(void *) { return hipSuccess; }
-int dd_ctx::fail(int code, const char *, ...) { return code; }
+int dd_ctx::fail(int code, const char *, ...) {
+    err = "failed";
+    return code;
+}
 
 static const size_t MB = size_t(1) << 20;
 
@@ -91,5 +94,9 @@ int main() {
     ddilu::pool_free(a);
     fail_malloc = true;
     CHECK(ddilu::pool_alloc(&c, 64 * MB) == hipErrorOutOfMemory && live.empty());
+    // memory that a call can do without leaves no error message behind
+    dd_ctx h;
+    CHECK(h.try_alloc(&c, 64 * MB) == hipErrorOutOfMemory && h.err.empty());
+    CHECK(h.alloc_bytes(&c, 64 * MB) == DD_ENOMEM && !h.err.empty());
     return 0;
 }
