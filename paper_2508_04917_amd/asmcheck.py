@@ -1,4 +1,6 @@
-"""Build-time check of the slot-layout apply kernels' hand-scheduled loads.
+"""Build-time checks of the device assembly: hand-scheduled loads, LDS at barriers.
+
+The first concerns the slot-layout apply kernels.
 
 The slot kernels issue their factor loads from inline assembly and wait for
 them with explicit ``s_waitcnt`` instructions, so the compiler does not know
@@ -17,6 +19,15 @@ register.  ``check_file`` applies it to every kernel whose symbol contains
 the given pattern.  The wait counts themselves are not checked here; the
 kernels are written so that a level's registers are claimed only after a
 wait that leaves just the loads of later levels outstanding.
+
+The second concerns every kernel of the library: at an ``s_barrier`` no LDS access of the
+wavefront may be outstanding, or another wavefront may read past the barrier
+what has not been written, or overwrite what has not been read.  The compiler
+places those waits for ``__syncthreads()``; for a barrier at the head of a
+loop whose last statement writes LDS it has left the wait out (it judged the
+head before it knew the loop's end).  ``barrier_hazards`` counts the LDS
+accesses in flight along the control-flow graph (they complete in order) and
+reports barriers reached with any.
 """
 
 import re
@@ -153,6 +164,58 @@ def check_kernel(body):
         _transfer(b, IN[b["name"]], bad)
     nload = sum(1 for it in items if it[0] == "asm" for t in it[1] if t.startswith("buffer_load"))
     return nload, bad
+
+
+_LGKM = re.compile(r"lgkmcnt\((\d+)\)")
+_MANY = 64  # the counter holds fewer
+
+
+def _lds_in_flight(block, n, report=None):
+    for it in block["items"]:
+        for t in it[1] if it[0] == "asm" else [it[1]]:
+            op = t.split()[0] if t else ""
+            if op.startswith("ds_") and not op.startswith(("ds_bpermute", "ds_permute", "ds_swizzle", "ds_nop")):
+                n = min(n + 1, _MANY)
+            elif op == "s_waitcnt":
+                m = _LGKM.search(t)
+                if m or re.fullmatch(r"s_waitcnt\s+(0|0x0)", t):
+                    n = min(n, int(m.group(1)) if m else 0)
+            elif op == "s_barrier" and n and report is not None:
+                report.append((it[2], n))
+    return n
+
+
+def barrier_hazards(body):
+    """[(line, most LDS accesses in flight)] of the barriers reached with any."""
+    blocks = _blocks(_items(body))
+    byname = {b["name"]: b for b in blocks}
+    IN = {b["name"]: 0 for b in blocks}
+    todo = list(blocks)
+    while todo:
+        b = todo.pop()
+        out = _lds_in_flight(b, IN[b["name"]])
+        for sname in b["succ"]:
+            if sname in byname and out > IN[sname]:
+                IN[sname] = out
+                todo.append(byname[sname])
+    bad = []
+    for b in blocks:
+        _lds_in_flight(b, IN[b["name"]], bad)
+    return bad
+
+
+def check_barriers(path, pattern="5ddilu"):
+    """Raise RuntimeError naming the first violations; return the count of the
+    library's own kernels with barriers."""
+    errors, count = [], 0
+    for name, body in kernel_bodies(open(path).read(), pattern).items():
+        if any(line.strip().startswith("s_barrier") for line in body):
+            count += 1
+            for line, n in barrier_hazards(body)[:2]:
+                errors.append(f"{name}: line {line}: s_barrier with {n} LDS accesses in flight")
+    if errors:
+        raise RuntimeError(f"LDS barrier check failed ({len(errors)}):\n  " + "\n  ".join(errors[:20]))
+    return count
 
 
 def check_file(path, pattern="k_dd_apply_slots"):

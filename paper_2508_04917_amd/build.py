@@ -30,8 +30,8 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-# Sources whose device assembly is checked after compilation (their kernels
-# schedule loads by hand; see asmcheck.py).
+# Sources whose kernels schedule loads by hand; the device assembly of all is
+# checked for LDS accesses in flight at barriers (see asmcheck.py).
 CHECKED = ("apply.hip",)
 
 
@@ -41,12 +41,9 @@ def build(verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory(prefix="ddilu_build_") as tmp:
         for src in sources():
             name = os.path.basename(src)[:-4]
-            obj = os.path.join(CSRC, name + ".o")
-            cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
-            if os.path.basename(src) in CHECKED:
-                # keep the device assembly this object is made from
-                obj = os.path.join(tmp, name + ".o")
-                cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj, "-save-temps=obj"]
+            # keep the device assembly this object is made from
+            obj = os.path.join(tmp, name + ".o")
+            cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj, "-save-temps=obj"]
             if verbose:
                 print(" ".join(cmd), flush=True)
             procs.append((subprocess.Popen(cmd, cwd=tmp), src))
@@ -54,11 +51,16 @@ def build(verbose: bool = False) -> str:
         for p, src in procs:
             if p.wait() != 0:
                 raise RuntimeError(f"hipcc failed on {src}")
-        for name in CHECKED:
+        for src in sources():
+            name = os.path.basename(src)
             asm = os.path.join(tmp, f"{name[:-4]}-hip-amdgcn-amd-amdhsa-gfx950.s")
-            n = asmcheck.check_file(asm)
+            n = asmcheck.check_barriers(asm)
             if verbose:
-                print(f"{name}: {n} slot kernels pass the in-flight register check", flush=True)
+                print(f"{name}: {n} kernels pass the LDS barrier check", flush=True)
+            if name in CHECKED:
+                n = asmcheck.check_file(asm)
+                if verbose:
+                    print(f"{name}: {n} slot kernels pass the in-flight register check", flush=True)
         _link(objs, verbose)
     build_rocsparse_ref(verbose)
     return LIB
@@ -89,8 +91,6 @@ def _link(objs, verbose):
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(out, LIB)
-    for o in objs:
-        os.remove(o)
 
 
 if __name__ == "__main__":

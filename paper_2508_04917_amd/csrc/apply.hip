@@ -846,6 +846,17 @@ __device__ __forceinline__ void slot_compute(TC *__restrict__ y, const SlotRegs<
     }
 }
 
+// The barrier between levels.  The wait for the wavefront's own LDS writes is
+// written out: at the head of sweep_slots' loop the compiler left it out
+// (the write it stands for is at the loop's end), so that a wavefront could
+// read a row of the level before from LDS ahead of its write; seen where
+// several workgroups share a CU's LDS, as different solutions from run to run
+// of the apply + product launch.  The build checks every barrier (asmcheck.py).
+__device__ __forceinline__ void level_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
 __device__ __forceinline__ int2 wave_entries(const int2 *__restrict__ tab, int n, int wave, int nw, int lane,
                                              int first) {
     return tab[max(min(wave + nw * (first + lane), n - 1), 0)];
@@ -902,14 +913,14 @@ __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, i
     auto step = [&](int u, auto drain) {
         const int l = lev[u];
         if (cur < l) {
-            __syncthreads();
+            level_barrier();
             ++cur;
         }
         if (!drain || next < steps)
             fetch((u + PD) % (PD + 1));
         else
             ++next;
-        for (; cur < l; ++cur) __syncthreads();
+        for (; cur < l; ++cur) level_barrier();
         if (drain && next > steps)
             vm_wait_all();
         else
@@ -938,7 +949,7 @@ __device__ __forceinline__ void sweep_slots(TC *__restrict__ y, int64_t pbase, i
     vm_wait_all();
 #pragma unroll
     for (int u = 0; u <= PD; ++u) slot_claim(R[u]);
-    for (; cur < nlev; ++cur) __syncthreads();
+    for (; cur < nlev; ++cur) level_barrier();
 }
 
 // The tables a slot kernel walks: wave-chunks of each sweep and, per

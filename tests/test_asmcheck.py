@@ -94,3 +94,46 @@ def test_shipped_apply_kernels(tmp_path):
                     "-o", str(out)], check=True, stderr=subprocess.DEVNULL, cwd=tmp_path)
     n = asmcheck.check_file(str(out))
     assert n >= 100  # every (block size, precision, threads, slots, depth, correction) instance
+
+
+def hazards(text):
+    return asmcheck.barrier_hazards(next(iter(asmcheck.kernel_bodies(text, "_Z1kv").values())))
+
+
+WRITE = "\tds_write_b64 v0, v[2:3]\n"
+BARRIER = "\ts_barrier\n"
+
+
+def test_barrier_after_a_write():
+    assert hazards(kernel(WRITE + "\ts_waitcnt lgkmcnt(0)\n" + BARRIER)) == []
+    assert hazards(kernel(WRITE + "\ts_waitcnt vmcnt(0) lgkmcnt(0)\n" + BARRIER)) == []
+    assert hazards(kernel(WRITE + "\t;;#ASMSTART\n\ts_waitcnt lgkmcnt(0)\n\t;;#ASMEND\n" + BARRIER)) == []
+    assert [n for _, n in hazards(kernel(WRITE + BARRIER))] == [1]
+    assert [n for _, n in hazards(kernel(WRITE + WRITE + WRITE + "\ts_waitcnt lgkmcnt(2)\n" + BARRIER))] == [2]
+    # a wait for memory alone, and a read that may still be in flight
+    assert len(hazards(kernel(WRITE + "\ts_waitcnt vmcnt(0)\n" + BARRIER))) == 1
+    assert len(hazards(kernel("\tds_read_b64 v[2:3], v0\n" + BARRIER))) == 1
+
+
+def test_barrier_at_the_head_of_a_loop():
+    def body(wait):
+        return kernel(".LBB0_1:\n" + wait + BARRIER + "\tds_read_b64 v[2:3], v0\n\ts_waitcnt lgkmcnt(0)\n" + WRITE
+                      + "\ts_cmp_lt_i32 s4, s5\n\ts_cbranch_scc1 .LBB0_1\n")
+    assert hazards(body("\ts_waitcnt lgkmcnt(0)\n")) == []
+    assert len(hazards(body(""))) == 1
+
+
+@pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
+def test_barriers_of_shipped_kernels(tmp_path):
+    """Device assembly of the sources, built with the library's flags (the
+    build checks them all; apply.hip takes two minutes and is left to it)."""
+    procs = []
+    for src in B.sources():
+        if os.path.basename(src) in B.CHECKED:
+            continue
+        out = str(tmp_path / (os.path.basename(src) + ".s"))
+        procs.append((subprocess.Popen([B.HIPCC, *B.FLAGS, "--cuda-device-only", "-S", src, "-o", out],
+                                       stderr=subprocess.DEVNULL, cwd=tmp_path), out))
+    for p, out in procs:
+        assert p.wait() == 0
+    assert sum(asmcheck.check_barriers(out) for _, out in procs) >= 80
