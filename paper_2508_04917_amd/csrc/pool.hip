@@ -5,7 +5,7 @@
 // destroyed handle's buffers therefore stay with the library for the next
 // handle, up to a bound (kShare of the device's memory).  What goes back to the
 // driver: over the bound the longest unused; what has lain unused for
-// kIdleSeconds, whenever the library allocates or frees device memory (there
+// kIdle, whenever the library allocates or frees device memory (there
 // is no thread that looks while it is not called); everything when an
 // allocation of the library's fails and on dd_destroy(NULL), which a program
 // calls that wants the memory for others.
@@ -29,7 +29,7 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 constexpr size_t kShare = 16;  // at most 1/kShare of a device's memory is kept
-constexpr int kIdleSeconds = 60;
+constexpr std::chrono::seconds kIdle{60};
 
 struct Block {
     void *p;
@@ -39,6 +39,7 @@ struct Block {
 struct Device {
     std::multimap<size_t, Block> free;
     size_t held = 0, bound = 0;
+    Clock::time_point look = Clock::time_point::max();  // no block is older than kIdle before
 };
 
 struct Pool {
@@ -66,9 +67,14 @@ void take_out(Pool &P, Device &D, std::multimap<size_t, Block>::iterator it, std
 
 void take_expired(Pool &P, Device &D, std::vector<void *> &out) {
     const Clock::time_point now = Clock::now();
+    if (now <= D.look) return;  // every call of the library passes here many times
+    D.look = Clock::time_point::max();
     for (auto it = D.free.begin(); it != D.free.end();) {
         const auto next = std::next(it);
-        if (now - it->second.since > std::chrono::seconds(kIdleSeconds)) take_out(P, D, it, out);
+        if (now - it->second.since > kIdle)
+            take_out(P, D, it, out);
+        else
+            D.look = std::min(D.look, it->second.since + kIdle);
         it = next;
     }
 }
@@ -132,8 +138,10 @@ void pool_free(void *q) {
             if (hipMemGetInfo(&avail, &total) != hipSuccess) total = 0;
             D.bound = std::max<size_t>(total / kShare, 1);
         }
-        D.free.insert({s->second.first, Block{q, Clock::now()}});
+        const Clock::time_point now = Clock::now();
+        D.free.insert({s->second.first, Block{q, now}});
         D.held += s->second.first;
+        D.look = std::min(D.look, now + kIdle);
         take_expired(P, D, out);
         // over the bound the longest unused go: the largest first would give
         // back what was just freed whenever the pool is full of smaller blocks
