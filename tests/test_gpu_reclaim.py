@@ -40,9 +40,9 @@ def free():
 @pytest.fixture
 def empty_pool():
     gc.collect()
-    dd.lib().dd_destroy(None)
+    dd.dd_destroy(None)
     yield
-    dd.lib().dd_destroy(None)
+    dd.dd_destroy(None)
 
 
 def test_refactor_loop_with_unscaled_factors(empty_pool):
